@@ -31,6 +31,7 @@
 // column index j to m. The epilogue goes through LDS so that every output row
 // segment of a wave is written (and any residual or pre-activation read) as
 // one contiguous run instead of 16-byte pieces of 32 rows.
+#include <numeric>
 #include <type_traits>
 
 #include "common.h"
@@ -131,6 +132,18 @@ DEV bf16x8 read_frag(const lds_char_t* stage, int row_base, int s, int lane) {
   }
 }
 
+// Wait until at most min(later, L) tiles of LOADS load instructions each are
+// still in flight (later is uniform across the wave).
+template <int L, int LOADS>
+DEV void wait_tiles(int later) {
+  if constexpr (L <= 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (later >= L) wait_vmcnt<L * LOADS>();
+    else wait_tiles<L - 1, LOADS>(later);
+  }
+}
+
 // Kernel parameters: the product's arguments, plus the group table of a
 // grouped launch
 struct GroupedParams {
@@ -149,7 +162,7 @@ DEV int group_tiles(const GemmGroup& gr) {
 }
 
 template <int BM, int BN, int BK, int NS, bool A_T, bool B_T, int EPI, bool SEG2 = false, bool GROUPED = false>
-__global__ __launch_bounds__(64 * gemm_waves(BM, BK), (NS <= 2 ? 2 : 1)) void gemm_kernel(KParams<GROUPED> P) {
+__global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParams<GROUPED> P) {
   GemmArgs g = args_of(P);
   constexpr int NW = gemm_waves(BM, BK), WM = NW / 2;
   constexpr int WTM = BM / WM, WTN = BN / 2;   // WM x 2 waves
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), (NS <= 2 ? 2 : 1)) void ge
   constexpr int EP_BYTES = NW * 32 * EP_LD * 4;
   constexpr int SMEM = NS * STAGE > EP_BYTES ? NS * STAGE : EP_BYTES;
   static_assert(KSTEPS % 2 == 0, "fragment double buffer alternates per k-step");
-  static_assert(NS >= 2 && NS - 2 <= 3 && (NS - 2) * LOADS < 64, "ring depth / vmcnt range");
+  static_assert(NS >= 2 && (NS - 2) * LOADS < 64, "ring depth / vmcnt range");
   __shared__ __attribute__((aligned(1024))) char smem_raw[SMEM];
   lds_char_t* smem = (lds_char_t*)smem_raw;
 
@@ -173,8 +186,9 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), (NS <= 2 ? 2 : 1)) void ge
   const int wm = wave >> 1, wn = wave & 1;
 
   // Blocks are dealt round-robin to the 8 XCDs; renumber them so each XCD
-  // works through a contiguous run of tiles (n fastest), which keeps the row
-  // panel of A it reads in its own L2.
+  // works through a contiguous run of tiles (the first tiles % 8 XCDs one
+  // more than the others): n fastest, which keeps the row panel of A it reads
+  // in its own L2, or m fastest, which keeps its column panel of B there.
   // With a contraction split over 8k blocks the grid is 1-D: block b works on
   // split b % splits... arranged so that split z always lands on XCD z % 8 and
   // each XCD's L2 serves one contraction range for all of its tiles.
@@ -232,17 +246,19 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), (NS <= 2 ? 2 : 1)) void ge
       }
     }
   }
-  const int ntn = (g.N + BN - 1) / BN, ntiles = ntn * ((g.M + BM - 1) / BM);
+  const int ntn = (g.N + BN - 1) / BN, ntm = (g.M + BM - 1) / BM, ntiles = ntn * ntm;
   if constexpr (GROUPED) {
   } else if (g.splits > 1) {
     split = blockIdx.x % g.splits;
     bid = blockIdx.x / g.splits;
   } else {
     split = 0;
-    bid = blockIdx.y * gridDim.x + blockIdx.x;
-    if ((ntiles & 7) == 0) bid = (bid & 7) * (ntiles >> 3) + (bid >> 3);
+    const int b = blockIdx.y * gridDim.x + blockIdx.x, x = b & 7;
+    bid = x * (ntiles >> 3) + min(x, ntiles & 7) + (b >> 3);
   }
-  const int m0 = (bid / ntn) * BM, n0 = (bid % ntn) * BN;
+  const bool m_fast = !GROUPED && !A_T && g.m_fast;
+  const int inner = m_fast ? ntm : ntn, t_out = bid / inner, t_in = bid - t_out * inner;
+  const int m0 = (m_fast ? t_in : t_out) * BM, n0 = (m_fast ? t_out : t_in) * BN;
 
   const int kbeg = split * g.k_chunk;
   const int kend = min(g.K, kbeg + g.k_chunk);
@@ -308,13 +324,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), (NS <= 2 ? 2 : 1)) void ge
   };
   // a tile has landed once at most the loads of the `later` tiles issued
   // after it are outstanding (loads complete in issue order)
-  auto wait_later = [&](int later) {
-    constexpr int L3 = NS - 2 >= 3 ? 3 : 0, L2 = NS - 2 >= 2 ? 2 : 0;
-    if (L3 && later >= 3) wait_vmcnt<L3 * LOADS>();
-    else if (L2 && later >= 2) wait_vmcnt<L2 * LOADS>();
-    else if (later >= 1) wait_vmcnt<LOADS>();
-    else wait_vmcnt<0>();
-  };
+  auto wait_later = [&](int later) { wait_tiles<NS - 2, LOADS>(later); };
 
   // Bias-gradient partial sums of a weight gradient: row m of A (dY^T) summed
   // over this workgroup's share of the contraction, from the A fragments the
@@ -707,40 +717,46 @@ hipError_t launch_grouped_t(const GemmGroupedArgs& gg, hipStream_t s) {
 }
 
 // Non-transposed A with an optional second contraction segment and output scale.
-template <int BM, int BN, int BK, bool B_T>
+template <int BM, int BN, int BK, int NS, bool B_T>
 hipError_t launch_bf16(const GemmArgs& g, hipStream_t s) {
   const bool scale = g.alpha != 0.0f && g.alpha != 1.0f;
   if (g.K2 > 0) {
     if (scale) return hipErrorInvalidValue;
-    return g.residual ? launch_t<BM, BN, BK, 2, false, B_T, EPI_BF16_RES, true>(g, s)
-                      : launch_t<BM, BN, BK, 2, false, B_T, EPI_BF16, true>(g, s);
+    return g.residual ? launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_RES, true>(g, s)
+                      : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16, true>(g, s);
   }
-  if (g.residual) return scale ? hipErrorInvalidValue : launch_t<BM, BN, BK, 2, false, B_T, EPI_BF16_RES>(g, s);
-  return scale ? launch_t<BM, BN, BK, 2, false, B_T, EPI_BF16_SCALE>(g, s)
-               : launch_t<BM, BN, BK, 2, false, B_T, EPI_BF16>(g, s);
+  if (g.residual) return scale ? hipErrorInvalidValue : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_RES>(g, s);
+  return scale ? launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_SCALE>(g, s)
+               : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16>(g, s);
 }
 
-template <int BM, int BN, int BK>
-hipError_t launch_cfg(const GemmArgs& g, int a_t, int b_t, int epi, hipStream_t s) {
-  if (g.K2 > 0 && (a_t || epi != EPI_BF16)) return hipErrorInvalidValue;
-  if (!a_t && !b_t && epi == EPI_BF16) return launch_bf16<BM, BN, BK, false>(g, s);
-  if (!a_t && !b_t && epi == EPI_GELU) return launch_t<BM, BN, BK, 2, false, false, EPI_GELU>(g, s);
-  if (!a_t && !b_t && epi == EPI_CE_STATS) return launch_t<BM, BN, BK, 2, false, false, EPI_CE_STATS>(g, s);
-  if (!a_t && !b_t && epi == EPI_CE_GRAD) return launch_t<BM, BN, BK, 2, false, false, EPI_CE_GRAD>(g, s);
-  if (!a_t && b_t && epi == EPI_BF16) return launch_bf16<BM, BN, BK, true>(g, s);
-  if (!a_t && b_t && epi == EPI_GELU_BWD) return launch_t<BM, BN, BK, 2, false, true, EPI_GELU_BWD>(g, s);
-  if (!a_t && b_t && epi == EPI_SWIGLU_BWD) return launch_t<BM, BN, BK, 2, false, true, EPI_SWIGLU_BWD>(g, s);
-  if (!a_t && !b_t && epi == EPI_SWIGLU) {
-    if constexpr (BN == 128) return launch_t<BM, BN, BK, 2, false, false, EPI_SWIGLU>(g, s);
+// Every product with A not transposed.
+template <int BM, int BN, int BK, int NS>
+hipError_t launch_cfg(const GemmArgs& g, int b_t, int epi, hipStream_t s) {
+  if (g.K2 > 0 && epi != EPI_BF16) return hipErrorInvalidValue;
+  if (!b_t && epi == EPI_BF16) return launch_bf16<BM, BN, BK, NS, false>(g, s);
+  if (!b_t && epi == EPI_GELU) return launch_t<BM, BN, BK, NS, false, false, EPI_GELU>(g, s);
+  if (!b_t && epi == EPI_CE_STATS) return launch_t<BM, BN, BK, NS, false, false, EPI_CE_STATS>(g, s);
+  if (!b_t && epi == EPI_CE_GRAD) return launch_t<BM, BN, BK, NS, false, false, EPI_CE_GRAD>(g, s);
+  if (b_t && epi == EPI_BF16) return launch_bf16<BM, BN, BK, NS, true>(g, s);
+  if (b_t && epi == EPI_GELU_BWD) return launch_t<BM, BN, BK, NS, false, true, EPI_GELU_BWD>(g, s);
+  if (b_t && epi == EPI_SWIGLU_BWD) return launch_t<BM, BN, BK, NS, false, true, EPI_SWIGLU_BWD>(g, s);
+  if (!b_t && epi == EPI_SWIGLU) {
+    if constexpr (BN == 128) return launch_t<BM, BN, BK, NS, false, false, EPI_SWIGLU>(g, s);
     return hipErrorInvalidValue;
   }
   // products with few output tiles and a long contraction, split into fp32 slices
-  if (!a_t && b_t && epi == EPI_F32 && !g.accumulate) return launch_t<BM, BN, BK, 2, false, true, EPI_F32>(g, s);
-  if (!a_t && !b_t && epi == EPI_F32 && !g.accumulate) return launch_t<BM, BN, BK, 2, false, false, EPI_F32>(g, s);
-  if (a_t && b_t && epi == EPI_F32)
-    return g.accumulate ? launch_t<BM, BN, BK, 2, true, true, EPI_F32_ACC>(g, s)
-                        : launch_t<BM, BN, BK, 2, true, true, EPI_F32>(g, s);
+  if (b_t && epi == EPI_F32 && !g.accumulate) return launch_t<BM, BN, BK, NS, false, true, EPI_F32>(g, s);
+  if (!b_t && epi == EPI_F32 && !g.accumulate) return launch_t<BM, BN, BK, NS, false, false, EPI_F32>(g, s);
   return hipErrorInvalidValue;
+}
+
+// Weight gradients: both operands transposed, fp32 output.
+template <int BM, int BN, int BK>
+hipError_t launch_dw(const GemmArgs& g, int b_t, int epi, hipStream_t s) {
+  if (!b_t || epi != EPI_F32 || g.K2 > 0) return hipErrorInvalidValue;
+  return g.accumulate ? launch_t<BM, BN, BK, 2, true, true, EPI_F32_ACC>(g, s)
+                      : launch_t<BM, BN, BK, 2, true, true, EPI_F32>(g, s);
 }
 
 }  // namespace
@@ -763,35 +779,98 @@ hipError_t launch_cfg(const GemmArgs& g, int a_t, int b_t, int epi, hipStream_t 
 // models) take 256 x 128 tiles when they give at least 512 of them, else
 // 128 x 128, 64-deep except for weight gradients (the Qwen3-shaped step:
 // input gradients -17 %, forward products -4 % against 32-deep stages).
-GemmConfig gemm_config(int M, int N, int a_t, int b_t, int epi) {
+static GemmConfig gemm_config_full(int M, int N, int a_t, int b_t, int epi) {
   // the fused SwiGLU pairs the two 32-column fragments of a wave: 128-wide tiles
   if (epi == EPI_SWIGLU)
-    return (M >= 256 && (long)((M + 255) / 256) * (N / 128) >= 512) ? GemmConfig{256, 128, 32} : GemmConfig{128, 128, 64};
+    return (M >= 256 && (long)((M + 255) / 256) * (N / 128) >= 512) ? GemmConfig{256, 128, 32, 2}
+                                                                    : GemmConfig{128, 128, 64, 2};
   if (N >= 192 && N % 192 == 0) {
     if (a_t) {
-      if (M >= 192 && M % 192 == 0) return {192, 192, 32};
-      if (M >= 128) return {128, 192, 32};
+      if (M >= 192 && M % 192 == 0) return {192, 192, 32, 2};
+      if (M >= 128) return {128, 192, 32, 2};
     } else {
-      if (M >= 256 && b_t && epi == EPI_BF16) return {256, 192, 64};
+      if (M >= 256 && b_t && epi == EPI_BF16) return {256, 192, 64, 2};
       const long tiles256 = (long)((M + 255) / 256) * (N / 192);
-      if (M >= 256 && epi == EPI_BF16 && tiles256 >= 1024 && tiles256 < 8192) return {256, 192, 64};
-      if (M >= 256 && (epi == EPI_GELU || tiles256 >= 8192)) return {256, 192, 32};
-      if (M >= 128) return {128, 192, 64};
+      if (M >= 256 && epi == EPI_BF16 && tiles256 >= 1024 && tiles256 < 8192) return {256, 192, 64, 2};
+      if (M >= 256 && (epi == EPI_GELU || tiles256 >= 8192)) return {256, 192, 32, 2};
+      if (M >= 128) return {128, 192, 64, 2};
     }
   }
   // 256-row tiles only when they still give two workgroups per CU (a
   // workgroup alone on a CU keeps its MFMA pipe about half busy)
-  if (M >= 256 && N >= 128 && N % 128 == 0 && (long)((M + 255) / 256) * (N / 128) >= 512) return {256, 128, 32};
-  return {128, 128, a_t ? 32 : 64};
+  if (M >= 256 && N >= 128 && N % 128 == 0 && (long)((M + 255) / 256) * (N / 128) >= 512) return {256, 128, 32, 2};
+  return {128, 128, a_t ? 32 : 64, 2};
 }
 
-int gemm_ce_parts(int M, int N) {
-  const GemmConfig c = gemm_config(M, N, 0, 0, EPI_CE_STATS);
+static long config_tiles(const GemmConfig& c, int M, int N) {
+  return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+}
+
+// Products (A not transposed) whose tiles of the configuration above would
+// number fewer than the 256 CUs. A workgroup alone on its CU draws its
+// operands at about 60 GB/s however many loads it keeps in flight, so such a
+// product takes the time of one workgroup's operand bytes: smaller tiles
+// spread the same product over more CUs (64 x 64 and 64 x 128 tiles with
+// deeper rings, still two workgroups per CU), and a contraction split
+// spreads it further. Estimated time of one launch: base + (64-deep k-tiles
+// per workgroup) x t1 while every workgroup has a CU to itself, x t2 when
+// two share one; fitted to timings at 64 to 4096 rows, widths 768 to 3072
+// and contractions 768 to 3072. Measured (us): 203 x 768 x 768 12.7 -> 5.6,
+// 203 x 768 x 3072 36.7 -> 14.0 (5.6 split 8 ways), 1024 x 3072 x 768
+// 14.3 -> 10.8, 1024 x 768 x 3072 37.7 -> 14.4, 4096 x 768 x 3072
+// 38.1 -> 29.4. Products of 256 to 511 tiles were timed too: the larger tiles
+// stay ahead there (4096 x 2304 x 768: 22.1 against 25.7).
+struct SmallTile {
+  GemmConfig c;
+  double base, t1, t2;
+};
+constexpr int M_FAST_BYTES = 3 << 20;
+static const SmallTile SMALL_TILES[] = {{{64, 64, 64, 4}, 2.6, 0.245, 0.42},
+                                        {{64, 128, 64, 3}, 2.7, 0.385, 0.62},
+                                        {{128, 128, 64, 2}, 3.5, 0.65, 1.12},
+                                        {{128, 192, 64, 2}, 3.9, 0.74, 1.6}};
+
+static double small_tile_us(const SmallTile& t, long tiles, int ktiles) {
+  return t.base + ktiles * (tiles <= 256 ? t.t1 : t.t2);
+}
+
+static bool small_tile_ok(const SmallTile& t, int N, int epi, int mult) {
+  if (epi == EPI_SWIGLU && t.c.bn != 128) return false;
+  if (t.c.bn == 192 && (N < 192 || N % 192)) return false;
+  return mult % t.c.bn == 0;
+}
+
+// mult: output columns that a tile must not straddle the multiples of (0: none)
+static GemmConfig gemm_config_for(int M, int N, int K, int a_t, int b_t, int epi, int mult) {
+  GemmConfig c = gemm_config_full(M, N, a_t, b_t, epi);
+  if (mult % c.bn)
+    c = (M >= 256 && (long)((M + 255) / 256) * ((N + 127) / 128) >= 512) ? GemmConfig{256, 128, 32, 2}
+                                                                        : GemmConfig{128, 128, 64, 2};
+  if (a_t || config_tiles(c, M, N) >= 256) return c;
+  double best = 0.0;
+  for (const SmallTile& t : SMALL_TILES) {
+    const long tiles = config_tiles(t.c, M, N);
+    if (tiles > 512 || !small_tile_ok(t, N, epi, mult)) continue;
+    const double us = small_tile_us(t, tiles, (K + 63) / 64);
+    if (best == 0.0 || us < best) {
+      best = us;
+      c = t.c;
+    }
+  }
+  return c;
+}
+
+GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi) {
+  return gemm_config_for(M, N, K, a_t, b_t, epi, 0);
+}
+
+int gemm_ce_parts(int M, int N, int K) {
+  const GemmConfig c = gemm_config(M, N, K, 0, 0, EPI_CE_STATS);
   return ((N + c.bn - 1) / c.bn) * 2;
 }
 
 int gemm_bias_parts(int M, int N, int splits) {
-  const GemmConfig c = gemm_config(M, N, 1, 1, EPI_F32);
+  const GemmConfig c = gemm_config(M, N, 0, 1, 1, EPI_F32);
   return (splits < 1 ? 1 : splits) * ((N + c.bn - 1) / c.bn) * 2;
 }
 
@@ -842,30 +921,38 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
     for (int i = 0; i < 2; ++i)
       if (g.b_bound[i] < 0 || g.b_bound[i] % 128) return hipErrorInvalidValue;
   }
-  GemmConfig c = gemm_config(g.M, g.N, a_t, b_t, epi);
   // a tile's output columns must lie within one block of the second segment
-  const bool bounded = g.K2 > 0 && (g.a2_bound[0] > 0 || g.a2_bound[1] > 0);
-  if (bounded) {
-    for (int i = 0; i < 2; ++i)
+  int mult = 0;
+  if (g.K2 > 0) {
+    for (int i = 0; i < 2; ++i) {
       if (g.a2_bound[i] < 0 || g.a2_bound[i] % 128) return hipErrorInvalidValue;
-    if ((g.a2_bound[0] % c.bn) || (g.a2_bound[1] % c.bn))
-      c = (g.M >= 256 && (long)((g.M + 255) / 256) * ((g.N + 127) / 128) >= 512) ? GemmConfig{256, 128, 32}
-                                                                                  : GemmConfig{128, 128, 64};
+      mult = std::gcd(mult, g.a2_bound[i]);
+    }
   }
+  const GemmConfig c = gemm_config_for(g.M, g.N, g.K + (g.K2 > 0 ? g.K2 : 0), a_t, b_t, epi, mult);
   // an output row block must not straddle a B column-offset bound
   if (g.b_step != 0 && ((g.b_bound[0] % c.bm) || (g.b_bound[1] % c.bm))) return hipErrorInvalidValue;
-  if (c.bm == 192) return launch_cfg<192, 192, 32>(g, a_t, b_t, epi, s);
+  // m fastest when A is the smaller operand and stays in an XCD's 4 MB L2
+  // while the column panels of B stream past it once (203 x 50304 x 768:
+  // 37 -> 30 us, 1024 x 50304 x 768: 118 -> 84 us with 128 x 192 tiles)
+  g.m_fast = !a_t && g.splits <= 1 && g.M < g.N && (size_t)g.M * g.K * 2 <= (size_t)M_FAST_BYTES;
+  if (a_t) {
+    if (c.bm == 192) return launch_dw<192, 192, 32>(g, b_t, epi, s);
+    if (c.bn == 192) return launch_dw<128, 192, 32>(g, b_t, epi, s);
+    if (c.bm == 256) return launch_dw<256, 128, 32>(g, b_t, epi, s);
+    return launch_dw<128, 128, 32>(g, b_t, epi, s);
+  }
+  if (c.bm == 64) {
+    if (c.bn == 64) return launch_cfg<64, 64, 64, 4>(g, b_t, epi, s);
+    return launch_cfg<64, 128, 64, 3>(g, b_t, epi, s);
+  }
   if (c.bm == 256 && c.bn == 192) {
-    if (c.bk == 64) return launch_cfg<256, 192, 64>(g, a_t, b_t, epi, s);
-    return launch_cfg<256, 192, 32>(g, a_t, b_t, epi, s);
+    if (c.bk == 64) return launch_cfg<256, 192, 64, 2>(g, b_t, epi, s);
+    return launch_cfg<256, 192, 32, 2>(g, b_t, epi, s);
   }
-  if (c.bm == 128 && c.bn == 192) {
-    if (c.bk == 64) return launch_cfg<128, 192, 64>(g, a_t, b_t, epi, s);
-    return launch_cfg<128, 192, 32>(g, a_t, b_t, epi, s);
-  }
-  if (c.bm == 256) return launch_cfg<256, 128, 32>(g, a_t, b_t, epi, s);
-  if (c.bk == 64) return launch_cfg<128, 128, 64>(g, a_t, b_t, epi, s);
-  return launch_cfg<128, 128, 32>(g, a_t, b_t, epi, s);
+  if (c.bm == 256) return launch_cfg<256, 128, 32, 2>(g, b_t, epi, s);
+  if (c.bn == 192) return launch_cfg<128, 192, 64, 2>(g, b_t, epi, s);
+  return launch_cfg<128, 128, 64, 2>(g, b_t, epi, s);
 }
 
 // One tile shape for every group: 192 x 192 when all of them are multiples of

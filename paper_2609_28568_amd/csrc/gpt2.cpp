@@ -86,7 +86,7 @@ const bool kDecay[K_NKIND] = {true, true, false, false, true, false, true, false
 // contraction splits for a weight-gradient GEMM with an M x N output
 // output tiles of the weight-gradient GEMM (the tile shape gemm.hip picks)
 long dw_tiles(int M, int N) {
-  const GemmConfig c = gemm_config(M, N, 1, 1, EPI_F32);
+  const GemmConfig c = gemm_config(M, N, 0, 1, 1, EPI_F32);
   return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
 }
 
@@ -126,13 +126,13 @@ struct DwTail {
 DwTail dw_tail(const Dims& d, int M, int N) {
   DwTail t{M, 1, 0};
   constexpr long ROUND = 512;
-  const GemmConfig c = gemm_config(M, N, 1, 1, EPI_F32);
+  const GemmConfig c = gemm_config(M, N, 0, 1, 1, EPI_F32);
   const long tm = (M + c.bm - 1) / c.bm, tn = (N + c.bn - 1) / c.bn, tiles = tm * tn;
   if (tiles < ROUND || tiles % ROUND == 0 || tiles % ROUND > ROUND / 2 || ROUND % tn != 0) return t;
   if (M % c.bm != 0 || N % c.bn != 0) return t;
   const int m_main = (int)(tiles / ROUND * ROUND / tn) * c.bm;
   const int m_rest = M - m_main;
-  const GemmConfig cr = gemm_config(m_rest, N, 1, 1, EPI_F32);
+  const GemmConfig cr = gemm_config(m_rest, N, 0, 1, 1, EPI_F32);
   if (m_rest % cr.bm != 0 || N % cr.bn != 0) return t;
   const long rest_tiles = (long)(m_rest / cr.bm) * (N / cr.bn);
   int want = (int)(ROUND / rest_tiles);
@@ -298,7 +298,7 @@ WsLayout ws_layout(const Dims& d) {
   const GemmGroupedArgs gg = dw_groups(d);
   w.gbs_qkv = o; o += align_up((size_t)gemm_grouped_bias_parts(gg, G_QKV) * d.L * 3 * C * 4);
   w.gbs_fc = o; o += align_up((size_t)gemm_grouped_bias_parts(gg, G_FC) * d.L * F * 4);
-  w.ce_stats = o; o += align_up(BT * (size_t)gemm_ce_parts((int)BT, d.Vp) * 8);
+  w.ce_stats = o; o += align_up(BT * (size_t)gemm_ce_parts((int)BT, d.Vp, d.C) * 8);
   w.ce_tlogit = o; o += align_up(BT * 4);
   w.ce_lse = o; o += align_up(BT * 4);
   w.total = o;
@@ -557,7 +557,7 @@ gpt2_status head_and_loss(Model* m, const int32_t* d_targets, float grad_scale, 
     g.ce_targets = d_targets; g.ce_stats = m->wsf(m->ws.ce_stats); g.ce_tlogit = m->wsf(m->ws.ce_tlogit);
     g.ce_lse = m->wsf(m->ws.ce_lse); g.ce_V = d.V; g.ce_scale = grad_scale;
     TRY(m->run(GPT2_K_GEMM_FWD, head_fl, 0.0, [&] { return launch_gemm(g, 0, 0, EPI_CE_STATS, m->stream); }));
-    const int parts = gemm_ce_parts(BT, d.Vp);
+    const int parts = gemm_ce_parts(BT, d.Vp, C);
     TRY(m->run(GPT2_K_CROSS_ENTROPY, 0.0, 8.0 * BT * parts + 16.0 * BT, [&] {
       return launch_ce_combine(g.ce_stats, parts, g.ce_tlogit, d_targets, d.V, m->wsf(m->ws.ce_lse), m->losses(), BT,
                                m->id_flag(), m->stream);

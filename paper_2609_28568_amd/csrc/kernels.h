@@ -73,7 +73,7 @@ struct GemmArgs {
   // targets outside [0, ce_V) read column 0):
   //   EPI_CE_STATS writes no C: for each row, per wave-column slice of each
   //     tile, the max and the sum of exp(logit - max) over its real columns
-  //     into ce_stats [M][gemm_ce_parts(N)] (float2), and the target's logit
+  //     into ce_stats [M][gemm_ce_parts(M, N, K)] (float2), and the target's logit
   //     into ce_tlogit [M];
   //   EPI_CE_GRAD writes C = bf16((exp(logit - ce_lse[m]) - [n == target])
   //     * ce_scale) on real columns, 0 on the others.
@@ -83,6 +83,9 @@ struct GemmArgs {
   const float* ce_lse;
   int ce_V;
   float ce_scale;
+  // order of the output tiles: 0 the column tiles of a row panel one after
+  // the other, 1 the row tiles of a column panel
+  int m_fast;
 };
 
 // Grouped weight gradients: launch_gemm_grouped runs, in one launch, every
@@ -125,18 +128,19 @@ hipError_t launch_gemm_grouped(const GemmGroupedArgs& g, hipStream_t s);
 // depends only on the groups' M and N
 int gemm_grouped_bias_parts(const GemmGroupedArgs& g, int i);
 
-// Block tile (bm x bn, contraction depth bk per stage) the GEMM uses for an
-// M x N product with the given operand orientation and epilogue.
-struct GemmConfig { int bm, bn, bk; };
-GemmConfig gemm_config(int M, int N, int a_t, int b_t, int epi);
+// Block tile (bm x bn, contraction depth bk per stage, ns stages) the GEMM
+// uses for an M x N product over K with the given operand orientation and
+// epilogue (K does not enter for a transposed A).
+struct GemmConfig { int bm, bn, bk, ns; };
+GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi);
 // Plan a contraction split of K into about `want` pieces: writes the chunk
 // length (a multiple of the 64-wide k tile) and returns the split count.
 int gemm_split_plan(int K, int want, int* k_chunk);
 // Partial rows a weight-gradient GEMM writes into GemmArgs::bsum
 int gemm_bias_parts(int M, int N, int splits);
 hipError_t launch_gemm(const GemmArgs& g, int a_t, int b_t, int epi, hipStream_t s);
-// float2 partials per row that EPI_CE_STATS writes for an M x N product
-int gemm_ce_parts(int M, int N);
+// float2 partials per row that EPI_CE_STATS writes for an M x N product over K
+int gemm_ce_parts(int M, int N, int K);
 // Combine the EPI_CE_STATS partials of each row: lse[r] = log-sum-exp of the
 // real columns, losses[r] = lse[r] - tlogit[r]; targets outside [0, V) set
 // bit ID_BAD_TARGET of *bad (when not null).

@@ -1,0 +1,54 @@
+"""The tile choice of the products on one 768-wide block, forward and
+backward, against the oracle: token counts at the edges of the 64-row tiles,
+at the sizes where the choice changes (64 x 64, 64 x 128, 128 x 128,
+128 x 192, 256-row tiles), and with ragged last tiles."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_28568_amd import synth
+from tests.util import REL_L2, oracle_config, rel_l2, workload
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _np(t):
+    return t.float().cpu().numpy()
+
+
+# (B, T): 1 row, 63..65 (one 64-row tile and its edges), 203, 705 and 1089
+# (64 x 128 and 128-row tiles with a one-row tail), 2050, and 16 x 1009 (the
+# 256-row tiles, ragged; only the last sequence goes through the oracle)
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (1, 64), (5, 13), (1, 203), (1, 705), (3, 363), (2, 1025), (16, 1009)])
+def test_block_against_oracle(B, T):
+    from paper_2609_28568_amd import binding
+    w = workload("tiny", n_layer=1, n_head=12, d_model=768, d_ff=3072, vocab=64, vocab_padded=64, max_seq_len=T, B=B,
+                 T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=71), seed=72)
+    x, dy = synth.block_inputs(w, seed=73)
+    b0 = max(0, B - 3)   # sequences b0.. carry gradient and are checked
+    x3, dy3 = x.reshape(B, T, 768), dy.reshape(B, T, 768)
+    dy3[:b0] = 0.0
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    tx, tdy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, dy))
+    out, dx = torch.empty_like(tx), torch.empty_like(tx)
+    print(f"block {B} x {T}", flush=True)
+    m.block_forward(0, tx, out)
+    m.block_backward(0, tdy, dx)
+    g = m.to_dict("grads")
+    out, dx = _np(out).reshape(B, T, 768), _np(dx).reshape(B, T, 768)
+    m.close()
+    ocfg = oracle_config(w)
+    y, cache = oracle.block_forward(x3[b0:], p, 0, ocfg)
+    grads = oracle.zero_grads(p)
+    ref = oracle.block_backward(dy3[b0:], cache, p, 0, ocfg, grads)
+    assert rel_l2(out[b0:], y) < REL_L2
+    assert rel_l2(dx[b0:], ref) < REL_L2
+    assert np.all(dx[:b0] == 0.0)
+    for k in ("ln1w", "ln1b", "qkvw", "qkvb", "attprojw", "attprojb", "ln2w", "ln2b", "fcw", "fcb", "fcprojw",
+              "fcprojb"):
+        # with one token the softmax is constant: its query and key gradients are exactly 0
+        e = rel_l2(g[k], grads[k])
+        assert e < REL_L2, (k, e)
