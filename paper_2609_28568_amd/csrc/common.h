@@ -73,6 +73,27 @@ DEV floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Four consecutive elements of a product left as n fp32 slices (stride
+// elements apart), summed in slice order with four loads in flight.
+DEV float4 sum_slices(const float* p, int n, size_t stride) {
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  int k = 0;
+  for (; k + 4 <= n; k += 4) {
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(p + (size_t)(k + j) * stride);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w;
+    }
+  }
+  for (; k < n; ++k) {
+    const float4 v = *reinterpret_cast<const float4*>(p + (size_t)k * stride);
+    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+  }
+  return a;
+}
+
 // Transpose two 4-byte words holding (r0c0,r0c1) and (r1c0,r1c1) into
 // (r0c0,r1c0) and (r0c1,r1c1).
 DEV uint32_t lo_pair(uint32_t r0, uint32_t r1) { return (r0 & 0xffffu) | (r1 << 16); }

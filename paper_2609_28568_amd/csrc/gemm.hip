@@ -260,11 +260,11 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   const int inner = m_fast ? ntm : ntn, t_out = bid / inner, t_in = bid - t_out * inner;
   const int m0 = (m_fast ? t_in : t_out) * BM, n0 = (m_fast ? t_out : t_in) * BN;
 
-  const int kbeg = split * g.k_chunk;
-  const int kend = min(g.K, kbeg + g.k_chunk);
-  // k-tiles of the first segment, then (SEG2) those of the second
-  const int nk1 = (kend - kbeg + BK - 1) / BK;
-  const int nk = SEG2 ? nk1 + g.K2 / BK : nk1;
+  // k-tiles of the first segment, then (SEG2) those of the second; this
+  // workgroup's split takes nk of them from kt0 on
+  const int nk1 = (g.K + BK - 1) / BK;
+  const int kt0 = split * (g.k_chunk / BK);
+  const int nk = min((SEG2 ? nk1 + g.K2 / BK : nk1) - kt0, g.k_chunk / BK);
 
   // buffer ranges: the whole operand matrices; reads past the end return 0
   const uint32_t a_rows = A_T ? (uint32_t)g.K : (uint32_t)g.M;
@@ -286,10 +286,11 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   const int bcol = g.b_step * ((g.b_bound[0] > 0 && m0 >= g.b_bound[0]) + (g.b_bound[1] > 0 && m0 >= g.b_bound[1]));
 
   auto stage = [&](int kt) { return smem + (kt % NS) * STAGE; };
-  auto issue = [&](int kt) {
-    lds_char_t* st = stage(kt);
+  auto issue = [&](int kti) {
+    lds_char_t* st = stage(kti);
+    const int kt = kt0 + kti;
     if (!SEG2 || kt < nk1) {
-      const int k0 = kbeg + kt * BK;
+      const int k0 = kt * BK;
       issue_tile<BM, BK, A_T, NW>(ra, g.lda, m0, k0, st, wave, lane);
       if constexpr (EPI == EPI_SWIGLU)
         issue_tile<BN, BK, B_T, NW, true>(rb, g.ldb, n0 / 2, k0, st + A_BYTES, wave, lane, g.N / 2);
@@ -733,7 +734,15 @@ hipError_t launch_bf16(const GemmArgs& g, hipStream_t s) {
 // Every product with A not transposed.
 template <int BM, int BN, int BK, int NS>
 hipError_t launch_cfg(const GemmArgs& g, int b_t, int epi, hipStream_t s) {
-  if (g.K2 > 0 && epi != EPI_BF16) return hipErrorInvalidValue;
+  if (g.K2 > 0 && epi != EPI_BF16) {
+    // with a second segment, the bf16 products and their fp32 slices only
+    if constexpr (BM <= 128) {
+      if (epi == EPI_F32 && g.splits > 1)
+        return b_t ? launch_t<BM, BN, BK, NS, false, true, EPI_F32, true>(g, s)
+                   : launch_t<BM, BN, BK, NS, false, false, EPI_F32, true>(g, s);
+    }
+    return hipErrorInvalidValue;
+  }
   if (!b_t && epi == EPI_BF16) return launch_bf16<BM, BN, BK, NS, false>(g, s);
   if (!b_t && epi == EPI_GELU) return launch_t<BM, BN, BK, NS, false, false, EPI_GELU>(g, s);
   if (!b_t && epi == EPI_CE_STATS) return launch_t<BM, BN, BK, NS, false, false, EPI_CE_STATS>(g, s);
@@ -840,8 +849,9 @@ static bool small_tile_ok(const SmallTile& t, int N, int epi, int mult) {
   return mult % t.c.bn == 0;
 }
 
-// mult: output columns that a tile must not straddle the multiples of (0: none)
-static GemmConfig gemm_config_for(int M, int N, int K, int a_t, int b_t, int epi, int mult) {
+// mult: output columns that a tile must not straddle the multiples of (0: none);
+// with splits > 1, K is the contraction length of one split
+static GemmConfig gemm_config_for(int M, int N, int K, int a_t, int b_t, int epi, int mult, int splits) {
   GemmConfig c = gemm_config_full(M, N, a_t, b_t, epi);
   if (mult % c.bn)
     c = (M >= 256 && (long)((M + 255) / 256) * ((N + 127) / 128) >= 512) ? GemmConfig{256, 128, 32, 2}
@@ -849,7 +859,7 @@ static GemmConfig gemm_config_for(int M, int N, int K, int a_t, int b_t, int epi
   if (a_t || config_tiles(c, M, N) >= 256) return c;
   double best = 0.0;
   for (const SmallTile& t : SMALL_TILES) {
-    const long tiles = config_tiles(t.c, M, N);
+    const long tiles = config_tiles(t.c, M, N) * splits;
     if (tiles > 512 || !small_tile_ok(t, N, epi, mult)) continue;
     const double us = small_tile_us(t, tiles, (K + 63) / 64);
     if (best == 0.0 || us < best) {
@@ -861,7 +871,42 @@ static GemmConfig gemm_config_for(int M, int N, int K, int a_t, int b_t, int epi
 }
 
 GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi) {
-  return gemm_config_for(M, N, K, a_t, b_t, epi, 0);
+  return gemm_config_for(M, N, K, a_t, b_t, epi, 0, 1);
+}
+
+// Splits of the contraction for a product with a non-transposed A whose
+// consumer sums fp32 slices itself (1: no split). A split product pays for
+// its slices, 8 bytes per element each (written by the product, read by the
+// consumer) instead of 4 in all; 6 TB/s is what they move at while they stay
+// in the caches. A split has to promise a quarter of the time, since near 1000
+// rows the smaller promises were not kept; products with at least 256 tiles
+// of their own are not split. Measured (us, product alone): 203 x 768 x 768
+// 5.6 -> 3.6 (4 splits), 203 x 768 x 3072 14.0 -> 5.8 (4), 1024 x 768 x 3072
+// 14.4 -> 11.1 (4, which the consumer's reads use up: not split).
+int gemm_slices(int M, int N, int K, int K2, int b_t, int* k_chunk) {
+  const int Kt = K + K2;
+  if (k_chunk) *k_chunk = (Kt + 63) / 64 * 64;
+  if (config_tiles(gemm_config_full(M, N, 0, b_t, EPI_BF16), M, N) >= 256) return 1;
+  double best = 0.0;   // 0.75 times the unsplit time, or the best split's
+  int n = 1;
+  for (int want = 1; want <= 16; ++want) {
+    int kc = 0;
+    const int sp = gemm_split_plan(Kt, want, &kc);
+    if (sp != want || (sp > 1 && kc < 128)) continue;
+    for (const SmallTile& t : SMALL_TILES) {
+      const long tiles = config_tiles(t.c, M, N) * sp;
+      if (tiles > 512 || !small_tile_ok(t, N, EPI_F32, 0)) continue;
+      const double slices = sp > 1 ? (8.0 * sp - 4.0) * M * N / 6e6 : 0.0;
+      const double us = small_tile_us(t, tiles, kc / 64) + slices;
+      if (best == 0.0 || us < best) {
+        best = us;
+        n = sp;
+        if (k_chunk) *k_chunk = kc;
+      }
+    }
+    if (want == 1) best *= 0.75;
+  }
+  return n;
 }
 
 int gemm_ce_parts(int M, int N, int K) {
@@ -891,13 +936,14 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
   if ((size_t)((a_t ? g.K : g.M) + 256) * g.lda * 2 >= (1ull << 32) ||
       (size_t)((b_t ? g.K : g.N) + 256) * g.ldb * 2 >= (1ull << 32))
     return hipErrorInvalidValue;
+  const int Kt = g.K + (g.K2 > 0 ? g.K2 : 0);   // both segments
   if (g.splits <= 1 || g.k_chunk <= 0) {
     g.splits = 1;
-    g.k_chunk = (g.K + 63) / 64 * 64;
+    g.k_chunk = (Kt + 63) / 64 * 64;
     if (g.k_chunk < 64) g.k_chunk = 64;
   } else {
     // the caller's plan: k_chunk a multiple of 64 and splits = ceil(K / k_chunk)
-    if (g.k_chunk % 64 || (long)g.k_chunk * g.splits < g.K || (long)g.k_chunk * (g.splits - 1) >= g.K)
+    if (g.k_chunk % 64 || (long)g.k_chunk * g.splits < Kt || (long)g.k_chunk * (g.splits - 1) >= Kt)
       return hipErrorInvalidValue;
     if (epi != EPI_F32) return hipErrorInvalidValue;
   }
@@ -910,7 +956,7 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
     if (epi == EPI_SWIGLU_BWD && (!b_t || g.N % 4 || !g.aux || g.ldc < 2 * g.N)) return hipErrorInvalidValue;
   }
   if (g.K2 > 0) {
-    if (g.splits > 1 || g.K % 64 || g.K2 % 64 || !g.A2 || !g.B2 || a_t) return hipErrorInvalidValue;
+    if (g.K % 64 || g.K2 % 64 || !g.A2 || !g.B2 || a_t) return hipErrorInvalidValue;
     if ((size_t)(g.M + 256) * g.lda2 * 2 >= (1ull << 32) ||
         (size_t)((b_t ? g.K2 : g.N) + 256) * g.ldb2 * 2 >= (1ull << 32))
       return hipErrorInvalidValue;
@@ -929,7 +975,7 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
       mult = std::gcd(mult, g.a2_bound[i]);
     }
   }
-  const GemmConfig c = gemm_config_for(g.M, g.N, g.K + (g.K2 > 0 ? g.K2 : 0), a_t, b_t, epi, mult);
+  const GemmConfig c = gemm_config_for(g.M, g.N, g.splits > 1 ? g.k_chunk : Kt, a_t, b_t, epi, mult, g.splits);
   // an output row block must not straddle a B column-offset bound
   if (g.b_step != 0 && ((g.b_bound[0] % c.bm) || (g.b_bound[1] % c.bm))) return hipErrorInvalidValue;
   // m fastest when A is the smaller operand and stays in an XCD's 4 MB L2

@@ -161,6 +161,9 @@ struct WsLayout {
   // groups
   size_t dres_l, dfc_l, dqkv_l, gbs_qkv, gbs_fc;
   size_t s_dres, s_dfc, s_dqkv;
+  // fp32 slices of the products that a norm consumes, when they are split
+  // (sliced_product)
+  size_t xsl;
   // the two-pass head + cross-entropy: per-row softmax statistics of every
   // head tile slice, the target logits and the log-sum-exp of each row
   size_t ce_stats, ce_tlogit, ce_lse;
@@ -275,7 +278,16 @@ WsLayout ws_layout(const Dims& d) {
   };
   bupd(3 * d.C, d.C); bupd(d.F, d.C); bupd(d.C, d.F);
   w.bsum_elems = bs;
+  // products into the residual stream: the attention and MLP-down projections,
+  // and the input gradients of MLP up, q|k|v and the head
+  size_t xs = 0;
+  auto xupd = [&](int K, int b_t) {
+    const int s = gemm_slices((int)BT, d.C, K, 0, b_t, nullptr);
+    if (s > 1) xs = std::max(xs, (size_t)s * BT * C);
+  };
+  xupd(d.C, 0); xupd(d.F, 0); xupd(d.F, 1); xupd(3 * d.C, 1); xupd(d.Vp, 1);
   size_t o = 0;
+  w.xsl = o; o += align_up(xs * 4);
   w.dres = o; o += align_up(BT * C * 2);
   w.dh = o; o += align_up(BT * C * 2);
   w.datt = o; o += align_up(BT * C * 2);
@@ -463,6 +475,21 @@ hipError_t weight_grad(Model* m, int M, int N, const bf16_t* dy, const bf16_t* x
                 });
 }
 
+// A product [BT, C] of the residual stream, A [BT, K] times B, left as fp32
+// slices for the norm that consumes it when splitting the contraction pays
+// (few rows); n = 0 and nothing launched when it does not.
+hipError_t sliced_product(Model* m, int K, const bf16_t* A, const bf16_t* B, int ldb, int b_t, double alg_flops,
+                          Slices* out) {
+  const int BT = (int)m->d.BT, C = m->d.C;
+  int kc = 0;
+  const int n = gemm_slices(BT, C, K, 0, b_t, &kc);
+  *out = {nullptr, 0};
+  if (n <= 1) return hipSuccess;
+  *out = {m->wsf(m->ws.xsl), n};
+  return gemm(m, 0, BT, C, K, A, K, 0, B, ldb, b_t, EPI_F32, m->wsf(m->ws.xsl), C, nullptr, nullptr, nullptr, nullptr,
+              0, n, (long)BT * C, kc, alg_flops);
+}
+
 hipError_t ln_fwd(Model* m, const bf16_t* x, const float* w, const float* b, bf16_t* y, float* mean, float* rstd) {
   const int BT = (int)m->d.BT, C = m->d.C;
   return m->run(GPT2_K_LAYERNORM, 0.0, 4.0 * BT * C + 8.0 * BT + 8.0 * C,
@@ -487,13 +514,14 @@ hipError_t reduce_ln_parts(Model* m) {
 
 // With slot >= 0 the partial sums go to that slot and their reduction is
 // queued for reduce_ln_parts; otherwise they are reduced at once.
-hipError_t ln_bwd(Model* m, const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, const float* w,
+// dy: the bf16 gradient, unless sl holds it as slices.
+hipError_t ln_bwd(Model* m, const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean, const float* rstd, const float* w,
                   const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* dw, float* db, float* dbias,
                   int accumulate, int slot = -1) {
   const int BT = (int)m->d.BT, C = m->d.C;
   float* part = m->wsf(m->ws.lnpart + (size_t)(slot < 0 ? 0 : slot) * m->ws.s_lnpart);
   hipError_t e = m->run(GPT2_K_LAYERNORM, 0.0, 2.0 * BT * C * (3 + has_res) + 8.0 * BT, [&] {
-    return launch_layernorm_bwd(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, BT, C, m->stream);
+    return launch_layernorm_bwd(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, BT, C, m->stream);
   });
   if (e != hipSuccess) return e;
   if (slot >= 0) {
@@ -588,6 +616,16 @@ hipError_t add_norm(Model* m, const bf16_t* res, const bf16_t* branch, bf16_t* x
   });
 }
 
+// The residual sum of a projection left as slices, and the pre-norm after it
+// (w == nullptr: the sum only).
+hipError_t slices_norm(Model* m, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
+                       const float* b, bf16_t* y, float* mean, float* rstd) {
+  const int BT = (int)m->d.BT, C = m->d.C;
+  return m->run(GPT2_K_LAYERNORM, 0.0, (6.0 + 4.0 * sl.n) * BT * C + 8.0 * BT + 8.0 * C, [&] {
+    return launch_slices_layernorm_fwd(sl, bias, res, xsum, w, b, y, mean, rstd, BT, C, m->cfg.ln_eps, m->stream);
+  });
+}
+
 // The pre-norm that follows block l's output: the next block's LN1 (into
 // activation slot a_next), or the final LayerNorm after the last block.
 struct NextNorm {
@@ -608,8 +646,9 @@ NextNorm next_norm(Model* m, int l, int a_next) {
 // in = a = l, out = l + 1 (everything kept for the backward); evaluation
 // reuses slot 0 and two residual slots. When ln1_done, the block's LN1 was
 // already computed together with the residual sum that forms its input.
-// With residual_norm 1 or 2 and next_a >= 0 the block also forms the next
-// pre-norm (next_norm) with its output and sets *next_done.
+// With residual_norm 1 or 2, or a split MLP-down projection (sliced_product),
+// and next_a >= 0 the block also forms the next pre-norm (next_norm) with its
+// output and sets *next_done.
 gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, bool ln1_done = false,
                       bool* next_done = nullptr) {
   const Dims& d = m->d;
@@ -624,7 +663,12 @@ gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, 
            3 * C, m->pf(K_QKVB) + o3C));
   AttnArgs aa = attn_args(m, a);
   TRY(m->run(GPT2_K_ATTN_FWD, attn_fwd_flops(d), 0.0, [&] { return launch_attention_fwd(aa, m->stream); }));
-  if (!fused) {
+  Slices sl{nullptr, 0};
+  if (!fused) TRY(sliced_product(m, C, m->att(a), m->pb(K_ATTPROJW) + oC * C, C, 0, 0.0, &sl));
+  if (sl.n > 0) {
+    TRY(slices_norm(m, sl, m->pf(K_ATTPROJB) + oC, m->res(in), m->xmid(a), m->pf(K_LN2W) + oC, m->pf(K_LN2B) + oC,
+                    m->ln2(a), m->ln2m(a), m->ln2r(a)));
+  } else if (!fused) {
     TRY(gemm(m, GPT2_K_GEMM_FWD, BT, C, C, m->att(a), C, 0, m->pb(K_ATTPROJW) + oC * C, C, 0, EPI_BF16, m->xmid(a),
              C, m->pf(K_ATTPROJB) + oC, m->res(in)));
     TRY(ln_fwd(m, m->xmid(a), m->pf(K_LN2W) + oC, m->pf(K_LN2B) + oC, m->ln2(a), m->ln2m(a), m->ln2r(a)));
@@ -636,7 +680,15 @@ gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, 
   }
   TRY(gemm(m, GPT2_K_GEMM_FWD, BT, F, C, m->ln2(a), C, 0, m->pb(K_FCW) + oF * C, C, 0, EPI_GELU, m->fc(a), F,
            m->pf(K_FCB) + oF, nullptr, m->gelu(a)));
-  if (!fused) {
+  sl.n = 0;
+  if (!fused) TRY(sliced_product(m, F, m->gelu(a), m->pb(K_FCPROJW) + oC * F, F, 0, 0.0, &sl));
+  if (sl.n > 0) {
+    // the sum, and the next pre-norm when there is one to form
+    NextNorm nn{};
+    if (next_a >= 0) nn = next_norm(m, l, next_a);
+    TRY(slices_norm(m, sl, m->pf(K_FCPROJB) + oC, m->xmid(a), m->res(out), nn.w, nn.b, nn.y, nn.mean, nn.rstd));
+    if (next_done) *next_done = next_a >= 0;
+  } else if (!fused) {
     TRY(gemm(m, GPT2_K_GEMM_FWD, BT, C, F, m->gelu(a), F, 0, m->pb(K_FCPROJW) + oC * F, F, 0, EPI_BF16, m->res(out),
              C, m->pf(K_FCPROJB) + oC, m->xmid(a)));
   } else {
@@ -696,9 +748,11 @@ gpt2_status block_bwd(Model* m, int l, int acc, bool fcproj_bias_done, bool writ
     TRY(weight_grad(m, C, F, gb.dres_out, m->gelu(l), m->gf(K_FCPROJW) + oC * F, acc, 0,
                     fcproj_bias_done ? nullptr : m->gf(K_FCPROJB) + oC));
   // MLP up projection
-  TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, F, gb.dfc, F, 0, m->pb(K_FCW) + oF * C, C, 1, EPI_BF16, dh, C));
+  Slices sl;
+  TRY(sliced_product(m, F, gb.dfc, m->pb(K_FCW) + oF * C, C, 1, 0.0, &sl));
+  if (sl.n == 0) TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, F, gb.dfc, F, 0, m->pb(K_FCW) + oF * C, C, 1, EPI_BF16, dh, C));
   if (!defer_dw) TRY(weight_grad(m, F, C, gb.dfc, m->ln2(l), m->gf(K_FCW) + oF * C, acc, 0, m->gf(K_FCB) + oF));
-  TRY(ln_bwd(m, dh, m->xmid(l), m->ln2m(l), m->ln2r(l), m->pf(K_LN2W) + oC, gb.dres_out, gb.dres_mid, 1,
+  TRY(ln_bwd(m, dh, sl, m->xmid(l), m->ln2m(l), m->ln2r(l), m->pf(K_LN2W) + oC, gb.dres_out, gb.dres_mid, 1,
              m->gf(K_LN2W) + oC, m->gf(K_LN2B) + oC, m->gf(K_ATTPROJB) + oC, acc, defer_dw ? 2 * l + 1 : -1));
   // attention output projection (its bias gradient came from the LayerNorm above)
   TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, C, gb.dres_mid, C, 0, m->pb(K_ATTPROJW) + oC * C, C, 1, EPI_BF16, datt, C));
@@ -707,11 +761,13 @@ gpt2_status block_bwd(Model* m, int l, int acc, bool fcproj_bias_done, bool writ
   AttnArgs aa = attn_args(m, l, gb.dqkv);
   TRY(m->run(GPT2_K_ATTN_BWD, 2.0 * attn_fwd_flops(d), 0.0, [&] { return launch_attention_bwd(aa, m->stream); }));
   // q|k|v projection
-  TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, 3 * C, gb.dqkv, 3 * C, 0, m->pb(K_QKVW) + o3C * C, C, 1, EPI_BF16, dh, C));
+  TRY(sliced_product(m, 3 * C, gb.dqkv, m->pb(K_QKVW) + o3C * C, C, 1, 0.0, &sl));
+  if (sl.n == 0)
+    TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, 3 * C, gb.dqkv, 3 * C, 0, m->pb(K_QKVW) + o3C * C, C, 1, EPI_BF16, dh, C));
   if (!defer_dw)
     TRY(weight_grad(m, 3 * C, C, gb.dqkv, m->ln1(l), m->gf(K_QKVW) + o3C * C, acc, 0, m->gf(K_QKVB) + o3C));
   float* prev_bias = (write_prev_bias && l > 0) ? m->gf(K_FCPROJB) + (size_t)(l - 1) * C : nullptr;
-  TRY(ln_bwd(m, dh, m->res(l), m->ln1m(l), m->ln1r(l), m->pf(K_LN1W) + oC, gb.dres_mid, gb.dres_in, 1,
+  TRY(ln_bwd(m, dh, sl, m->res(l), m->ln1m(l), m->ln1r(l), m->pf(K_LN1W) + oC, gb.dres_mid, gb.dres_in, 1,
              m->gf(K_LN1W) + oC, m->gf(K_LN1B) + oC, prev_bias, acc, defer_dw ? 2 * l : -1));
   return GPT2_OK;
 }
@@ -1067,11 +1123,15 @@ gpt2_status gpt2_backward(gpt2_model* m, int32_t accumulate) {
   bf16_t* dh = m->wsb(m->ws.dh);
   m->ln_jobs.count = 0;   // nothing queued from a pass that failed part-way
   // tied LM head: input gradient and the head's share of the token-table gradient
-  TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, d.Vp, m->logits(), d.Vp, 0, m->pb(K_WTE), C, 1, EPI_BF16, dh, C, nullptr,
-           nullptr, nullptr, nullptr, 0, 1, 0, 0, 2.0 * BT * (double)d.V * C));
+  const double head_fl = 2.0 * BT * (double)d.V * C;
+  Slices sl;
+  TRY(sliced_product(m, d.Vp, m->logits(), m->pb(K_WTE), C, 1, head_fl, &sl));
+  if (sl.n == 0)
+    TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, d.Vp, m->logits(), d.Vp, 0, m->pb(K_WTE), C, 1, EPI_BF16, dh, C, nullptr,
+             nullptr, nullptr, nullptr, 0, 1, 0, 0, head_fl));
   TRY(weight_grad(m, d.Vp, C, m->logits(), m->lnf(), m->gf(K_WTE), acc, d.V));
   bf16_t* dres_top = grads_of_layer(m, d.L - 1).dres_out;   // written, not read (has_res 0)
-  TRY(ln_bwd(m, dh, m->res(d.L), m->lnfm(), m->lnfr(), m->pf(K_LNFW), dres_top, dres_top, 0, m->gf(K_LNFW),
+  TRY(ln_bwd(m, dh, sl, m->res(d.L), m->lnfm(), m->lnfr(), m->pf(K_LNFW), dres_top, dres_top, 0, m->gf(K_LNFW),
              m->gf(K_LNFB), m->gf(K_FCPROJB) + (size_t)(d.L - 1) * C, acc, 2 * d.L));
   for (int l = d.L - 1; l >= 0; --l) {
     gpt2_status s = block_bwd(m, l, acc, true, true, grads_of_layer(m, l), true);

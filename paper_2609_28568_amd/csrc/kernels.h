@@ -52,8 +52,8 @@ struct GemmArgs {
   // EPI_BF16 without residual: the accumulator is multiplied by alpha before
   // the bias (0 or 1: no scaling)
   float alpha;
-  // Optional second contraction segment (K2 > 0; A not transposed, no split,
-  // K and K2 multiples of 64): C += A2 B2 over K2 more indices, A2 [M][lda2]
+  // Optional second contraction segment (K2 > 0; A not transposed, K and K2
+  // multiples of 64; a split runs over both segments as one contraction): C += A2 B2 over K2 more indices, A2 [M][lda2]
   // and B2 in B's orientation (row stride ldb2). Output columns n >=
   // a2_bound[i] (for each non-zero bound, multiples of 128) read A2 from K2
   // columns further right per bound passed, so column blocks of the output
@@ -136,6 +136,14 @@ GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi);
 // Plan a contraction split of K into about `want` pieces: writes the chunk
 // length (a multiple of the 64-wide k tile) and returns the split count.
 int gemm_split_plan(int K, int want, int* k_chunk);
+// Splits (1: none) for a product with a non-transposed A, contraction K plus a
+// second segment K2, whose consumer sums fp32 slices; writes the chunk length
+int gemm_slices(int M, int N, int K, int K2, int b_t, int* k_chunk);
+// A product left as n fp32 slices [n][rows][C] whose sum is its output
+struct Slices {
+  const float* p;
+  int n;
+};
 // Partial rows a weight-gradient GEMM writes into GemmArgs::bsum
 int gemm_bias_parts(int M, int N, int splits);
 hipError_t launch_gemm(const GemmArgs& g, int a_t, int b_t, int epi, hipStream_t s);
@@ -175,6 +183,11 @@ hipError_t launch_layernorm_fwd(const bf16_t* x, const float* w, const float* b,
 // followed by launch_layernorm_fwd gives. res == nullptr: plain LayerNorm of x.
 hipError_t launch_add_layernorm_fwd(const bf16_t* x, const bf16_t* res, bf16_t* xsum, const float* w, const float* b,
                                     bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s);
+// The same with the branch given as a product's fp32 slices: xsum = bf16(sum of
+// the slices + bias + res), y = LayerNorm(xsum); with w == nullptr xsum only.
+hipError_t launch_slices_layernorm_fwd(const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum,
+                                       const float* w, const float* b, bf16_t* y, float* mean, float* rstd, int rows,
+                                       int C, float eps, hipStream_t s);
 // out = bf16(res + x) elementwise (n % 4 == 0)
 hipError_t launch_residual_add(const bf16_t* res, const bf16_t* x, bf16_t* out, long n, hipStream_t s);
 // dres_out = (has_res ? dres_in : 0) + dx (dres_in may be dres_out; it is not
@@ -183,7 +196,8 @@ hipError_t launch_residual_add(const bf16_t* res, const bf16_t* x, bf16_t* out, 
 // dy*xhat (gain gradient), dy (shift gradient) and the new dres (the bias
 // gradient of the linear layer whose output gradient dres is).
 int layernorm_bwd_blocks(int rows);
-hipError_t launch_layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* mean,
+// dy is a bf16 row-major array, or (slices.n > 0, dy unused) fp32 slices.
+hipError_t launch_layernorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* mean,
                                 const float* rstd, const float* w, const bf16_t* dres_in, bf16_t* dres_out,
                                 int has_res, float* part, int rows, int C, hipStream_t s);
 
@@ -191,8 +205,6 @@ hipError_t launch_layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* 
 // dst[i] (fp32, n elements) = (accumulate ? dst[i] : 0) + sum_s src[s*n + i]
 hipError_t launch_reduce_slices(const float* src, int nslices, long n, float* dst, int accumulate,
                                 hipStream_t s);
-// dst[i] (bf16, n elements, n % 4 == 0) = scale * sum_s src[s*n + i]
-hipError_t launch_reduce_slices_bf16(const float* src, int nslices, long n, float scale, bf16_t* dst, hipStream_t s);
 // The same for two independent segments in one launch (n and n2 multiples of 4)
 hipError_t launch_reduce_slices2(const float* src, int nslices, long n, float* dst, const float* src2,
                                  int nslices2, long n2, float* dst2, int accumulate, hipStream_t s);
@@ -252,10 +264,14 @@ hipError_t launch_embed_gather(const int32_t* ids, const bf16_t* table, bf16_t* 
 // n = T - mask_from (mask_from = 0: every row, in place order).
 hipError_t launch_rmsnorm_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, float* rstd, int rows, int C, float eps,
                               int T, int mask_from, hipStream_t s);
+// The same over all rows of x = bf16(sum of the slices + res), which is also
+// stored to xsum; with w == nullptr xsum only
+hipError_t launch_slices_rmsnorm_fwd(const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w, bf16_t* y,
+                                     float* rstd, int rows, int C, float eps, hipStream_t s);
 // dres (=|+=) the RMSNorm input gradient (the gain is frozen) over all rows of
-// x; dy and rstd hold only the rows of positions t >= mask_from, compacted as
+// x; dy (a bf16 array, or with slices.n > 0 fp32 slices) and rstd hold only the rows of positions t >= mask_from, compacted as
 // launch_rmsnorm_fwd writes them; the other rows get a zero gradient
-hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const bf16_t* x, const float* rstd, const bf16_t* w, bf16_t* dres,
+hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* rstd, const bf16_t* w, bf16_t* dres,
                               int accumulate, int rows, int C, int T, int mask_from, hipStream_t s);
 // raw q|k|v [BT][(H + 2 Hkv) hd] -> packed q|k|v in the same layout for the
 // grouped-query attention kernels: query and key heads RMS-normalised and

@@ -2,6 +2,9 @@
 // the final norm, Figure 1). Statistics in fp32, biased variance, eps from the
 // config. One wavefront per row; each lane owns channels {4*(lane + 64*i)..+3},
 // read as 8-byte bf16 chunks.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -14,12 +17,17 @@ DEV uint2 add_rows(uint2 r, uint2 a) {
                     pack2(lo_f(r.y) + lo_f(a.y), hi_f(r.y) + hi_f(a.y)));
 }
 
-// MAXCH: 4-channel chunks per lane, C <= 256*MAXCH. With RES the row is first
-// formed as the residual sum x = bf16(res + x) (stored to xsum), and the
+// MAXCH: 4-channel chunks per lane, C <= 256*MAXCH. With SRC_RES the row is
+// first formed as the residual sum x = bf16(res + x) (stored to xsum), and the
 // normalisation then reads those rounded values, exactly as a separate
-// addition followed by this kernel would.
-template <int MAXCH, bool RES = false>
-__global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ res,
+// addition followed by this kernel would. With SRC_SLICES the branch comes as
+// fp32 slices of the projection before it (few rows: the product is split to
+// fill the chip), x = bf16(sum + bias + res), so the split costs no launch of
+// its own; w == nullptr then stops after xsum.
+constexpr int SRC_X = 0, SRC_RES = 1, SRC_SLICES = 2;
+template <int MAXCH, int SRC = SRC_X>
+__global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ x, Slices sl,
+                                                     const float* __restrict__ bias, const bf16_t* __restrict__ res,
                                                      bf16_t* __restrict__ xsum, const float* __restrict__ w,
                                                      const float* __restrict__ b, bf16_t* __restrict__ y,
                                                      float* __restrict__ mean_out, float* __restrict__ rstd_out,
@@ -36,18 +44,32 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ 
 #pragma unroll
   for (int i = 0; i < MAXCH; ++i) {
     const int c = min(4 * (lane + 64 * i), C - 4);
-    xu[i] = *reinterpret_cast<const uint2*>(xr + c);
-    if constexpr (RES) ru[i] = *reinterpret_cast<const uint2*>(res + (size_t)row * C + c);
-    wv[i] = *reinterpret_cast<const float4*>(w + c);
-    bv[i] = *reinterpret_cast<const float4*>(b + c);
+    if constexpr (SRC != SRC_SLICES) xu[i] = *reinterpret_cast<const uint2*>(xr + c);
+    if constexpr (SRC != SRC_X) ru[i] = *reinterpret_cast<const uint2*>(res + (size_t)row * C + c);
+    if (SRC != SRC_SLICES || w) {
+      wv[i] = *reinterpret_cast<const float4*>(w + c);
+      bv[i] = *reinterpret_cast<const float4*>(b + c);
+    }
   }
-  if constexpr (RES) {
+  if constexpr (SRC == SRC_SLICES) {
+    const float* sr = sl.p + (size_t)row * C;
 #pragma unroll
     for (int i = 0; i < MAXCH; ++i) {
-      xu[i] = add_rows(ru[i], xu[i]);
+      const int c = min(4 * (lane + 64 * i), C - 4);
+      const float4 t = sum_slices(sr + c, sl.n, (size_t)rows * C);
+      const float4 bb = *reinterpret_cast<const float4*>(bias + c);
+      xu[i] = make_uint2(pack2(t.x + bb.x + lo_f(ru[i].x), t.y + bb.y + hi_f(ru[i].x)),
+                         pack2(t.z + bb.z + lo_f(ru[i].y), t.w + bb.w + hi_f(ru[i].y)));
+    }
+  }
+  if constexpr (SRC != SRC_X) {
+#pragma unroll
+    for (int i = 0; i < MAXCH; ++i) {
+      if constexpr (SRC == SRC_RES) xu[i] = add_rows(ru[i], xu[i]);
       const int c = 4 * (lane + 64 * i);
       if (c < C) *reinterpret_cast<uint2*>(xsum + (size_t)row * C + c) = xu[i];
     }
+    if (SRC == SRC_SLICES && !w) return;
   }
   float v[MAXCH][4];
   float s = 0.0f;
@@ -94,8 +116,11 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ 
 // added to the residual-stream gradient read from dres_in and written to
 // dres_out (the two may be the same buffer: each row is read before it is
 // written, by the same wave). Per-block sums of dy*xhat and dy.
-template <int MAXCH>
-__global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+// With SL the upstream gradient is the sum of fp32 slices of the product before
+// it (few rows), taken unrounded.
+template <int MAXCH, bool SL>
+__global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ dy, Slices sl,
+                                                     const bf16_t* __restrict__ x,
                                                      const float* __restrict__ mean_in,
                                                      const float* __restrict__ rstd_in, const float* __restrict__ w,
                                                      const bf16_t* dres_in, bf16_t* dres_out, int has_res,
@@ -115,11 +140,13 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ 
   // Rows are software-pipelined: the next row's inputs (x, dy, the residual
   // gradient, mean, rstd) are loaded while the current row is reduced and
   // written, so each row costs one memory round trip, not two.
-  uint2 xu[MAXCH], du[MAXCH], ru[MAXCH];
+  using Dy = std::conditional_t<SL, float4, uint2>;   // four elements of dy
+  uint2 xu[MAXCH], ru[MAXCH];
+  Dy du[MAXCH];
   float mean = 0.0f, rstd = 0.0f;
-  auto load_row = [&](int row, uint2 (&xl)[MAXCH], uint2 (&dl)[MAXCH], uint2 (&rl)[MAXCH], float& ml, float& sl) {
+  auto load_row = [&](int row, uint2 (&xl)[MAXCH], Dy (&dl)[MAXCH], uint2 (&rl)[MAXCH], float& ml, float& sdl) {
     ml = mean_in[row];
-    sl = rstd_in[row];
+    sdl = rstd_in[row];
     const bf16_t* xr = x + (size_t)row * C;
     const bf16_t* dr = dy + (size_t)row * C;
     const bf16_t* rr = dres_in + (size_t)row * C;
@@ -129,7 +156,8 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ 
     for (int i = 0; i < MAXCH; ++i) {
       const int c = min(4 * (lane + 64 * i), C - 4);
       xl[i] = *reinterpret_cast<const uint2*>(xr + c);
-      dl[i] = *reinterpret_cast<const uint2*>(dr + c);
+      if constexpr (SL) dl[i] = sum_slices(sl.p + (size_t)row * C + c, sl.n, (size_t)rows * C);
+      else dl[i] = *reinterpret_cast<const uint2*>(dr + c);
       rl[i] = has_res ? *reinterpret_cast<const uint2*>(rr + c) : make_uint2(0, 0);
     }
   };
@@ -137,7 +165,8 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ 
   int row = blockIdx.x * 4 + wave;
   if (row < rows) load_row(row, xu, du, ru, mean, rstd);
   for (; row < rows; row += stride) {
-    uint2 xn[MAXCH], dn[MAXCH], rn[MAXCH];
+    uint2 xn[MAXCH], rn[MAXCH];
+    Dy dn[MAXCH];
     float mean_n = 0.0f, rstd_n = 0.0f;
     if (row + stride < rows) load_row(row + stride, xn, dn, rn, mean_n, rstd_n);
     float xh[MAXCH][4], gg[MAXCH][4];
@@ -147,7 +176,12 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16_t* __restrict__ 
       int c = 4 * (lane + 64 * i);
       if (c < C) {
         float xv[4] = {lo_f(xu[i].x), hi_f(xu[i].x), lo_f(xu[i].y), hi_f(xu[i].y)};
-        float dv[4] = {lo_f(du[i].x), hi_f(du[i].x), lo_f(du[i].y), hi_f(du[i].y)};
+        float dv[4];
+        if constexpr (SL) {
+          dv[0] = du[i].x; dv[1] = du[i].y; dv[2] = du[i].z; dv[3] = du[i].w;
+        } else {
+          dv[0] = lo_f(du[i].x); dv[1] = hi_f(du[i].x); dv[2] = lo_f(du[i].y); dv[3] = hi_f(du[i].y);
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           xh[i][e] = (xv[e] - mean) * rstd;
@@ -216,22 +250,42 @@ __global__ void residual_add_kernel(const bf16_t* __restrict__ res, const bf16_t
 }
 
 template <int MAXCH>
-hipError_t fwd_t(const bf16_t* x, const bf16_t* res, bf16_t* xsum, const float* w, const float* b, bf16_t* y,
-                 float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
-  if (res)
-    hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, true>), dim3((rows + 3) / 4), dim3(256), 0, s, x, res, xsum, w, b, y,
+hipError_t fwd_t(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
+                 const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
+  const dim3 grid((rows + 3) / 4), block(256);
+  if (sl.n > 0)
+    hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_SLICES>), grid, block, 0, s, nullptr, sl, bias, res, xsum, w, b, y,
                        mean, rstd, rows, C, eps);
+  else if (res)
+    hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_RES>), grid, block, 0, s, x, sl, nullptr, res, xsum, w, b, y, mean,
+                       rstd, rows, C, eps);
   else
-    hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, false>), dim3((rows + 3) / 4), dim3(256), 0, s, x, nullptr, nullptr, w,
-                       b, y, mean, rstd, rows, C, eps);
+    hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_X>), grid, block, 0, s, x, sl, nullptr, nullptr, nullptr, w, b, y,
+                       mean, rstd, rows, C, eps);
   return hipGetLastError();
 }
 
+hipError_t fwd(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
+               const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
+  if (C <= 256) return fwd_t<1>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  if (C <= 512) return fwd_t<2>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  if (C <= 768) return fwd_t<3>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  if (C <= 1024) return fwd_t<4>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  if (C <= 2048) return fwd_t<8>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  return hipErrorInvalidValue;
+}
+
 template <int MAXCH>
-hipError_t bwd_t(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, const float* w,
-                 const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* part, int rows, int C, hipStream_t s) {
-  hipLaunchKernelGGL(ln_bwd_kernel<MAXCH>, dim3(layernorm_bwd_blocks(rows)), dim3(256), 0, s, dy, x, mean, rstd, w,
-                     dres_in, dres_out, has_res, part, rows, C);
+hipError_t bwd_t(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean, const float* rstd,
+                 const float* w, const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* part, int rows, int C,
+                 hipStream_t s) {
+  const dim3 grid(layernorm_bwd_blocks(rows)), block(256);
+  if (sl.n > 0)
+    hipLaunchKernelGGL((ln_bwd_kernel<MAXCH, true>), grid, block, 0, s, nullptr, sl, x, mean, rstd, w, dres_in,
+                       dres_out, has_res, part, rows, C);
+  else
+    hipLaunchKernelGGL((ln_bwd_kernel<MAXCH, false>), grid, block, 0, s, dy, sl, x, mean, rstd, w, dres_in, dres_out,
+                       has_res, part, rows, C);
   return hipGetLastError();
 }
 
@@ -240,12 +294,14 @@ hipError_t bwd_t(const bf16_t* dy, const bf16_t* x, const float* mean, const flo
 hipError_t launch_add_layernorm_fwd(const bf16_t* x, const bf16_t* res, bf16_t* xsum, const float* w, const float* b,
                                     bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
   if (C % 4 || (res && !xsum)) return hipErrorInvalidValue;
-  if (C <= 256) return fwd_t<1>(x, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 512) return fwd_t<2>(x, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 768) return fwd_t<3>(x, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 1024) return fwd_t<4>(x, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 2048) return fwd_t<8>(x, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  return hipErrorInvalidValue;
+  return fwd(x, {nullptr, 0}, nullptr, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+}
+
+hipError_t launch_slices_layernorm_fwd(const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum,
+                                       const float* w, const float* b, bf16_t* y, float* mean, float* rstd, int rows,
+                                       int C, float eps, hipStream_t s) {
+  if (C % 4 || sl.n < 1 || !sl.p || !bias || !res || !xsum) return hipErrorInvalidValue;
+  return fwd(nullptr, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
 }
 
 hipError_t launch_layernorm_fwd(const bf16_t* x, const float* w, const float* b, bf16_t* y, float* mean,
@@ -259,23 +315,24 @@ hipError_t launch_residual_add(const bf16_t* res, const bf16_t* x, bf16_t* out, 
   return hipGetLastError();
 }
 
-// At least 4 rows per wave, 4 waves per block, each block writing one row of
-// partial sums; at most 768 blocks, three per CU, which is what the
+// Four waves per block, each block writing one row of partial sums. Many rows:
+// 4 rows per wave and at most 768 blocks, three per CU, which is what the
 // backward's registers (two rows' inputs in flight per wave) let stay
-// resident at once
+// resident at once. Fewer than 4096 rows: one row per wave up to 256 blocks,
+// since a wave's rows follow one another.
 int layernorm_bwd_blocks(int rows) {
-  int n = (rows + 15) / 16;
+  int n = std::max((rows + 15) / 16, std::min((rows + 3) / 4, 256));
   return n < 768 ? (n < 1 ? 1 : n) : 768;
 }
 
-hipError_t launch_layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd,
-                                const float* w, const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* part,
-                                int rows, int C, hipStream_t s) {
+hipError_t launch_layernorm_bwd(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean,
+                                const float* rstd, const float* w, const bf16_t* dres_in, bf16_t* dres_out,
+                                int has_res, float* part, int rows, int C, hipStream_t s) {
   if (C % 4) return hipErrorInvalidValue;
-  if (C <= 256) return bwd_t<1>(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
-  if (C <= 512) return bwd_t<2>(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
-  if (C <= 768) return bwd_t<3>(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
-  if (C <= 1024) return bwd_t<4>(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
-  if (C <= 2048) return bwd_t<8>(dy, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
+  if (C <= 256) return bwd_t<1>(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
+  if (C <= 512) return bwd_t<2>(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
+  if (C <= 768) return bwd_t<3>(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
+  if (C <= 1024) return bwd_t<4>(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
+  if (C <= 2048) return bwd_t<8>(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, rows, C, s);
   return hipErrorInvalidValue;
 }

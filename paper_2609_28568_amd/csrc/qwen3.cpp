@@ -174,10 +174,16 @@ ActLayout act_layout(const Dims& d) {
 }
 
 constexpr int DW_SPLITS = 16;   // token-contraction split of the adapter gradients
-constexpr int HEAD_SPLITS = 4;  // vocabulary-contraction split of the LM head's input gradient
+// vocabulary-contraction split of the LM head's input gradient: at least 4 (its
+// output tiles are few at every batch size), more for few rows
+int head_splits(const Dims& d, int* chunk) {
+  const int n = gemm_slices((int)d.BTL, d.C, d.V, 0, 1, chunk);
+  return n >= 4 ? n : gemm_split_plan(d.V, 4, chunk);
+}
 constexpr int BT_ROWS = 32;     // rows of the transposed B copies: the largest rank
 
 struct WsLayout {
+  size_t xsl;   // fp32 slices of the split products into the residual stream
   size_t dres, dh, datt, dpacked, draw, dgu, dm, du, dsum, cosT, sinT, part, part2, sumsq, normcoef, total;
   size_t bt[G_N];   // per adapted group: B transposed, [L][BT_ROWS][out_total] bf16
 };
@@ -188,16 +194,27 @@ WsLayout ws_layout(const Dims& d) {
   // split partial slices: adapter B gradients [split][out][RP] (or the LM
   // head's input gradient [split][BTL][C]) and adapter A gradients
   // [split][n RP][in]
-  size_t part = (size_t)d.BTL * d.C * HEAD_SPLITS, part2 = 0;
+  size_t part = (size_t)d.BTL * d.C * head_splits(d, nullptr), part2 = 0;
   for (int g = 0; g < G_N; ++g) {
     if (!(d.groups & (1 << g))) continue;
     const GroupGeom gg = group_geom(d, g);
     part = std::max(part, (size_t)DW_SPLITS * gg.out_total * RP);
     part2 = std::max(part2, (size_t)DW_SPLITS * gg.n * RP * gg.in);
   }
+  // the o and down projections (with their adapters as a second segment), and
+  // the input gradients of q|k|v and gate|up
+  size_t xs = 0;
+  for (int g = 0; g < G_N; ++g) {
+    const GroupGeom gg = group_geom(d, g);
+    const bool fwd = g == G_O || g == G_DN;
+    const int K2 = (d.groups & (1 << g)) ? (fwd ? RP : gg.n * RP) : 0;
+    const int n = gemm_slices((int)BT, d.C, fwd ? gg.in : gg.out_total, K2, fwd ? 0 : 1, nullptr);
+    if (n > 1) xs = std::max(xs, (size_t)n * BT * d.C);
+  }
   size_t o = 0;
+  w.xsl = o; o += align_up(xs * 4);
   w.dres = o; o += align_up(BT * d.C * 2);
-  w.dh = o; o += align_up(BT * d.C * 2);   // also the LM head's input gradient (loss rows)
+  w.dh = o; o += align_up(BT * d.C * 2);
   w.datt = o; o += align_up(BT * d.QD * 2);
   w.dpacked = o; o += align_up(BT * d.QKVD * 2);
   w.draw = o; o += align_up(BT * d.QKVD * 2);
@@ -315,13 +332,33 @@ hipError_t run_gemm(qwen3_model* m, int cls, double fl, const GemmArgs& g, int a
   return m->run(cls, fl, 0.0, [&] { return launch_gemm(g, a_t, b_t, epi, m->stream); });
 }
 
+// Turn product a (into the residual stream, C columns) into one left as fp32
+// slices when splitting its contraction pays; false: unchanged, *sl empty.
+bool sliced(qwen3_model* m, GemmArgs& a, int b_t, Slices* sl) {
+  int kc = 0;
+  const int n = gemm_slices(a.M, a.N, a.K, a.K2, b_t, &kc);
+  *sl = {nullptr, 0};
+  if (n <= 1) return false;
+  a.C = m->wf(m->ws.xsl);
+  a.ldc = a.N;
+  a.residual = nullptr;
+  a.splits = n;
+  a.k_chunk = kc;
+  a.split_stride = (long)a.M * a.N;
+  *sl = {m->wf(m->ws.xsl), n};
+  return true;
+}
+
 // Frozen projection of group g at layer l: y (row stride ldy) = x W^T
 // (+ residual). When the group is adapted, u = s x A^T first (its own small
 // GEMM, kept for the backward), and the adapter's up-projection u B^T rides
 // in the same GEMM as a second contraction segment, projection j's output
-// columns contracting with u's j-th block of RP columns.
+// columns contracting with u's j-th block of RP columns. With sl (a projection
+// into the residual stream) the product may be left as fp32 slices for the
+// norm that consumes it, when splitting the contraction pays (few rows): then
+// *sl holds them and neither y nor the residual is touched.
 hipError_t proj_fwd(qwen3_model* m, int g, int l, const bf16_t* x, const bf16_t* W, bf16_t* y, int ldy,
-                    const bf16_t* residual) {
+                    const bf16_t* residual, Slices* sl = nullptr) {
   const Dims& d = m->d;
   const GroupGeom gg = group_geom(d, g);
   GemmArgs a{};
@@ -354,6 +391,7 @@ hipError_t proj_fwd(qwen3_model* m, int g, int l, const bf16_t* x, const bf16_t*
     }
     fl += mnk2(d.BT, gg.out_total, d.r);
   }
+  if (sl && sliced(m, a, 0, sl)) return run_gemm(m, QWEN3_K_GEMM_FWD, fl, a, 0, 0, EPI_F32);
   return run_gemm(m, QWEN3_K_GEMM_FWD, fl, a, 0, 0, EPI_BF16);
 }
 
@@ -362,9 +400,10 @@ hipError_t proj_fwd(qwen3_model* m, int g, int l, const bf16_t* x, const bf16_t*
 // dx = dy W (+ du A with du = s dy_j B_j per projection, as a second
 // contraction segment of the same GEMM). The adapter gradients contract over
 // the tokens, split DW_SPLITS ways into the partial areas and summed by one
-// launch: dB_j = dy_j^T u_j, dA = du^T x.
+// launch: dB_j = dy_j^T u_j, dA = du^T x. With sl, dx may be left as slices as
+// in proj_fwd.
 hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, const bf16_t* x, const bf16_t* W,
-                    bf16_t* dx) {
+                    bf16_t* dx, Slices* sl = nullptr) {
   const Dims& d = m->d;
   const GroupGeom gg = group_geom(d, g);
   const int BT = (int)d.BT, nu = gg.n * RP;
@@ -433,6 +472,7 @@ hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, con
     fl += mnk2(d.BT, gg.in, gg.n * d.r);
   }
   if (!dx) return hipSuccess;
+  if (sl && sliced(m, a, 1, sl)) return run_gemm(m, QWEN3_K_GEMM_DX, fl, a, 0, 1, EPI_F32);
   return run_gemm(m, QWEN3_K_GEMM_DX, fl, a, 0, 1, EPI_BF16);
 }
 
@@ -573,6 +613,7 @@ gpt2_status qwen3_forward(qwen3_model* m, const int32_t* d_inputs, const int32_t
   const double rowb = 2.0 * d.BT * d.C;   // bytes of one bf16 [BT, C] activation
   TRY(m->run(OTHER, 0.0, 2.0 * rowb + 4.0 * d.BT,
              [&] { return launch_embed_gather(d_inputs, m->base(B_EMBED), m->res(0), d.BT, d.C, m->stream); }));
+  bool in_norm_done = false;   // formed with the previous layer's output
   for (int l = 0; l < d.L; ++l) {
     bf16_t* h = m->ab(m->act.h + l * m->act.s_act);
     float* r1 = m->af(m->act.r1 + l * m->act.s_row);
@@ -583,10 +624,11 @@ gpt2_status qwen3_forward(qwen3_model* m, const int32_t* d_inputs, const int32_t
     bf16_t* gu = m->ab(m->act.gu + l * m->act.s_gu);
     bf16_t* mm = m->ab(m->act.m + l * m->act.s_m);
     // attention sub-layer
-    TRY(m->run(NORM, 0.0, 2.0 * rowb + 4.0 * d.BT, [&] {
-      return launch_rmsnorm_fwd(m->res(l), m->base(B_IN_NORM) + (size_t)l * d.C, h, r1, BT, d.C, m->cfg.rms_eps, 1, 0,
-                                m->stream);
-    }));
+    if (!in_norm_done)
+      TRY(m->run(NORM, 0.0, 2.0 * rowb + 4.0 * d.BT, [&] {
+        return launch_rmsnorm_fwd(m->res(l), m->base(B_IN_NORM) + (size_t)l * d.C, h, r1, BT, d.C, m->cfg.rms_eps, 1,
+                                  0, m->stream);
+      }));
     TRY(proj_fwd(m, G_QKV, l, h, m->base(B_QKV) + (size_t)l * d.QKVD * d.C, raw, d.QKVD, nullptr));
     AttnArgs aa = attn_args(m, l);
     TRY(m->run(NORM, 0.0, 4.0 * d.BT * d.QKVD + 4.0 * d.BT * (d.H + d.Hkv), [&] {
@@ -596,11 +638,13 @@ gpt2_status qwen3_forward(qwen3_model* m, const int32_t* d_inputs, const int32_t
                                     d.H, d.Hkv, d.hd, m->cfg.rms_eps, m->stream);
     }));
     TRY(m->run(QWEN3_K_ATTN_FWD, attn_fwd_flops(d), 0.0, [&] { return launch_attention_fwd(aa, m->stream); }));
-    TRY(proj_fwd(m, G_O, l, aa.out, m->base(B_O) + (size_t)l * d.C * d.QD, xmid, d.C, m->res(l)));
+    Slices sl;
+    TRY(proj_fwd(m, G_O, l, aa.out, m->base(B_O) + (size_t)l * d.C * d.QD, xmid, d.C, m->res(l), &sl));
     // MLP sub-layer
-    TRY(m->run(NORM, 0.0, 2.0 * rowb + 4.0 * d.BT, [&] {
-      return launch_rmsnorm_fwd(xmid, m->base(B_POST_NORM) + (size_t)l * d.C, h2, r2, BT, d.C, m->cfg.rms_eps, 1, 0,
-                                m->stream);
+    TRY(m->run(NORM, 0.0, (2.0 + 2.0 * sl.n) * rowb + 4.0 * d.BT, [&] {
+      const bf16_t* w = m->base(B_POST_NORM) + (size_t)l * d.C;
+      return sl.n > 0 ? launch_slices_rmsnorm_fwd(sl, m->res(l), xmid, w, h2, r2, BT, d.C, m->cfg.rms_eps, m->stream)
+                      : launch_rmsnorm_fwd(xmid, w, h2, r2, BT, d.C, m->cfg.rms_eps, 1, 0, m->stream);
     }));
     if (m->swiglu_fused && !m->has(G_GU)) {
       // gate|up projection with the SwiGLU in its epilogue: writes the
@@ -613,7 +657,19 @@ gpt2_status qwen3_forward(qwen3_model* m, const int32_t* d_inputs, const int32_t
       TRY(proj_fwd(m, G_GU, l, h2, m->base(B_GU) + (size_t)l * 2 * d.F * d.C, gu, 2 * d.F, nullptr));
       TRY(m->run(OTHER, 0.0, 6.0 * d.BT * d.F, [&] { return launch_swiglu_fwd(gu, mm, d.BT, d.F, m->stream); }));
     }
-    TRY(proj_fwd(m, G_DN, l, mm, m->base(B_DOWN) + (size_t)l * d.C * d.F, m->res(l + 1), d.C, xmid));
+    TRY(proj_fwd(m, G_DN, l, mm, m->base(B_DOWN) + (size_t)l * d.C * d.F, m->res(l + 1), d.C, xmid, &sl));
+    in_norm_done = sl.n > 0;
+    if (sl.n > 0) {
+      // the residual sum, and the next layer's input norm (none after the
+      // last layer: the final norm takes the rows with loss only)
+      const bool last = l + 1 == d.L;
+      const size_t n = last ? 0 : (size_t)(l + 1);
+      TRY(m->run(NORM, 0.0, (2.0 + 2.0 * sl.n) * rowb + 4.0 * d.BT, [&] {
+        return launch_slices_rmsnorm_fwd(sl, xmid, m->res(l + 1), last ? nullptr : m->base(B_IN_NORM) + n * d.C,
+                                         m->ab(m->act.h + n * m->act.s_act), m->af(m->act.r1 + n * m->act.s_row), BT,
+                                         d.C, m->cfg.rms_eps, m->stream);
+      }));
+    }
   }
   // final norm and LM head on the positions that carry loss (compacted rows)
   bf16_t* xf = m->ab(m->act.xf);
@@ -655,21 +711,19 @@ gpt2_status qwen3_backward(qwen3_model* m) {
                [&] { return launch_lora_bt(b, m->wb(m->ws.bt[g]), d.L, out, RP, m->stream); }));
   }
   // LM head: dxf = dlogits embed over the loss rows, the long vocabulary
-  // contraction split so that the few output tiles fill the GPU, then the
-  // final RMSNorm (rows without loss get a zero gradient)
+  // contraction split so that the few output tiles fill the GPU, its slices
+  // summed by the final RMSNorm (rows without loss get a zero gradient)
   {
     int kc = 0;
-    const int splits = gemm_split_plan(d.V, HEAD_SPLITS, &kc);
+    const int splits = head_splits(d, &kc);
     float* part = m->wf(m->ws.part);
     TRY(gemm(m, DX, mnk2(BTL, d.C, d.V), BTL, d.C, d.V, m->ab(m->act.logits), d.V, 0, m->base(B_EMBED), d.C, 1,
              EPI_F32, part, d.C, nullptr, splits, kc, (long)d.BTL * d.C));
-    TRY(m->run(QWEN3_K_OTHER, 0.0, (4.0 * splits + 2.0) * d.BTL * d.C,
-               [&] { return launch_reduce_slices_bf16(part, splits, d.BTL * d.C, 1.0f, dh, m->stream); }));
+    TRY(m->run(NORM, 0.0, 2.0 * rowb + (2.0 + 4.0 * splits) * d.BTL * d.C + 4.0 * d.BTL, [&] {
+      return launch_rmsnorm_bwd(nullptr, {part, splits}, m->res(d.L), m->af(m->act.rf), m->base(B_FINAL_NORM), dres, 0,
+                                BT, d.C, d.T, d.mask_from, m->stream);
+    }));
   }
-  TRY(m->run(NORM, 0.0, 2.0 * rowb + 4.0 * d.BTL * d.C + 4.0 * d.BTL, [&] {
-    return launch_rmsnorm_bwd(dh, m->res(d.L), m->af(m->act.rf), m->base(B_FINAL_NORM), dres, 0, BT, d.C, d.T,
-                              d.mask_from, m->stream);
-  }));
   for (int l = d.L - 1; l >= 0; --l) {
     const bf16_t* h = m->ab(m->act.h + l * m->act.s_act);
     const float* r1 = m->af(m->act.r1 + l * m->act.s_row);
@@ -694,9 +748,10 @@ gpt2_status qwen3_backward(qwen3_model* m) {
       TRY(m->run(QWEN3_K_OTHER, 0.0, 10.0 * d.BT * d.F,
                  [&] { return launch_swiglu_bwd(dm, gu, dgu, d.BT, d.F, m->stream); }));
     }
-    TRY(proj_bwd(m, G_GU, l, dgu, 2 * d.F, h2, m->base(B_GU) + (size_t)l * 2 * d.F * d.C, dh));
+    Slices sl{nullptr, 0};
+    TRY(proj_bwd(m, G_GU, l, dgu, 2 * d.F, h2, m->base(B_GU) + (size_t)l * 2 * d.F * d.C, dh, &sl));
     TRY(m->run(NORM, 0.0, 4.0 * rowb + 4.0 * d.BT, [&] {
-      return launch_rmsnorm_bwd(dh, xmid, r2, m->base(B_POST_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
+      return launch_rmsnorm_bwd(dh, sl, xmid, r2, m->base(B_POST_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
                                 m->stream);
     }));
     // attention output projection: xmid = res(l) + att o^T (+ adapter)
@@ -714,10 +769,11 @@ gpt2_status qwen3_backward(qwen3_model* m) {
     // the first layer's input gradient would only reach the frozen token
     // table: its q|k|v input gradient and the norm behind it are skipped
     const bool need_dx = l > 0;
-    TRY(proj_bwd(m, G_QKV, l, draw, d.QKVD, h, m->base(B_QKV) + (size_t)l * d.QKVD * d.C, need_dx ? dh : nullptr));
+    TRY(proj_bwd(m, G_QKV, l, draw, d.QKVD, h, m->base(B_QKV) + (size_t)l * d.QKVD * d.C, need_dx ? dh : nullptr,
+                 &sl));
     if (need_dx)
       TRY(m->run(NORM, 0.0, 4.0 * rowb + 4.0 * d.BT, [&] {
-        return launch_rmsnorm_bwd(dh, m->res(l), r1, m->base(B_IN_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
+        return launch_rmsnorm_bwd(dh, sl, m->res(l), r1, m->base(B_IN_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
                                   m->stream);
       }));
   }

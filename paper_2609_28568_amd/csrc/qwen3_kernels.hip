@@ -32,21 +32,37 @@ DEV int loss_index(int p, int T, int mask_from) {
 
 // One row per wave; lane owns 4-channel chunks c = 4*(lane + 64*i). Loads of
 // a row are issued at once from clamped addresses and masked afterwards.
-// Output row i normalises input row loss_row(i) (rows = output rows).
-template <int MAXCH>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
-                                                          bf16_t* __restrict__ y, float* __restrict__ rstd_out,
+// Output row i normalises input row loss_row(i) (rows = output rows). With SL
+// the input rows are formed first, from the fp32 slices of the projection
+// before the norm (few rows: the product is split to fill the chip) and the
+// residual, x = bf16(sum + res), and stored to xsum; w == nullptr then stops
+// there.
+template <int MAXCH, bool SL>
+__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restrict__ x, Slices sl,
+                                                          const bf16_t* __restrict__ res, bf16_t* __restrict__ xsum,
+                                                          const bf16_t* __restrict__ w, bf16_t* __restrict__ y, float* __restrict__ rstd_out,
                                                           int rows, int C, float eps, int T, int mask_from) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  const bf16_t* xr = x + (size_t)loss_row(row, T, mask_from) * C;
+  const bf16_t* xr = SL ? res + (size_t)row * C : x + (size_t)loss_row(row, T, mask_from) * C;
   uint2 xu[MAXCH], wu[MAXCH];
 #pragma unroll
   for (int i = 0; i < MAXCH; ++i) {
     const int c = min(4 * (lane + 64 * i), C - 4);
     xu[i] = *reinterpret_cast<const uint2*>(xr + c);
-    wu[i] = *reinterpret_cast<const uint2*>(w + c);
+    if (!SL || w) wu[i] = *reinterpret_cast<const uint2*>(w + c);
+  }
+  if constexpr (SL) {
+#pragma unroll
+    for (int i = 0; i < MAXCH; ++i) {
+      const int c = min(4 * (lane + 64 * i), C - 4);
+      const float4 t = sum_slices(sl.p + (size_t)row * C + c, sl.n, (size_t)rows * C);
+      xu[i] = make_uint2(pack2(t.x + lo_f(xu[i].x), t.y + hi_f(xu[i].x)),
+                         pack2(t.z + lo_f(xu[i].y), t.w + hi_f(xu[i].y)));
+      if (4 * (lane + 64 * i) < C) *reinterpret_cast<uint2*>(xsum + (size_t)row * C + c) = xu[i];
+    }
+    if (!w) return;
   }
   float v[MAXCH][4];
   float ss = 0.0f;
@@ -76,8 +92,11 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restri
 // dres (=|+=) rstd (g - xhat mean(g xhat)), g = dy w, xhat = x rstd (gain frozen).
 // dy and rstd hold compact rows (loss_index); rows p with p % T < mask_from
 // have no upstream gradient: dres is left as is (accumulate) or zeroed.
-template <int MAXCH>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
+// With SL dy comes as fp32 slices of dy_rows rows each; their sum is rounded to
+// bf16, as the product stored whole is.
+template <int MAXCH, bool SL>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restrict__ dy, Slices sl, int dy_rows,
+                                                          const bf16_t* __restrict__ x,
                                                           const float* __restrict__ rstd_in,
                                                           const bf16_t* __restrict__ w, bf16_t* __restrict__ dres,
                                                           int accumulate, int rows, int C, int T, int mask_from) {
@@ -93,12 +112,16 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
   const int ci = loss_index(row, T, mask_from);
   const bf16_t* xr = x + (size_t)row * C;
   const bf16_t* dr = dy + (size_t)ci * C;
-  uint2 xu[MAXCH], du[MAXCH], wu[MAXCH], ru[MAXCH];
+  uint2 xu[MAXCH], wu[MAXCH], ru[MAXCH];
+  uint2 du[MAXCH];
 #pragma unroll
   for (int i = 0; i < MAXCH; ++i) {
     const int c = min(4 * (lane + 64 * i), C - 4);
     xu[i] = *reinterpret_cast<const uint2*>(xr + c);
-    du[i] = *reinterpret_cast<const uint2*>(dr + c);
+    if constexpr (SL) {
+      const float4 t = sum_slices(sl.p + (size_t)ci * C + c, sl.n, (size_t)dy_rows * C);
+      du[i] = make_uint2(pack2(t.x, t.y), pack2(t.z, t.w));
+    } else du[i] = *reinterpret_cast<const uint2*>(dr + c);
     wu[i] = *reinterpret_cast<const uint2*>(w + c);
     ru[i] = accumulate ? *reinterpret_cast<const uint2*>(rr + c) : make_uint2(0, 0);
   }
@@ -325,30 +348,60 @@ hipError_t launch_embed_gather(const int32_t* ids, const bf16_t* table, bf16_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, float* rstd, int rows, int C, float eps,
-                              int T, int mask_from, hipStream_t s) {
-  if (C % 4 || T < 1 || mask_from < 0 || mask_from >= T) return hipErrorInvalidValue;
+template <int MAXCH>
+static void rms_fwd_t(const bf16_t* x, const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w, bf16_t* y,
+                      float* rstd, int rows, int C, float eps, int T, int mask_from, hipStream_t s) {
   const dim3 g((rows + 3) / 4), b(256);
-  if (C <= 256) hipLaunchKernelGGL(rmsnorm_fwd_kernel<1>, g, b, 0, s, x, w, y, rstd, rows, C, eps, T, mask_from);
-  else if (C <= 512) hipLaunchKernelGGL(rmsnorm_fwd_kernel<2>, g, b, 0, s, x, w, y, rstd, rows, C, eps, T, mask_from);
-  else if (C <= 1024) hipLaunchKernelGGL(rmsnorm_fwd_kernel<4>, g, b, 0, s, x, w, y, rstd, rows, C, eps, T, mask_from);
-  else if (C <= 2048) hipLaunchKernelGGL(rmsnorm_fwd_kernel<8>, g, b, 0, s, x, w, y, rstd, rows, C, eps, T, mask_from);
+  if (sl.n > 0)
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<MAXCH, true>), g, b, 0, s, x, sl, res, xsum, w, y, rstd, rows, C, eps, T,
+                       mask_from);
+  else
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<MAXCH, false>), g, b, 0, s, x, sl, res, xsum, w, y, rstd, rows, C, eps, T,
+                       mask_from);
+}
+
+static hipError_t rms_fwd(const bf16_t* x, const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w,
+                          bf16_t* y, float* rstd, int rows, int C, float eps, int T, int mask_from, hipStream_t s) {
+  if (C <= 256) rms_fwd_t<1>(x, sl, res, xsum, w, y, rstd, rows, C, eps, T, mask_from, s);
+  else if (C <= 512) rms_fwd_t<2>(x, sl, res, xsum, w, y, rstd, rows, C, eps, T, mask_from, s);
+  else if (C <= 1024) rms_fwd_t<4>(x, sl, res, xsum, w, y, rstd, rows, C, eps, T, mask_from, s);
+  else if (C <= 2048) rms_fwd_t<8>(x, sl, res, xsum, w, y, rstd, rows, C, eps, T, mask_from, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const bf16_t* x, const float* rstd, const bf16_t* w, bf16_t* dres,
-                              int accumulate, int rows, int C, int T, int mask_from, hipStream_t s) {
+hipError_t launch_rmsnorm_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, float* rstd, int rows, int C, float eps,
+                              int T, int mask_from, hipStream_t s) {
   if (C % 4 || T < 1 || mask_from < 0 || mask_from >= T) return hipErrorInvalidValue;
+  return rms_fwd(x, {nullptr, 0}, nullptr, nullptr, w, y, rstd, rows, C, eps, T, mask_from, s);
+}
+
+hipError_t launch_slices_rmsnorm_fwd(const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w, bf16_t* y,
+                                     float* rstd, int rows, int C, float eps, hipStream_t s) {
+  if (C % 4 || sl.n < 1 || !sl.p || !res || !xsum) return hipErrorInvalidValue;
+  return rms_fwd(nullptr, sl, res, xsum, w, y, rstd, rows, C, eps, 1, 0, s);
+}
+
+template <int MAXCH>
+static void rms_bwd_t(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* rstd, const bf16_t* w,
+                      bf16_t* dres, int accumulate, int rows, int C, int T, int mask_from, hipStream_t s) {
   const dim3 g((rows + 3) / 4), b(256);
-  if (C <= 256)
-    hipLaunchKernelGGL(rmsnorm_bwd_kernel<1>, g, b, 0, s, dy, x, rstd, w, dres, accumulate, rows, C, T, mask_from);
-  else if (C <= 512)
-    hipLaunchKernelGGL(rmsnorm_bwd_kernel<2>, g, b, 0, s, dy, x, rstd, w, dres, accumulate, rows, C, T, mask_from);
-  else if (C <= 1024)
-    hipLaunchKernelGGL(rmsnorm_bwd_kernel<4>, g, b, 0, s, dy, x, rstd, w, dres, accumulate, rows, C, T, mask_from);
-  else if (C <= 2048)
-    hipLaunchKernelGGL(rmsnorm_bwd_kernel<8>, g, b, 0, s, dy, x, rstd, w, dres, accumulate, rows, C, T, mask_from);
+  const int dy_rows = rows / T * (T - mask_from);
+  if (sl.n > 0)
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, true>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres, accumulate,
+                       rows, C, T, mask_from);
+  else
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, false>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres, accumulate,
+                       rows, C, T, mask_from);
+}
+
+hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* rstd, const bf16_t* w,
+                              bf16_t* dres, int accumulate, int rows, int C, int T, int mask_from, hipStream_t s) {
+  if (C % 4 || T < 1 || mask_from < 0 || mask_from >= T || rows % T) return hipErrorInvalidValue;
+  if (C <= 256) rms_bwd_t<1>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 512) rms_bwd_t<2>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 1024) rms_bwd_t<4>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 2048) rms_bwd_t<8>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
