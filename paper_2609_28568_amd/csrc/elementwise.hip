@@ -23,24 +23,19 @@ __global__ void reduce_slices_kernel(const float* __restrict__ src, int nslices,
   *reinterpret_cast<float4*>(dst + i) = acc;
 }
 
-// Two independent reductions in one launch; blockIdx.y picks the segment.
-__global__ void reduce_slices2_kernel(const float* __restrict__ src, int nslices, long n, float* __restrict__ dst,
-                                      const float* __restrict__ src2, int nslices2, long n2,
-                                      float* __restrict__ dst2, int accumulate) {
-  const bool second = blockIdx.y == 1;
-  const float* sp = second ? src2 : src;
-  const int ns = second ? nslices2 : nslices;
-  const long nn = second ? n2 : n;
-  float* dp = second ? dst2 : dst;
-  long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i >= nn) return;
-  float4 acc = accumulate ? *reinterpret_cast<const float4*>(dp + i) : make_float4(0, 0, 0, 0);
+// Several independent reductions in one launch; blockIdx.y picks the segment,
+// whose blocks stride over its elements.
+__global__ __launch_bounds__(256) void reduce_segs_kernel(ReduceSegs r, int accumulate) {
+  const ReduceSeg g = r.s[blockIdx.y];
+  for (long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4; i < g.n; i += (long)gridDim.x * 1024) {
+    float4 acc = accumulate ? *reinterpret_cast<const float4*>(g.dst + i) : make_float4(0, 0, 0, 0);
 #pragma unroll 16
-  for (int k = 0; k < ns; ++k) {
-    float4 v = *reinterpret_cast<const float4*>(sp + (size_t)k * nn + i);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    for (int k = 0; k < g.slices; ++k) {
+      float4 v = *reinterpret_cast<const float4*>(g.src + (size_t)k * g.stride + i);
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    }
+    *reinterpret_cast<float4*>(g.dst + i) = acc;
   }
-  *reinterpret_cast<float4*>(dp + i) = acc;
 }
 
 // 16 waves per block, 64 columns per block: wave w sums slices w, w+16, ...
@@ -77,15 +72,8 @@ DEV void reduce_parts_block(const float* __restrict__ part, int S, long stride, 
   }
 }
 
-__global__ __launch_bounds__(1024) void reduce_parts_kernel(const float* __restrict__ part, int S, long stride,
-                                                            int n, int nd, float* __restrict__ d0,
-                                                            float* __restrict__ d1, float* __restrict__ d2,
-                                                            int accumulate) {
-  reduce_parts_block(part, S, stride, n, nd, d0, d1, d2, accumulate);
-}
-
-// The same reduction for several partial-sum arrays of one shape at once:
-// blockIdx.y picks the array and its destinations.
+// Several partial-sum arrays of one shape at once: blockIdx.y picks the array
+// and its destinations.
 __global__ __launch_bounds__(1024) void reduce_parts_multi_kernel(ReducePartsJobs J, int S, long stride, int n, int nd,
                                                                   int accumulate) {
   const int j = blockIdx.y;
@@ -573,12 +561,17 @@ hipError_t launch_reduce_slices(const float* src, int nslices, long n, float* ds
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_slices2(const float* src, int nslices, long n, float* dst, const float* src2,
-                                 int nslices2, long n2, float* dst2, int accumulate, hipStream_t s) {
-  if (n % 4 || n2 % 4) return hipErrorInvalidValue;
-  const long nmax = n > n2 ? n : n2;
-  hipLaunchKernelGGL(reduce_slices2_kernel, dim3(blocks_for(nmax / 4, 256), 2), dim3(256), 0, s, src, nslices, n, dst,
-                     src2, nslices2, n2, dst2, accumulate);
+hipError_t launch_reduce_segs(const ReduceSegs& r, int accumulate, hipStream_t s) {
+  if (r.count < 1 || r.count > REDUCE_SEGS) return hipErrorInvalidValue;
+  long nmax = 0;
+  for (int i = 0; i < r.count; ++i) {
+    if (r.s[i].n % 4 || r.s[i].n < 4 || r.s[i].stride % 4) return hipErrorInvalidValue;
+    nmax = r.s[i].n > nmax ? r.s[i].n : nmax;
+  }
+  // up to 2048 blocks per segment, eight on each CU
+  const unsigned blocks = blocks_for(nmax / 4, 256);
+  hipLaunchKernelGGL(reduce_segs_kernel, dim3(blocks < 2048 ? blocks : 2048, (unsigned)r.count), dim3(256), 0, s, r,
+                     accumulate);
   return hipGetLastError();
 }
 
@@ -587,14 +580,6 @@ hipError_t launch_reduce_parts_multi(const ReducePartsJobs& J, int S, long strid
   if (nd < 1 || nd > 3 || J.count < 1 || J.count > REDUCE_JOBS) return hipErrorInvalidValue;
   hipLaunchKernelGGL(reduce_parts_multi_kernel, dim3((unsigned)((n * nd + 63) / 64), (unsigned)J.count), dim3(1024), 0,
                      s, J, S, stride, n, nd, accumulate);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_parts(const float* part, int S, long stride, int n, int nd, float* d0, float* d1,
-                               float* d2, int accumulate, hipStream_t s) {
-  if (nd < 1 || nd > 3) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((n * nd + 63) / 64)), dim3(1024), 0, s, part, S, stride, n,
-                     nd, d0, d1, d2, accumulate);
   return hipGetLastError();
 }
 

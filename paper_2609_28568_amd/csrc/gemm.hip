@@ -669,7 +669,11 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
               if constexpr (EPI == EPI_BF16_RES) {
                 v0 += lo_f(rd[cc].x); v1 += hi_f(rd[cc].x); v2 += lo_f(rd[cc].y); v3 += hi_f(rd[cc].y);
               }
-              *reinterpret_cast<uint2*>(Cbi + off) = make_uint2(pack2(v0, v1), pack2(v2, v3));
+              const uint2 o = make_uint2(pack2(v0, v1), pack2(v2, v3));
+              *reinterpret_cast<uint2*>(Cbi + off) = o;
+              if constexpr (EPI == EPI_BF16_RES) {
+                if (g.C2) *reinterpret_cast<uint2*>(g.C2 + bo + off) = o;
+              }
             }
           }
         }
@@ -1025,7 +1029,7 @@ hipError_t launch_gemm_grouped(const GemmGroupedArgs& gg, hipStream_t s) {
     if (!gr.A || !gr.B || !gr.C || gr.M < 1 || gr.N < 1 || gr.count < 1 || gr.N % 4) return hipErrorInvalidValue;
     if (gr.splits > 1) {
       // chunks of whole 64-token steps covering K; slices of plain sums
-      if (gr.bsum || gr.k_chunk < 64 || gr.k_chunk % 64 || (long)gr.k_chunk * gr.splits < gg.K ||
+      if (gr.k_chunk < 64 || gr.k_chunk % 64 || (long)gr.k_chunk * gr.splits < gg.K ||
           (long)gr.k_chunk * (gr.splits - 1) >= gg.K || gr.split_stride < (long)gr.count * gr.c_stride)
         return hipErrorInvalidValue;
     }

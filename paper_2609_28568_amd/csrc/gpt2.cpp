@@ -10,6 +10,7 @@
 #include <new>
 #include <algorithm>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/gpt2.h"
@@ -151,15 +152,15 @@ struct ActLayout {
 };
 
 struct WsLayout {
-  size_t dres, dh, datt, dbig, dsum, splitk, bsum, lnpart, sumsq, normcoef, total;
-  size_t splitk_elems, bsum_elems, s_lnpart;
+  size_t dh, datt, dsum, splitk, lnpart, sumsq, normcoef, total;
+  size_t s_lnpart;
   // the training backward keeps every layer's output gradients until one
   // grouped launch computes all block weight gradients: residual-stream
   // gradients [2L+1][BT][C] (slot 2l+2 enters block l, 2l+1 is after its MLP
   // branch, 2l leaves it), MLP pre-activation gradients [L][BT][F], q|k|v
   // gradients [L][BT][3C], and the bias partial sums of the q|k|v and MLP-up
-  // groups
-  size_t dres_l, dfc_l, dqkv_l, gbs_qkv, gbs_fc;
+  // groups (and of one layer's MLP-down product, for a block in isolation)
+  size_t dres_l, dfc_l, dqkv_l, gbs_qkv, gbs_fc, gbs_fp;
   size_t s_dres, s_dfc, s_dqkv;
   // fp32 slices of the products that a norm consumes, when they are split
   // (sliced_product)
@@ -202,11 +203,11 @@ ActLayout act_layout(const Dims& d) {
   return a;
 }
 
-// The four groups of the grouped weight-gradient launch, shapes only (the
-// pointers are filled in by the backward): q|k|v [3C, C], attention
-// projection [C, C], MLP up [F, C], MLP down [C, F], each over the L layers.
+// The four groups of the grouped weight-gradient launch over nl layers, shapes
+// only (the pointers are filled in by the backward): q|k|v [3C, C], attention
+// projection [C, C], MLP up [F, C], MLP down [C, F].
 enum { G_QKV, G_ATTPROJ, G_FC, G_FCPROJ };
-GemmGroupedArgs dw_groups(const Dims& d) {
+GemmGroupedArgs dw_groups(const Dims& d, int nl) {
   GemmGroupedArgs g{};
   g.ngroups = 4;
   g.K = (int)d.BT;
@@ -214,43 +215,71 @@ GemmGroupedArgs dw_groups(const Dims& d) {
   for (int i = 0; i < 4; ++i) {
     g.grp[i].M = mn[i][0];
     g.grp[i].N = mn[i][1];
-    g.grp[i].count = d.L;
+    g.grp[i].count = nl;
   }
   return g;
 }
 
-// The grouped weight-gradient launch runs in rounds of 512 tiles (two
-// workgroups on each of the 256 CUs). When its last round would be at most
-// half full and consists of whole MLP-down products (the last group), those
-// products split their token contraction into `splits` chunks, so that the
-// final round is full of shorter work items; their fp32 slices are reduced
-// afterwards. np = 0: no such plan.
-struct DwGroupedTail {
-  int np = 0, splits = 1, chunk = 0;
+// How the grouped weight-gradient launch over nl layers fills the chip, which
+// runs 512 tiles at a time (two workgroups on each of the 256 CUs).
+// Many layers: when the last round would be at most half full and consists
+// of whole MLP-down products (the last group), np of those split their token
+// contraction into tail_splits chunks, so that the final round is full of
+// shorter work items. Few layers (one block in isolation, shallow models),
+// less than a round in all: every product splits into `splits` chunks. Either
+// way the split products' fp32 slices are reduced afterwards.
+struct DwPlan {
+  int splits = 1, chunk = 0;
+  int np = 0, tail_splits = 1, tail_chunk = 0;
   long nfull = 0;
 };
 
-DwGroupedTail dw_grouped_tail(const Dims& d) {
-  DwGroupedTail t;
+DwPlan dw_plan(const Dims& d, int nl) {
+  DwPlan t;
   constexpr long ROUND = 512;
-  const GemmGroupedArgs g = dw_groups(d);
+  const GemmGroupedArgs g = dw_groups(d, nl);
   int bm = 192;
   for (int i = 0; i < g.ngroups; ++i)
     if (g.grp[i].M % 192 || g.grp[i].N % 192) bm = 128;
-  long total = 0;
-  for (int i = 0; i < g.ngroups; ++i) total += (long)((g.grp[i].M + bm - 1) / bm) * ((g.grp[i].N + bm - 1) / bm) * g.grp[i].count;
+  long total = 0, elems = 0;
+  for (int i = 0; i < g.ngroups; ++i) {
+    total += (long)((g.grp[i].M + bm - 1) / bm) * ((g.grp[i].N + bm - 1) / bm) * g.grp[i].count;
+    elems += (long)g.grp[i].M * g.grp[i].N * g.grp[i].count;
+  }
+  if (total < ROUND) {
+    // Time per 64 tokens with one tile per CU and with two, and the slices
+    // written and read back at about 3 TB/s, in us; no split past one round.
+    // One 768-wide block on 16,384 tokens (192 tiles), launch + reduction:
+    // 421 + 11 us unsplit, 282 + 32 split 2 ways, 275 + 98 5 ways, 280 + 149
+    // 8 ways (325 as four launches split 8 or 16 ways each); on 999 tokens
+    // unsplit is best.
+    const double t1 = bm == 192 ? 1.64 : 0.85, t2 = bm == 192 ? 2.2 : 1.2;
+    double best = 0.0;
+    for (int want = 1; want <= 16 && want * total <= ROUND; ++want) {
+      int chunk = 0;
+      const int s = gemm_split_plan((int)d.BT, want, &chunk);
+      if (s != want || (s > 1 && chunk < 512)) continue;
+      const double us = chunk / 64 * (total * s <= ROUND / 2 ? t1 : t2) + (s > 1 ? 8.0 * s * elems / 3e6 : 0.0);
+      if (best == 0.0 || us < 0.95 * best) {
+        best = us;
+        t.splits = s;
+        t.chunk = chunk;
+      }
+    }
+    return t;
+  }
   const GemmGroup& last = g.grp[G_FCPROJ];
   const long tpp = (long)((last.M + bm - 1) / bm) * ((last.N + bm - 1) / bm);
   const long tail = total % ROUND;
-  if (total < ROUND || tail == 0 || tail > ROUND / 2 || tail % tpp || tail / tpp > last.count) return t;
+  if (tail == 0 || tail > ROUND / 2 || tail % tpp || tail / tpp > last.count) return t;
   int splits = (int)(ROUND / tail);
   if (splits > 4) splits = 4;
   int chunk = 0;
   splits = gemm_split_plan((int)d.BT, splits, &chunk);
   if (splits < 2 || ((tail * splits) % 8) != 0) return t;
   t.np = (int)(tail / tpp);
-  t.splits = splits;
-  t.chunk = chunk;
+  t.tail_splits = splits;
+  t.tail_chunk = chunk;
   t.nfull = total - tail;
   return t;
 }
@@ -258,26 +287,23 @@ DwGroupedTail dw_grouped_tail(const Dims& d) {
 WsLayout ws_layout(const Dims& d) {
   WsLayout w{};
   const size_t BT = d.BT, C = d.C, F = d.F;
-  size_t wide = F > 3 * C ? F : 3 * C;
+  // slices of split weight gradients: the head's, the grouped launch's tail
+  // or (shallow models, and one block in isolation) all of its products
   size_t sk = 0;
-  auto upd = [&](int M, int N) {
-    int s = dw_splits(d, M, N);
-    if (s > 1) sk = std::max(sk, (size_t)s * M * N);
-    const DwTail t = dw_tail(d, M, N);
-    if (t.splits > 1) sk = std::max(sk, (size_t)t.splits * (M - t.m_main) * N);
-  };
-  upd(3 * d.C, d.C); upd(d.C, d.C); upd(d.F, d.C); upd(d.C, d.F); upd(d.Vp, d.C);
-  const DwGroupedTail gt = dw_grouped_tail(d);
-  if (gt.np > 0) sk = std::max(sk, (size_t)gt.splits * gt.np * d.C * d.F);
-  w.splitk_elems = sk;
-  // bias partial sums of the weight gradients that carry a bias gradient
-  size_t bs = 0;
-  auto bupd = [&](int M, int N) {
-    const int s = dw_splits(d, M, N);
-    bs = std::max(bs, (size_t)gemm_bias_parts(M, N, s) * M);
-  };
-  bupd(3 * d.C, d.C); bupd(d.F, d.C); bupd(d.C, d.F);
-  w.bsum_elems = bs;
+  if (const int s = dw_splits(d, d.Vp, d.C); s > 1) sk = (size_t)s * d.Vp * d.C;
+  const DwTail ht = dw_tail(d, d.Vp, d.C);
+  if (ht.splits > 1) sk = std::max(sk, (size_t)ht.splits * (d.Vp - ht.m_main) * d.C);
+  size_t pq = 0, pf = 0, pp = 0;   // bias partial rows of the groups, times their layers
+  for (int nl : {1, d.L}) {
+    const DwPlan p = dw_plan(d, nl);
+    const size_t per_layer = 4 * C * C + 2 * C * F;
+    if (p.splits > 1) sk = std::max(sk, (size_t)p.splits * nl * per_layer);
+    if (p.np > 0) sk = std::max(sk, (size_t)p.tail_splits * p.np * C * F);
+    const GemmGroupedArgs gg = dw_groups(d, nl);
+    pq = std::max(pq, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_QKV));
+    pf = std::max(pf, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_FC));
+    if (nl == 1) pp = (size_t)p.splits * gemm_grouped_bias_parts(gg, G_FCPROJ);
+  }
   // products into the residual stream: the attention and MLP-down projections,
   // and the input gradients of MLP up, q|k|v and the head
   size_t xs = 0;
@@ -288,13 +314,10 @@ WsLayout ws_layout(const Dims& d) {
   xupd(d.C, 0); xupd(d.F, 0); xupd(d.F, 1); xupd(3 * d.C, 1); xupd(d.Vp, 1);
   size_t o = 0;
   w.xsl = o; o += align_up(xs * 4);
-  w.dres = o; o += align_up(BT * C * 2);
   w.dh = o; o += align_up(BT * C * 2);
   w.datt = o; o += align_up(BT * C * 2);
-  w.dbig = o; o += align_up(BT * wide * 2);
   w.dsum = o; o += align_up((size_t)d.B * d.H * d.T * 4);
   w.splitk = o; o += align_up(sk * 4);
-  w.bsum = o; o += align_up(w.bsum_elems * 4);
   // LayerNorm backward partial sums: one slot per LayerNorm of the model
   // (2L + 1), so that the training backward reduces them all in one launch
   w.s_lnpart = align_up((size_t)layernorm_bwd_blocks((int)BT) * 3 * C * 4);
@@ -307,9 +330,9 @@ WsLayout ws_layout(const Dims& d) {
   w.dres_l = o; o += (2 * (size_t)d.L + 1) * w.s_dres;
   w.dfc_l = o; o += (size_t)d.L * w.s_dfc;
   w.dqkv_l = o; o += (size_t)d.L * w.s_dqkv;
-  const GemmGroupedArgs gg = dw_groups(d);
-  w.gbs_qkv = o; o += align_up((size_t)gemm_grouped_bias_parts(gg, G_QKV) * d.L * 3 * C * 4);
-  w.gbs_fc = o; o += align_up((size_t)gemm_grouped_bias_parts(gg, G_FC) * d.L * F * 4);
+  w.gbs_qkv = o; o += align_up(pq * 3 * C * 4);
+  w.gbs_fc = o; o += align_up(pf * F * 4);
+  w.gbs_fp = o; o += align_up(pp * C * 4);
   w.ce_stats = o; o += align_up(BT * (size_t)gemm_ce_parts((int)BT, d.Vp, d.C) * 8);
   w.ce_tlogit = o; o += align_up(BT * 4);
   w.ce_lse = o; o += align_up(BT * 4);
@@ -413,13 +436,12 @@ int gemm_class(int a_t, int b_t, int epi) {
 hipError_t gemm(Model* m, int cls, int M, int N, int K, const bf16_t* A, int lda, int a_t, const bf16_t* B,
                 int ldb, int b_t, int epi, void* C, int ldc, const float* bias = nullptr,
                 const bf16_t* residual = nullptr, bf16_t* C2 = nullptr, const bf16_t* aux = nullptr,
-                int accumulate = 0, int splits = 1, long split_stride = 0, int k_chunk = 0, double alg_flops = 0.0,
-                float* bsum = nullptr) {
+                int accumulate = 0, int splits = 1, long split_stride = 0, int k_chunk = 0,
+                double alg_flops = 0.0) {
   GemmArgs g{};
   g.A = A; g.B = B; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb;
   g.C = C; g.ldc = ldc; g.bias = bias; g.residual = residual; g.C2 = C2; g.aux = aux;
   g.accumulate = accumulate; g.splits = splits; g.split_stride = split_stride; g.k_chunk = k_chunk;
-  g.bsum = bsum;
   // algorithmic FLOPs: the tied head passes its count over the real vocabulary
   // only (the padded columns are computed but carry no probability)
   const double fl = alg_flops > 0.0 ? alg_flops : 2.0 * M * N * K;
@@ -427,29 +449,21 @@ hipError_t gemm(Model* m, int cls, int M, int N, int K, const bf16_t* A, int lda
   return m->run(gemm_class(a_t, b_t, epi), fl, 0.0, [&] { return launch_gemm(g, a_t, b_t, epi, m->stream); });
 }
 
-// weight gradient dW[M][N] (=|+=) sum_t A[t][m] * X[t][n] (fp32); with db,
-// also the bias gradient db[M] (=|+=) sum_t A[t][m], summed by the GEMM from
-// the A fragments it reads and reduced together with its contraction split
+// weight gradient dW[M][N] (=|+=) sum_t A[t][m] * X[t][n] (fp32) of one product;
+// m_real: the rows that count as work
 hipError_t weight_grad(Model* m, int M, int N, const bf16_t* dy, const bf16_t* x, float* dW, int accumulate,
-                       int m_real = 0, float* db = nullptr) {
+                       int m_real) {
   const int BT = (int)m->d.BT;
-  const int mr = m_real ? m_real : M;
-  const double fl = 2.0 * mr * (double)N * BT;
-  int s = dw_splits(m->d, M, N);
-  float* bp = db ? m->wsf(m->ws.bsum) : nullptr;
+  const double fl = 2.0 * m_real * (double)N * BT;
+  const int s = dw_splits(m->d, M, N);
   if (s <= 1) {
     const DwTail t = dw_tail(m->d, M, N);
-    if (t.splits <= 1 || db) {
-      hipError_t e = gemm(m, GPT2_K_GEMM_DW, M, N, BT, dy, M, 1, x, N, 1, EPI_F32, dW, N, nullptr, nullptr, nullptr,
-                          nullptr, accumulate, 1, 0, 0, fl, bp);
-      if (e != hipSuccess || !db) return e;
-      const int np = gemm_bias_parts(M, N, 1);
-      return m->run(GPT2_K_OTHER, 0.0, 4.0 * (double)M * (np + 1 + accumulate),
-                    [&] { return launch_reduce_slices(bp, np, M, db, accumulate, m->stream); });
-    }
+    if (t.splits <= 1)
+      return gemm(m, GPT2_K_GEMM_DW, M, N, BT, dy, M, 1, x, N, 1, EPI_F32, dW, N, nullptr, nullptr, nullptr, nullptr,
+                  accumulate, 1, 0, 0, fl);
     // whole rounds unsplit, the rest split over tokens and reduced
     const int m0 = t.m_main, m1 = M - t.m_main;
-    const double fl0 = 2.0 * std::min(mr, m0) * (double)N * BT, fl1 = fl - fl0;
+    const double fl0 = 2.0 * std::min(m_real, m0) * (double)N * BT, fl1 = fl - fl0;
     hipError_t e = gemm(m, GPT2_K_GEMM_DW, m0, N, BT, dy, M, 1, x, N, 1, EPI_F32, dW, N, nullptr, nullptr, nullptr,
                         nullptr, accumulate, 1, 0, 0, fl0);
     if (e != hipSuccess) return e;
@@ -463,16 +477,10 @@ hipError_t weight_grad(Model* m, int M, int N, const bf16_t* dy, const bf16_t* x
   }
   float* part = m->wsf(m->ws.splitk);
   hipError_t e = gemm(m, GPT2_K_GEMM_DW, M, N, BT, dy, M, 1, x, N, 1, EPI_F32, part, N, nullptr, nullptr, nullptr,
-                      nullptr, 0, s, (long)M * N, dw_chunk(m->d, M, N), fl, bp);
+                      nullptr, 0, s, (long)M * N, dw_chunk(m->d, M, N), fl);
   if (e != hipSuccess) return e;
-  if (!db)
-    return m->run(GPT2_K_OTHER, 0.0, 4.0 * (double)M * N * (s + 1 + accumulate),
-                  [&] { return launch_reduce_slices(part, s, (long)M * N, dW, accumulate, m->stream); });
-  const int np = gemm_bias_parts(M, N, s);
-  return m->run(GPT2_K_OTHER, 0.0, 4.0 * ((double)M * N * (s + 1 + accumulate) + (double)M * (np + 1 + accumulate)),
-                [&] {
-                  return launch_reduce_slices2(part, s, (long)M * N, dW, bp, np, M, db, accumulate, m->stream);
-                });
+  return m->run(GPT2_K_OTHER, 0.0, 4.0 * (double)M * N * (s + 1 + accumulate),
+                [&] { return launch_reduce_slices(part, s, (long)M * N, dW, accumulate, m->stream); });
 }
 
 // A product [BT, C] of the residual stream, A [BT, K] times B, left as fp32
@@ -490,16 +498,14 @@ hipError_t sliced_product(Model* m, int K, const bf16_t* A, const bf16_t* B, int
               0, n, (long)BT * C, kc, alg_flops);
 }
 
-hipError_t ln_fwd(Model* m, const bf16_t* x, const float* w, const float* b, bf16_t* y, float* mean, float* rstd) {
+// xcopy: also write x there (null: not)
+hipError_t ln_fwd(Model* m, const bf16_t* x, const float* w, const float* b, bf16_t* y, float* mean, float* rstd,
+                  bf16_t* xcopy = nullptr) {
   const int BT = (int)m->d.BT, C = m->d.C;
-  return m->run(GPT2_K_LAYERNORM, 0.0, 4.0 * BT * C + 8.0 * BT + 8.0 * C,
-                [&] { return launch_layernorm_fwd(x, w, b, y, mean, rstd, BT, C, m->cfg.ln_eps, m->stream); });
+  return m->run(GPT2_K_LAYERNORM, 0.0, (xcopy ? 6.0 : 4.0) * BT * C + 8.0 * BT + 8.0 * C,
+                [&] { return launch_layernorm_fwd(x, w, b, y, mean, rstd, BT, C, m->cfg.ln_eps, m->stream, xcopy); });
 }
 
-// LayerNorm backward into the residual-stream gradient: dres_out = (has_res ?
-// dres_in : 0) + dx; also writes the gain and shift gradients and, when dbias
-// is given, the column sum of the new residual gradient (the bias gradient of
-// the projection that produced it).
 // The queued LayerNorm backward reductions, in one launch.
 hipError_t reduce_ln_parts(Model* m) {
   ReducePartsJobs& J = m->ln_jobs;
@@ -512,44 +518,41 @@ hipError_t reduce_ln_parts(Model* m) {
   return e;
 }
 
-// With slot >= 0 the partial sums go to that slot and their reduction is
-// queued for reduce_ln_parts; otherwise they are reduced at once.
-// dy: the bf16 gradient, unless sl holds it as slices.
-hipError_t ln_bwd(Model* m, const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean, const float* rstd, const float* w,
-                  const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* dw, float* db, float* dbias,
-                  int accumulate, int slot = -1) {
+// LayerNorm backward into the residual-stream gradient: dres_out = (has_res ?
+// dres_in : 0) + dx; also writes the gain and shift gradients and, when dbias
+// is given, the column sum of the new residual gradient (the bias gradient of
+// the projection that produced it). The partial sums go to slot `slot` of the LayerNorm partials and their
+// reduction is queued for reduce_ln_parts. dy: the bf16 gradient, unless sl
+// holds it as slices.
+hipError_t ln_bwd(Model* m, const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean, const float* rstd,
+                  const float* w, const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* dw, float* db,
+                  float* dbias, int accumulate, int slot) {
   const int BT = (int)m->d.BT, C = m->d.C;
-  float* part = m->wsf(m->ws.lnpart + (size_t)(slot < 0 ? 0 : slot) * m->ws.s_lnpart);
+  float* part = m->wsf(m->ws.lnpart + (size_t)slot * m->ws.s_lnpart);
   hipError_t e = m->run(GPT2_K_LAYERNORM, 0.0, 2.0 * BT * C * (3 + has_res) + 8.0 * BT, [&] {
     return launch_layernorm_bwd(dy, sl, x, mean, rstd, w, dres_in, dres_out, has_res, part, BT, C, m->stream);
   });
   if (e != hipSuccess) return e;
-  if (slot >= 0) {
-    ReducePartsJobs& J = m->ln_jobs;
-    if (J.count == REDUCE_JOBS || (J.count > 0 && m->ln_jobs_acc != accumulate)) {
-      e = reduce_ln_parts(m);
-      if (e != hipSuccess) return e;
-    }
-    J.part[J.count] = part;
-    J.d[J.count][0] = dw;
-    J.d[J.count][1] = db;
-    J.d[J.count][2] = dbias;
-    ++J.count;
-    m->ln_jobs_acc = accumulate;
-    return hipSuccess;
+  ReducePartsJobs& J = m->ln_jobs;
+  if (J.count == REDUCE_JOBS || (J.count > 0 && m->ln_jobs_acc != accumulate)) {
+    e = reduce_ln_parts(m);
+    if (e != hipSuccess) return e;
   }
-  int nb = layernorm_bwd_blocks(BT);
-  return m->run(GPT2_K_OTHER, 0.0, 4.0 * 3 * C * (nb + 1 + accumulate), [&] {
-    return launch_reduce_parts(part, nb, 3L * C, C, 3, dw, db, dbias, accumulate, m->stream);
-  });
+  J.part[J.count] = part;
+  J.d[J.count][0] = dw;
+  J.d[J.count][1] = db;
+  J.d[J.count][2] = dbias;
+  ++J.count;
+  m->ln_jobs_acc = accumulate;
+  return hipSuccess;
 }
 
-
+// dqkv: for the backward
 AttnArgs attn_args(Model* m, int slot, bf16_t* dqkv = nullptr) {
   AttnArgs a{};
   a.B = m->d.B; a.T = m->d.T; a.H = m->d.H; a.hd = m->d.hd;
   a.qkv = m->qkv(slot); a.out = m->att(slot); a.lse = m->lse(slot);
-  a.dout = m->wsb(m->ws.datt); a.dsum = m->wsf(m->ws.dsum); a.dqkv = dqkv ? dqkv : m->wsb(m->ws.dbig);
+  a.dout = m->wsb(m->ws.datt); a.dsum = m->wsf(m->ws.dsum); a.dqkv = dqkv;
   return a;
 }
 
@@ -619,10 +622,11 @@ hipError_t add_norm(Model* m, const bf16_t* res, const bf16_t* branch, bf16_t* x
 // The residual sum of a projection left as slices, and the pre-norm after it
 // (w == nullptr: the sum only).
 hipError_t slices_norm(Model* m, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
-                       const float* b, bf16_t* y, float* mean, float* rstd) {
+                       const float* b, bf16_t* y, float* mean, float* rstd, bf16_t* xcopy = nullptr) {
   const int BT = (int)m->d.BT, C = m->d.C;
   return m->run(GPT2_K_LAYERNORM, 0.0, (6.0 + 4.0 * sl.n) * BT * C + 8.0 * BT + 8.0 * C, [&] {
-    return launch_slices_layernorm_fwd(sl, bias, res, xsum, w, b, y, mean, rstd, BT, C, m->cfg.ln_eps, m->stream);
+    return launch_slices_layernorm_fwd(sl, bias, res, xsum, w, b, y, mean, rstd, BT, C, m->cfg.ln_eps, m->stream,
+                                       xcopy);
   });
 }
 
@@ -649,8 +653,10 @@ NextNorm next_norm(Model* m, int l, int a_next) {
 // With residual_norm 1 or 2, or a split MLP-down projection (sliced_product),
 // and next_a >= 0 the block also forms the next pre-norm (next_norm) with its
 // output and sets *next_done.
+// x_in: the block input to copy into slot `in` (null: it is there already);
+// x_out: a second place for the block output (null: none).
 gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, bool ln1_done = false,
-                      bool* next_done = nullptr) {
+                      bool* next_done = nullptr, const bf16_t* x_in = nullptr, bf16_t* x_out = nullptr) {
   const Dims& d = m->d;
   const int BT = (int)d.BT, C = d.C, F = d.F;
   const size_t oC = (size_t)l * C, o3C = (size_t)l * 3 * C, oF = (size_t)l * F;
@@ -658,7 +664,8 @@ gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, 
   bf16_t* branch = m->wsb(m->ws.datt);   // free during the forward pass
   if (next_done) *next_done = false;
   if (!ln1_done)
-    TRY(ln_fwd(m, m->res(in), m->pf(K_LN1W) + oC, m->pf(K_LN1B) + oC, m->ln1(a), m->ln1m(a), m->ln1r(a)));
+    TRY(ln_fwd(m, x_in ? x_in : m->res(in), m->pf(K_LN1W) + oC, m->pf(K_LN1B) + oC, m->ln1(a), m->ln1m(a),
+               m->ln1r(a), x_in ? m->res(in) : nullptr));
   TRY(gemm(m, GPT2_K_GEMM_FWD, BT, 3 * C, C, m->ln1(a), C, 0, m->pb(K_QKVW) + o3C * C, C, 0, EPI_BF16, m->qkv(a),
            3 * C, m->pf(K_QKVB) + o3C));
   AttnArgs aa = attn_args(m, a);
@@ -686,11 +693,14 @@ gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, 
     // the sum, and the next pre-norm when there is one to form
     NextNorm nn{};
     if (next_a >= 0) nn = next_norm(m, l, next_a);
-    TRY(slices_norm(m, sl, m->pf(K_FCPROJB) + oC, m->xmid(a), m->res(out), nn.w, nn.b, nn.y, nn.mean, nn.rstd));
+    TRY(slices_norm(m, sl, m->pf(K_FCPROJB) + oC, m->xmid(a), m->res(out), nn.w, nn.b, nn.y, nn.mean, nn.rstd,
+                    x_out));
+    x_out = nullptr;
     if (next_done) *next_done = next_a >= 0;
   } else if (!fused) {
     TRY(gemm(m, GPT2_K_GEMM_FWD, BT, C, F, m->gelu(a), F, 0, m->pb(K_FCPROJW) + oC * F, F, 0, EPI_BF16, m->res(out),
-             C, m->pf(K_FCPROJB) + oC, m->xmid(a)));
+             C, m->pf(K_FCPROJB) + oC, m->xmid(a), x_out));
+    x_out = nullptr;
   } else {
     TRY(gemm(m, GPT2_K_GEMM_FWD, BT, C, F, m->gelu(a), F, 0, m->pb(K_FCPROJW) + oC * F, F, 0, EPI_BF16, branch, C,
              m->pf(K_FCPROJB) + oC));
@@ -702,22 +712,18 @@ gpt2_status block_fwd(Model* m, int l, int in, int out, int a, int next_a = -1, 
       TRY(add_norm(m, m->xmid(a), branch, m->res(out), nullptr, nullptr, nullptr, nullptr, nullptr));
     }
   }
+  if (x_out) TRY(hipMemcpyAsync(x_out, m->res(out), (size_t)BT * C * 2, hipMemcpyDeviceToDevice, m->stream));
   return GPT2_OK;
 }
 
 // Gradient buffers of one block's backward: the residual-stream gradient
-// entering the block (at its output), after its MLP branch, and leaving it
-// (at its input); the MLP pre-activation gradient and the q|k|v gradient.
-// They may alias (the single-block path runs in place).
+// entering the block (at its output, only read), after its MLP branch, and
+// leaving it (at its input); the MLP pre-activation gradient and the q|k|v
+// gradient. All but the last are read again by the grouped weight gradients.
 struct BlockGrads {
-  bf16_t *dres_out, *dres_mid, *dres_in, *dfc, *dqkv;
+  const bf16_t* dres_out;
+  bf16_t *dres_mid, *dres_in, *dfc, *dqkv;
 };
-
-BlockGrads grads_in_place(Model* m) {
-  bf16_t* dres = m->wsb(m->ws.dres);
-  bf16_t* dbig = m->wsb(m->ws.dbig);
-  return {dres, dres, dres, dbig, dbig};
-}
 
 // the per-layer buffers the training backward keeps for the grouped
 // weight-gradient launch
@@ -728,14 +734,13 @@ BlockGrads grads_of_layer(Model* m, int l) {
           m->wsb(w.dqkv_l + (size_t)l * w.s_dqkv)};
 }
 
-// Backward of block l from the residual-stream gradient in gb.dres_out. When
-// fcproj_bias_done, the MLP output bias gradient (the column sum of dres_out)
-// was already produced by the LayerNorm backward that wrote it. When
-// write_prev_bias, the column sum of the outgoing gradient is the MLP output
-// bias gradient of block l-1. With defer_dw the four weight gradients (and
-// the q|k|v and MLP-up bias gradients) are left to the grouped launch.
-gpt2_status block_bwd(Model* m, int l, int acc, bool fcproj_bias_done, bool write_prev_bias, const BlockGrads& gb,
-                      bool defer_dw) {
+// Backward of block l from the residual-stream gradient in gb.dres_out (whose
+// column sum, the MLP output bias gradient, is left to whoever produced it or
+// to the grouped launch). When write_prev_bias, the column sum of the outgoing
+// gradient is the MLP output bias gradient of block l-1. The four weight
+// gradients (and the q|k|v and MLP-up bias gradients) are left to the grouped
+// launch.
+gpt2_status block_bwd(Model* m, int l, int acc, bool write_prev_bias, const BlockGrads& gb) {
   const Dims& d = m->d;
   const int BT = (int)d.BT, C = d.C, F = d.F;
   const size_t oC = (size_t)l * C, o3C = (size_t)l * 3 * C, oF = (size_t)l * F;
@@ -744,19 +749,14 @@ gpt2_status block_bwd(Model* m, int l, int acc, bool fcproj_bias_done, bool writ
   // MLP down projection; GELU backward fused into the input-gradient epilogue
   TRY(gemm(m, GPT2_K_GEMM_DX, BT, F, C, gb.dres_out, C, 0, m->pb(K_FCPROJW) + oC * F, F, 1, EPI_GELU_BWD, gb.dfc, F,
            nullptr, nullptr, nullptr, m->fc(l)));
-  if (!defer_dw)
-    TRY(weight_grad(m, C, F, gb.dres_out, m->gelu(l), m->gf(K_FCPROJW) + oC * F, acc, 0,
-                    fcproj_bias_done ? nullptr : m->gf(K_FCPROJB) + oC));
   // MLP up projection
   Slices sl;
   TRY(sliced_product(m, F, gb.dfc, m->pb(K_FCW) + oF * C, C, 1, 0.0, &sl));
   if (sl.n == 0) TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, F, gb.dfc, F, 0, m->pb(K_FCW) + oF * C, C, 1, EPI_BF16, dh, C));
-  if (!defer_dw) TRY(weight_grad(m, F, C, gb.dfc, m->ln2(l), m->gf(K_FCW) + oF * C, acc, 0, m->gf(K_FCB) + oF));
   TRY(ln_bwd(m, dh, sl, m->xmid(l), m->ln2m(l), m->ln2r(l), m->pf(K_LN2W) + oC, gb.dres_out, gb.dres_mid, 1,
-             m->gf(K_LN2W) + oC, m->gf(K_LN2B) + oC, m->gf(K_ATTPROJB) + oC, acc, defer_dw ? 2 * l + 1 : -1));
+             m->gf(K_LN2W) + oC, m->gf(K_LN2B) + oC, m->gf(K_ATTPROJB) + oC, acc, 2 * l + 1));
   // attention output projection (its bias gradient came from the LayerNorm above)
   TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, C, gb.dres_mid, C, 0, m->pb(K_ATTPROJW) + oC * C, C, 1, EPI_BF16, datt, C));
-  if (!defer_dw) TRY(weight_grad(m, C, C, gb.dres_mid, m->att(l), m->gf(K_ATTPROJW) + oC * C, acc));
   // attention
   AttnArgs aa = attn_args(m, l, gb.dqkv);
   TRY(m->run(GPT2_K_ATTN_BWD, 2.0 * attn_fwd_flops(d), 0.0, [&] { return launch_attention_bwd(aa, m->stream); }));
@@ -764,80 +764,107 @@ gpt2_status block_bwd(Model* m, int l, int acc, bool fcproj_bias_done, bool writ
   TRY(sliced_product(m, 3 * C, gb.dqkv, m->pb(K_QKVW) + o3C * C, C, 1, 0.0, &sl));
   if (sl.n == 0)
     TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, 3 * C, gb.dqkv, 3 * C, 0, m->pb(K_QKVW) + o3C * C, C, 1, EPI_BF16, dh, C));
-  if (!defer_dw)
-    TRY(weight_grad(m, 3 * C, C, gb.dqkv, m->ln1(l), m->gf(K_QKVW) + o3C * C, acc, 0, m->gf(K_QKVB) + o3C));
   float* prev_bias = (write_prev_bias && l > 0) ? m->gf(K_FCPROJB) + (size_t)(l - 1) * C : nullptr;
   TRY(ln_bwd(m, dh, sl, m->res(l), m->ln1m(l), m->ln1r(l), m->pf(K_LN1W) + oC, gb.dres_mid, gb.dres_in, 1,
-             m->gf(K_LN1W) + oC, m->gf(K_LN1B) + oC, prev_bias, acc, defer_dw ? 2 * l : -1));
+             m->gf(K_LN1W) + oC, m->gf(K_LN1B) + oC, prev_bias, acc, 2 * l));
   return GPT2_OK;
 }
 
-// Every block weight gradient in one launch, from the layers' kept gradients
-// and saved activations: no contraction split, so no partial slices; then the
-// q|k|v and MLP-up bias gradients from the launch's partial sums.
-gpt2_status grouped_weight_grads(Model* m, int acc) {
+// The weight gradients of blocks l0 .. l0+nl-1 in one launch, from the layers'
+// kept gradients and saved activations (dw_plan says how it fills the chip);
+// then one launch for every reduction it leaves: split products' slices and
+// the bias gradients from the launch's partial sums. dres_out: for a block in
+// isolation, the gradient at its output (the MLP-down product's dY, whose
+// column sum is then taken here as well); null: the kept ones.
+gpt2_status grouped_weight_grads(Model* m, int l0, int nl, int acc, const bf16_t* dres_out = nullptr) {
   const Dims& d = m->d;
   const WsLayout& w = m->ws;
   const ActLayout& a = m->act;
-  const size_t C = d.C, F = d.F;
-  GemmGroupedArgs g = dw_groups(d);
+  const size_t C = d.C, F = d.F, l = l0;
+  GemmGroupedArgs g = dw_groups(d, nl);
   g.accumulate = acc;
   GemmGroup* q = &g.grp[G_QKV];
-  q->A = m->wsb(w.dqkv_l); q->a_stride = (long)(w.s_dqkv / 2); q->lda = (int)(3 * C);
-  q->B = m->ln1(0); q->b_stride = (long)(a.s_act / 2); q->ldb = (int)C;
-  q->C = m->gf(K_QKVW); q->c_stride = (long)(3 * C * C);
+  q->A = m->wsb(w.dqkv_l + l * w.s_dqkv); q->a_stride = (long)(w.s_dqkv / 2); q->lda = (int)(3 * C);
+  q->B = m->ln1(l0); q->b_stride = (long)(a.s_act / 2); q->ldb = (int)C;
+  q->C = m->gf(K_QKVW) + l * 3 * C * C; q->c_stride = (long)(3 * C * C);
   q->bsum = m->wsf(w.gbs_qkv);
   GemmGroup* ap = &g.grp[G_ATTPROJ];
-  ap->A = m->wsb(w.dres_l + w.s_dres); ap->a_stride = (long)(w.s_dres); ap->lda = (int)C;   // slots 2l+1
-  ap->B = m->att(0); ap->b_stride = (long)(a.s_act / 2); ap->ldb = (int)C;
-  ap->C = m->gf(K_ATTPROJW); ap->c_stride = (long)(C * C);
+  ap->A = m->wsb(w.dres_l + (2 * l + 1) * w.s_dres); ap->a_stride = (long)(w.s_dres); ap->lda = (int)C;   // slots 2l+1
+  ap->B = m->att(l0); ap->b_stride = (long)(a.s_act / 2); ap->ldb = (int)C;
+  ap->C = m->gf(K_ATTPROJW) + l * C * C; ap->c_stride = (long)(C * C);
   GemmGroup* fc = &g.grp[G_FC];
-  fc->A = m->wsb(w.dfc_l); fc->a_stride = (long)(w.s_dfc / 2); fc->lda = (int)F;
-  fc->B = m->ln2(0); fc->b_stride = (long)(a.s_act / 2); fc->ldb = (int)C;
-  fc->C = m->gf(K_FCW); fc->c_stride = (long)(F * C);
+  fc->A = m->wsb(w.dfc_l + l * w.s_dfc); fc->a_stride = (long)(w.s_dfc / 2); fc->lda = (int)F;
+  fc->B = m->ln2(l0); fc->b_stride = (long)(a.s_act / 2); fc->ldb = (int)C;
+  fc->C = m->gf(K_FCW) + l * F * C; fc->c_stride = (long)(F * C);
   fc->bsum = m->wsf(w.gbs_fc);
   GemmGroup* fp = &g.grp[G_FCPROJ];
-  fp->A = m->wsb(w.dres_l + 2 * w.s_dres); fp->a_stride = (long)(w.s_dres); fp->lda = (int)C;   // slots 2l+2
-  fp->B = m->gelu(0); fp->b_stride = (long)(a.s_ff / 2); fp->ldb = (int)F;
-  fp->C = m->gf(K_FCPROJW); fp->c_stride = (long)(C * F);
-  // the last np MLP-down products as a fifth group with a split contraction
-  // (slices in the split-K buffer)
-  const DwGroupedTail gt = dw_grouped_tail(d);
-  float* tail_dst = nullptr;
-  if (gt.np > 0) {
-    const int keep = (int)d.L - gt.np;
+  fp->A = dres_out ? dres_out : m->wsb(w.dres_l + (2 * l + 2) * w.s_dres);   // slots 2l+2
+  fp->a_stride = (long)(w.s_dres); fp->lda = (int)C;
+  fp->B = m->gelu(l0); fp->b_stride = (long)(a.s_ff / 2); fp->ldb = (int)F;
+  fp->C = m->gf(K_FCPROJW) + l * C * F; fp->c_stride = (long)(C * F);
+  if (dres_out) fp->bsum = m->wsf(w.gbs_fp);
+
+  ReduceSegs rs{};
+  const DwPlan plan = dw_plan(d, nl);
+  if (plan.splits > 1) {
+    // every product in slices, group after group in the split-K buffer
+    float* part = m->wsf(w.splitk);
+    for (int i = 0; i < 4; ++i) {
+      GemmGroup& gr = g.grp[i];
+      const long n = (long)gr.M * gr.N * nl;
+      rs.add(part, plan.splits, n, gr.C, n);
+      gr.C = part;
+      gr.splits = plan.splits;
+      gr.k_chunk = plan.chunk;
+      gr.split_stride = n;
+      part += (size_t)plan.splits * n;
+    }
+  } else if (plan.np > 0) {
+    // the last np MLP-down products as a fifth group with a split contraction
+    const int keep = nl - plan.np;
     GemmGroup* tl = &g.grp[g.ngroups++];
     *tl = *fp;
     fp->count = keep;
-    tl->count = gt.np;
+    tl->count = plan.np;
     tl->A = fp->A + (size_t)keep * fp->a_stride;
     tl->B = fp->B + (size_t)keep * fp->b_stride;
     tl->C = m->wsf(w.splitk);
-    tl->splits = gt.splits;
-    tl->k_chunk = gt.chunk;
-    tl->split_stride = (long)gt.np * (long)(C * F);
-    g.nfull = gt.nfull;
-    tail_dst = m->gf(K_FCPROJW) + (size_t)keep * C * F;
+    tl->splits = plan.tail_splits;
+    tl->k_chunk = plan.tail_chunk;
+    tl->split_stride = (long)plan.np * (long)(C * F);
+    g.nfull = plan.nfull;
+    rs.add(tl->C, plan.tail_splits, tl->split_stride, fp->C + (size_t)keep * C * F, tl->split_stride);
   }
-  double fl = 0.0;
+  const long nq = (long)nl * 3 * C, nf = (long)nl * F;
+  rs.add(q->bsum, plan.splits * gemm_grouped_bias_parts(g, G_QKV), nq, m->gf(K_QKVB) + l * 3 * C, nq);
+  rs.add(fc->bsum, plan.splits * gemm_grouped_bias_parts(g, G_FC), nf, m->gf(K_FCB) + l * F, nf);
+  if (dres_out)
+    rs.add(fp->bsum, plan.splits * gemm_grouped_bias_parts(g, G_FCPROJ), (long)C, m->gf(K_FCPROJB) + l * C, (long)C);
+  double fl = 0.0, by = 0.0;
   for (int i = 0; i < g.ngroups; ++i) fl += 2.0 * g.grp[i].M * (double)g.grp[i].N * d.BT * g.grp[i].count;
+  for (int i = 0; i < rs.count; ++i) by += 4.0 * rs.s[i].n * (rs.s[i].slices + 1 + acc);
   TRY(m->run(GPT2_K_GEMM_DW_GROUPED, fl, 0.0, [&] { return launch_gemm_grouped(g, m->stream); }));
-  if (tail_dst) {
-    const long n = (long)gt.np * (long)(C * F);
-    TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * n * (gt.splits + 1 + acc), [&] {
-      return launch_reduce_slices2(m->wsf(w.splitk), gt.splits, n, tail_dst, nullptr, 0, 0, nullptr, acc, m->stream);
-    }));
-  }
-  const int pq = gemm_grouped_bias_parts(g, G_QKV), pf = gemm_grouped_bias_parts(g, G_FC);
-  const long nq = (long)d.L * 3 * C, nf = (long)d.L * F;
-  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * nq * (pq + 1 + acc), [&] {
-    return launch_reduce_parts(m->wsf(w.gbs_qkv), pq, nq, (int)nq, 1, m->gf(K_QKVB), nullptr, nullptr, acc,
-                               m->stream);
-  }));
-  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * nf * (pf + 1 + acc), [&] {
-    return launch_reduce_parts(m->wsf(w.gbs_fc), pf, nf, (int)nf, 1, m->gf(K_FCB), nullptr, nullptr, acc, m->stream);
-  }));
+  TRY(m->run(GPT2_K_OTHER, 0.0, by, [&] { return launch_reduce_segs(rs, acc, m->stream); }));
   return GPT2_OK;
+}
+
+// Whether kernels can take a caller's [BT, C] buffer in place of a copy: its
+// alignment allows their accesses, and it is none of the model's own memory
+// (which the pass reads and writes as it goes) nor overlaps `other`.
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
+bool in_place_ok(const Model* m, const void* p, size_t align, const void* other) {
+  const size_t bytes = (size_t)m->d.BT * m->d.C * 2, n = m->n_params;
+  if (!p || reinterpret_cast<uintptr_t>(p) % align || overlap(p, bytes, other, bytes)) return false;
+  const gpt2_buffers& b = m->buf;
+  const std::pair<const void*, size_t> own[] = {
+      {b.params_f32, 4 * n}, {b.grads_f32, 4 * n}, {b.adam_m, 4 * n},         {b.adam_v, 4 * n},
+      {b.params_bf16, 2 * n}, {b.activations, m->act.total}, {b.workspace, m->ws.total}};
+  for (const auto& o : own)
+    if (overlap(p, bytes, o.first, o.second)) return false;
+  return true;
 }
 
 double lr_schedule(const gpt2_config& c, int64_t step) {
@@ -1130,11 +1157,11 @@ gpt2_status gpt2_backward(gpt2_model* m, int32_t accumulate) {
     TRY(gemm(m, GPT2_K_GEMM_DX, BT, C, d.Vp, m->logits(), d.Vp, 0, m->pb(K_WTE), C, 1, EPI_BF16, dh, C, nullptr,
              nullptr, nullptr, nullptr, 0, 1, 0, 0, head_fl));
   TRY(weight_grad(m, d.Vp, C, m->logits(), m->lnf(), m->gf(K_WTE), acc, d.V));
-  bf16_t* dres_top = grads_of_layer(m, d.L - 1).dres_out;   // written, not read (has_res 0)
+  bf16_t* dres_top = m->wsb(m->ws.dres_l + 2 * (size_t)d.L * m->ws.s_dres);   // written, not read (has_res 0)
   TRY(ln_bwd(m, dh, sl, m->res(d.L), m->lnfm(), m->lnfr(), m->pf(K_LNFW), dres_top, dres_top, 0, m->gf(K_LNFW),
              m->gf(K_LNFB), m->gf(K_FCPROJB) + (size_t)(d.L - 1) * C, acc, 2 * d.L));
   for (int l = d.L - 1; l >= 0; --l) {
-    gpt2_status s = block_bwd(m, l, acc, true, true, grads_of_layer(m, l), true);
+    gpt2_status s = block_bwd(m, l, acc, true, grads_of_layer(m, l));
     if (s != GPT2_OK) return s;
   }
   const bf16_t* dres = grads_of_layer(m, 0).dres_in;
@@ -1144,7 +1171,7 @@ gpt2_status gpt2_backward(gpt2_model* m, int32_t accumulate) {
   TRY(m->run(GPT2_K_OTHER, 0.0, 2.0 * BT * C + 4.0 * d.Tmax * C * (1 + acc),
              [&] { return launch_embed_bwd_pos(dres, m->gf(K_WPE), d.B, d.T, d.Tmax, C, acc, m->stream); }));
   {
-    gpt2_status s = grouped_weight_grads(m, acc);
+    gpt2_status s = grouped_weight_grads(m, 0, d.L, acc);
     if (s != GPT2_OK) return s;
   }
   // every LayerNorm's gain, shift and following-bias gradients
@@ -1283,10 +1310,18 @@ gpt2_status gpt2_block_forward(gpt2_model* m, int32_t layer, const void* d_x_in,
   if (!m) return GPT2_ERR_INVALID_ARG;
   if (!d_x_in || layer < 0 || layer >= m->d.L) return m->fail(GPT2_ERR_INVALID_ARG, "bad block_forward argument");
   const size_t bytes = (size_t)m->d.BT * m->d.C * 2;
-  TRY(hipMemcpyAsync(m->res(layer), d_x_in, bytes, hipMemcpyDeviceToDevice, m->stream));
-  gpt2_status s = block_fwd(m, layer, layer, layer + 1, layer);
+  // the block's first kernel copies the input into the residual slot and its
+  // last one writes the output twice
+  const bf16_t* x_in = static_cast<const bf16_t*>(d_x_in);
+  bf16_t* x_out = static_cast<bf16_t*>(d_x_out);
+  if (!in_place_ok(m, x_in, 8, nullptr)) {
+    TRY(hipMemcpyAsync(m->res(layer), x_in, bytes, hipMemcpyDeviceToDevice, m->stream));
+    x_in = nullptr;
+  }
+  const bool direct = in_place_ok(m, x_out, 8, nullptr);
+  gpt2_status s = block_fwd(m, layer, layer, layer + 1, layer, -1, false, nullptr, x_in, direct ? x_out : nullptr);
   if (s != GPT2_OK) return s;
-  if (d_x_out) TRY(hipMemcpyAsync(d_x_out, m->res(layer + 1), bytes, hipMemcpyDeviceToDevice, m->stream));
+  if (x_out && !direct) TRY(hipMemcpyAsync(x_out, m->res(layer + 1), bytes, hipMemcpyDeviceToDevice, m->stream));
   return GPT2_OK;
 }
 
@@ -1295,11 +1330,27 @@ gpt2_status gpt2_block_backward(gpt2_model* m, int32_t layer, const void* d_dx_o
   if (!m) return GPT2_ERR_INVALID_ARG;
   if (!d_dx_out || layer < 0 || layer >= m->d.L) return m->fail(GPT2_ERR_INVALID_ARG, "bad block_backward argument");
   const size_t bytes = (size_t)m->d.BT * m->d.C * 2;
-  bf16_t* dres = m->wsb(m->ws.dres);
-  TRY(hipMemcpyAsync(dres, d_dx_out, bytes, hipMemcpyDeviceToDevice, m->stream));
-  gpt2_status s = block_bwd(m, layer, accumulate ? 1 : 0, false, false, grads_in_place(m), false);
+  const int acc = accumulate ? 1 : 0;
+  m->ln_jobs.count = 0;   // nothing queued from a pass that failed part-way
+  BlockGrads gb = grads_of_layer(m, layer);
+  // The gradient at the output is read until the weight gradients at the end,
+  // so it is copied when the gradient at the input goes over it.
+  const bf16_t* dy = static_cast<const bf16_t*>(d_dx_out);
+  bf16_t* dx = static_cast<bf16_t*>(d_dx_in);
+  bf16_t* dx_to = in_place_ok(m, dx, 8, nullptr) ? dx : gb.dres_in;
+  if (!in_place_ok(m, dy, 16, dx)) {
+    bf16_t* copy = m->wsb(m->ws.dres_l + (2 * (size_t)layer + 2) * m->ws.s_dres);
+    if (copy != dy) TRY(hipMemcpyAsync(copy, dy, bytes, hipMemcpyDeviceToDevice, m->stream));
+    dy = copy;
+  }
+  gb.dres_out = dy;
+  gb.dres_in = dx_to;
+  gpt2_status s = block_bwd(m, layer, acc, false, gb);
   if (s != GPT2_OK) return s;
-  if (d_dx_in) TRY(hipMemcpyAsync(d_dx_in, dres, bytes, hipMemcpyDeviceToDevice, m->stream));
+  s = grouped_weight_grads(m, layer, 1, acc, dy);
+  if (s != GPT2_OK) return s;
+  TRY(reduce_ln_parts(m));
+  if (dx && dx != dx_to) TRY(hipMemcpyAsync(dx, dx_to, bytes, hipMemcpyDeviceToDevice, m->stream));
   return GPT2_OK;
 }
 

@@ -38,7 +38,7 @@ struct GemmArgs {
   int ldc;
   const float* bias;       // [N] or null
   const bf16_t* residual;  // [M][ldc] or null
-  bf16_t* C2;              // second output of EPI_GELU
+  bf16_t* C2;              // second output of EPI_GELU; with a residual, a second copy of C (or null)
   const bf16_t* aux;       // pre-activation for EPI_GELU_BWD
   int accumulate;
   int splits;              // split of the contraction over grid.z (EPI_F32 only)
@@ -99,8 +99,8 @@ struct GemmArgs {
 // the group's products, stored one after another.
 // A group with splits > 1 divides its contraction into `splits` chunks of
 // k_chunk tokens (a multiple of 64): product p's chunk z writes the plain sum
-// (never accumulating) to C_p + z * split_stride, for the caller to reduce;
-// such a group carries no bsum. With nfull > 0 the groups before the last
+// (never accumulating) to C_p + z * split_stride, for the caller to reduce,
+// and its bsum rows to slots z * gemm_bias_parts(M, N, 1) on. With nfull > 0 the groups before the last
 // one hold nfull tiles and the last one the rest (both multiples of 8), and
 // each of the 8 XCDs takes an equal share of both (the last group's tiles
 // filling the final round).
@@ -124,8 +124,8 @@ struct GemmGroupedArgs {
   int nfull;   // tiles before the last group when its tiles fill the final round (0: no such plan)
 };
 hipError_t launch_gemm_grouped(const GemmGroupedArgs& g, hipStream_t s);
-// Partial rows (slots) a grouped launch writes for group i's bias sums; it
-// depends only on the groups' M and N
+// Partial rows (slots) a grouped launch writes for group i's bias sums, per
+// contraction chunk; it depends only on the groups' M and N
 int gemm_grouped_bias_parts(const GemmGroupedArgs& g, int i);
 
 // Block tile (bm x bn, contraction depth bk per stage, ns stages) the GEMM
@@ -176,7 +176,8 @@ hipError_t launch_attention_bwd(const AttnArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- layernorm
 hipError_t launch_layernorm_fwd(const bf16_t* x, const float* w, const float* b, bf16_t* y,
-                                float* mean, float* rstd, int rows, int C, float eps, hipStream_t s);
+                                float* mean, float* rstd, int rows, int C, float eps, hipStream_t s,
+                                bf16_t* xcopy = nullptr);   // xcopy: also write x there
 // The residual connection and the following pre-norm in one pass: xsum =
 // bf16(res + x) (fp32 sum, rounded to nearest even), then y = LayerNorm(xsum)
 // read from those rounded values, bit for bit what launch_residual_add
@@ -185,9 +186,10 @@ hipError_t launch_add_layernorm_fwd(const bf16_t* x, const bf16_t* res, bf16_t* 
                                     bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s);
 // The same with the branch given as a product's fp32 slices: xsum = bf16(sum of
 // the slices + bias + res), y = LayerNorm(xsum); with w == nullptr xsum only.
+// xcopy: xsum goes there too.
 hipError_t launch_slices_layernorm_fwd(const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum,
                                        const float* w, const float* b, bf16_t* y, float* mean, float* rstd, int rows,
-                                       int C, float eps, hipStream_t s);
+                                       int C, float eps, hipStream_t s, bf16_t* xcopy = nullptr);
 // out = bf16(res + x) elementwise (n % 4 == 0)
 hipError_t launch_residual_add(const bf16_t* res, const bf16_t* x, bf16_t* out, long n, hipStream_t s);
 // dres_out = (has_res ? dres_in : 0) + dx (dres_in may be dres_out; it is not
@@ -205,17 +207,25 @@ hipError_t launch_layernorm_bwd(const bf16_t* dy, const Slices& slices, const bf
 // dst[i] (fp32, n elements) = (accumulate ? dst[i] : 0) + sum_s src[s*n + i]
 hipError_t launch_reduce_slices(const float* src, int nslices, long n, float* dst, int accumulate,
                                 hipStream_t s);
-// The same for two independent segments in one launch (n and n2 multiples of 4)
-hipError_t launch_reduce_slices2(const float* src, int nslices, long n, float* dst, const float* src2,
-                                 int nslices2, long n2, float* dst2, int accumulate, hipStream_t s);
-// Sum over S slices of partial rows, for narrow rows and many slices:
-// dst_j[c] (=|+=) sum_s part[s*stride + j*n + c], for j < nd (up to 3
+// The same for several independent segments in one launch (n multiples of 4):
+// dst[i] (=|+=) sum_s src[s*stride + i]
+constexpr int REDUCE_SEGS = 8;
+struct ReduceSeg {
+  const float* src;
+  float* dst;
+  long n, stride;
+  int slices;
+};
+struct ReduceSegs {
+  ReduceSeg s[REDUCE_SEGS];
+  int count;
+  void add(const float* src, int slices, long stride, float* dst, long n) { s[count++] = {src, dst, n, stride, slices}; }
+};
+hipError_t launch_reduce_segs(const ReduceSegs& r, int accumulate, hipStream_t s);
+// Sums over S slices of partial rows, for narrow rows and many slices: job j
+// of up to REDUCE_JOBS, all of one shape, in one launch,
+// d[j][i][c] (=|+=) sum_s part[j][s*stride + i*n + c], for i < nd (up to 3
 // destinations, null ones skipped) and c < n. Fixed summation order.
-hipError_t launch_reduce_parts(const float* part, int S, long stride, int n, int nd, float* d0, float* d1,
-                               float* d2, int accumulate, hipStream_t s);
-// Up to REDUCE_JOBS such reductions of one shape (S slices of stride floats,
-// nd outputs of n) in one launch: job j sums part[j] into d[j][0..nd-1]
-// (null destinations skipped).
 constexpr int REDUCE_JOBS = 32;
 struct ReducePartsJobs {
   int count;

@@ -23,7 +23,8 @@ DEV uint2 add_rows(uint2 r, uint2 a) {
 // addition followed by this kernel would. With SRC_SLICES the branch comes as
 // fp32 slices of the projection before it (few rows: the product is split to
 // fill the chip), x = bf16(sum + bias + res), so the split costs no launch of
-// its own; w == nullptr then stops after xsum.
+// its own; w == nullptr then stops after xsum. xcopy (when not null) takes the
+// row that is normalised as well.
 constexpr int SRC_X = 0, SRC_RES = 1, SRC_SLICES = 2;
 template <int MAXCH, int SRC = SRC_X>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ x, Slices sl,
@@ -31,7 +32,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ 
                                                      bf16_t* __restrict__ xsum, const float* __restrict__ w,
                                                      const float* __restrict__ b, bf16_t* __restrict__ y,
                                                      float* __restrict__ mean_out, float* __restrict__ rstd_out,
-                                                     int rows, int C, float eps) {
+                                                     int rows, int C, float eps, bf16_t* __restrict__ xcopy) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -69,8 +70,15 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const bf16_t* __restrict__ 
       const int c = 4 * (lane + 64 * i);
       if (c < C) *reinterpret_cast<uint2*>(xsum + (size_t)row * C + c) = xu[i];
     }
-    if (SRC == SRC_SLICES && !w) return;
   }
+  if (xcopy) {
+#pragma unroll
+    for (int i = 0; i < MAXCH; ++i) {
+      const int c = 4 * (lane + 64 * i);
+      if (c < C) *reinterpret_cast<uint2*>(xcopy + (size_t)row * C + c) = xu[i];
+    }
+  }
+  if (SRC == SRC_SLICES && !w) return;
   float v[MAXCH][4];
   float s = 0.0f;
 #pragma unroll
@@ -251,27 +259,27 @@ __global__ void residual_add_kernel(const bf16_t* __restrict__ res, const bf16_t
 
 template <int MAXCH>
 hipError_t fwd_t(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
-                 const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
+                 const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s, bf16_t* xcopy) {
   const dim3 grid((rows + 3) / 4), block(256);
   if (sl.n > 0)
     hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_SLICES>), grid, block, 0, s, nullptr, sl, bias, res, xsum, w, b, y,
-                       mean, rstd, rows, C, eps);
+                       mean, rstd, rows, C, eps, xcopy);
   else if (res)
     hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_RES>), grid, block, 0, s, x, sl, nullptr, res, xsum, w, b, y, mean,
-                       rstd, rows, C, eps);
+                       rstd, rows, C, eps, xcopy);
   else
     hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_X>), grid, block, 0, s, x, sl, nullptr, nullptr, nullptr, w, b, y,
-                       mean, rstd, rows, C, eps);
+                       mean, rstd, rows, C, eps, xcopy);
   return hipGetLastError();
 }
 
 hipError_t fwd(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
-               const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
-  if (C <= 256) return fwd_t<1>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 512) return fwd_t<2>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 768) return fwd_t<3>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 1024) return fwd_t<4>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
-  if (C <= 2048) return fwd_t<8>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+               const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s, bf16_t* xcopy) {
+  if (C <= 256) return fwd_t<1>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
+  if (C <= 512) return fwd_t<2>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
+  if (C <= 768) return fwd_t<3>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
+  if (C <= 1024) return fwd_t<4>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
+  if (C <= 2048) return fwd_t<8>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
   return hipErrorInvalidValue;
 }
 
@@ -294,19 +302,20 @@ hipError_t bwd_t(const bf16_t* dy, const Slices& sl, const bf16_t* x, const floa
 hipError_t launch_add_layernorm_fwd(const bf16_t* x, const bf16_t* res, bf16_t* xsum, const float* w, const float* b,
                                     bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s) {
   if (C % 4 || (res && !xsum)) return hipErrorInvalidValue;
-  return fwd(x, {nullptr, 0}, nullptr, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  return fwd(x, {nullptr, 0}, nullptr, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, nullptr);
 }
 
 hipError_t launch_slices_layernorm_fwd(const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum,
                                        const float* w, const float* b, bf16_t* y, float* mean, float* rstd, int rows,
-                                       int C, float eps, hipStream_t s) {
+                                       int C, float eps, hipStream_t s, bf16_t* xcopy) {
   if (C % 4 || sl.n < 1 || !sl.p || !bias || !res || !xsum) return hipErrorInvalidValue;
-  return fwd(nullptr, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s);
+  return fwd(nullptr, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
 }
 
 hipError_t launch_layernorm_fwd(const bf16_t* x, const float* w, const float* b, bf16_t* y, float* mean,
-                                float* rstd, int rows, int C, float eps, hipStream_t s) {
-  return launch_add_layernorm_fwd(x, nullptr, nullptr, w, b, y, mean, rstd, rows, C, eps, s);
+                                float* rstd, int rows, int C, float eps, hipStream_t s, bf16_t* xcopy) {
+  if (C % 4) return hipErrorInvalidValue;
+  return fwd(x, {nullptr, 0}, nullptr, nullptr, nullptr, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
 }
 
 hipError_t launch_residual_add(const bf16_t* res, const bf16_t* x, bf16_t* out, long n, hipStream_t s) {

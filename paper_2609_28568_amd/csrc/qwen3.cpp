@@ -463,10 +463,11 @@ hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, con
     e = run_gemm(m, AD, mnk2(gg.n * d.r, gg.in, d.BT), r, 1, 1, EPI_F32);
     if (e != hipSuccess) return e;
     const long nb = (long)gg.out_total * RP, na = (long)nu * gg.in;
-    e = m->run(QWEN3_K_OTHER, 0.0, 4.0 * (double)(nb + na) * (splits + 1), [&] {
-      return launch_reduce_slices2(pb, splits, nb, static_cast<float*>(m->buf.lora_grads) + ob, pa, splits, na,
-                                   static_cast<float*>(m->buf.lora_grads) + oa, 0, m->stream);
-    });
+    ReduceSegs rs{};
+    rs.add(pb, splits, nb, static_cast<float*>(m->buf.lora_grads) + ob, nb);
+    rs.add(pa, splits, na, static_cast<float*>(m->buf.lora_grads) + oa, na);
+    e = m->run(QWEN3_K_OTHER, 0.0, 4.0 * (double)(nb + na) * (splits + 1),
+               [&] { return launch_reduce_segs(rs, 0, m->stream); });
     if (e != hipSuccess || !dx) return e;
     a.A2 = du; a.lda2 = nu; a.B2 = wa; a.ldb2 = gg.in; a.K2 = nu;
     fl += mnk2(d.BT, gg.in, gg.n * d.r);

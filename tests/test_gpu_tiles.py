@@ -52,3 +52,49 @@ def test_block_against_oracle(B, T):
         # with one token the softmax is constant: its query and key gradients are exactly 0
         e = rel_l2(g[k], grads[k])
         assert e < REL_L2, (k, e)
+
+
+# The caller's buffers stand in for copies unless they are misaligned, overlap
+# or lie in the model's own memory: every form gives the same bits.
+@pytest.mark.parametrize("form", ["misaligned", "same_buffer", "own_memory"])
+def test_block_buffer_forms(form):
+    from paper_2609_28568_amd import binding
+    B, T, C = 2, 75, 64
+    w = workload("tiny", n_layer=1, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=71), seed=72)
+    x, dy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in synth.block_inputs(w, seed=73))
+
+    def passes(x_in, x_out, d_out, d_in, m):
+        x_in.copy_(x)
+        m.block_forward(0, x_in, x_out)
+        y = x_out.clone()
+        d_out.copy_(dy)
+        m.block_backward(0, d_out, d_in)
+        return y, d_in.clone(), m.flat("grads")[64 * C + T * C:-2 * C].clone()
+
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    ref = passes(*(torch.empty_like(x) for _ in range(4)), m)
+    n = x.numel()
+
+    def odd():
+        return torch.empty(n + 1, dtype=torch.bfloat16, device="cuda")[1:].view(B * T, C)
+
+    if form == "misaligned":
+        bufs = [odd() for _ in range(4)]
+    elif form == "same_buffer":
+        a, b = torch.empty_like(x), torch.empty_like(x)
+        bufs = [a, a, b, b]
+    else:
+        bufs = [m.activation("lnf").view(B * T, C), m.activation("att", 0).view(B * T, C),
+                m.activation("lnf").view(B * T, C), m.activation("residual", 0).view(B * T, C)]
+        # the output lies over a saved activation that the backward reads: only
+        # the forward is compared with it, the backward with a fresh forward
+        bufs[0].copy_(x)
+        m.block_forward(0, bufs[0], bufs[1])
+        assert torch.equal(bufs[1], ref[0])
+        bufs[1] = torch.empty_like(x)
+    got = passes(*bufs, m)
+    m.close()
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
