@@ -821,19 +821,21 @@ gpt2_status grouped_weight_grads(Model* m, int l0, int nl, int acc, const bf16_t
     }
   } else if (plan.np > 0) {
     // the last np MLP-down products as a fifth group with a split contraction
+    // (the fourth when they are all of them)
     const int keep = nl - plan.np;
-    GemmGroup* tl = &g.grp[g.ngroups++];
-    *tl = *fp;
+    const GemmGroup whole = *fp;
+    GemmGroup* tl = keep > 0 ? &g.grp[g.ngroups++] : fp;
     fp->count = keep;
+    *tl = whole;
     tl->count = plan.np;
-    tl->A = fp->A + (size_t)keep * fp->a_stride;
-    tl->B = fp->B + (size_t)keep * fp->b_stride;
+    tl->A = whole.A + (size_t)keep * whole.a_stride;
+    tl->B = whole.B + (size_t)keep * whole.b_stride;
     tl->C = m->wsf(w.splitk);
     tl->splits = plan.tail_splits;
     tl->k_chunk = plan.tail_chunk;
     tl->split_stride = (long)plan.np * (long)(C * F);
     g.nfull = plan.nfull;
-    rs.add(tl->C, plan.tail_splits, tl->split_stride, fp->C + (size_t)keep * C * F, tl->split_stride);
+    rs.add(tl->C, plan.tail_splits, tl->split_stride, whole.C + (size_t)keep * C * F, tl->split_stride);
   }
   const long nq = (long)nl * 3 * C, nf = (long)nl * F;
   rs.add(q->bsum, plan.splits * gemm_grouped_bias_parts(g, G_QKV), nq, m->gf(K_QKVB) + l * 3 * C, nq);

@@ -98,3 +98,26 @@ def test_block_buffer_forms(form):
     m.close()
     for a, b in zip(got, ref):
         assert torch.equal(a, b)
+
+
+# Depths at the edges of the grouped weight-gradient plan at 768 wide (192
+# tiles a layer, rounds of 512): under a round (1, 2), every MLP-down product
+# in the split tail (4), a tail of some of them (7), no tail (8)
+@pytest.mark.parametrize("L", [1, 2, 4, 7, 8])
+def test_grouped_weight_gradients_by_depth(L):
+    from paper_2609_28568_amd import binding
+    w = workload("tiny", n_layer=L, n_head=12, d_model=768, d_ff=3072, vocab=64, vocab_padded=64, max_seq_len=33, B=2,
+                 T=33)
+    p = synth.perturb_params(synth.init_params(w, seed=81), seed=82)
+    ids, tgt = synth.token_batch(w, seed=83)
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    print(f"step of {L} layers", flush=True)
+    m.forward(torch.from_numpy(ids), torch.from_numpy(tgt))
+    m.backward()
+    g = m.to_dict("grads")
+    m.close()
+    ocfg = oracle_config(w)
+    ref = oracle.backward(p, oracle.forward(p, ids, tgt, ocfg), ocfg)
+    for k in oracle.KINDS:
+        assert rel_l2(g[k], ref[k]) < REL_L2, (k, rel_l2(g[k], ref[k]))
