@@ -121,3 +121,29 @@ def test_grouped_weight_gradients_by_depth(L):
     ref = oracle.backward(p, oracle.forward(p, ids, tgt, ocfg), ocfg)
     for k in oracle.KINDS:
         assert rel_l2(g[k], ref[k]) < REL_L2, (k, rel_l2(g[k], ref[k]))
+
+
+# The token-table scatter against a float64 sum: runs of one id that span
+# half-waves and workgroups, ids out of range skipped, few and many positions
+@pytest.mark.parametrize("n,distinct", [(1, 1), (255, 1), (257, 3), (1000, 500), (4096, 2), (4097, 4000), (5000, 37)])
+@pytest.mark.parametrize("C", [64, 192])
+def test_embedding_scatter(n, distinct, C):
+    from paper_2609_28568_amd import binding
+    V = 5000
+    w = workload("tiny", n_layer=1, n_head=C // 16, d_model=C, d_ff=4 * C, vocab=V, vocab_padded=5056, max_seq_len=n, B=1, T=n)
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    r = np.random.default_rng([91, n, distinct])
+    ids = r.permutation(V)[r.integers(0, distinct, n)].astype(np.int32)
+    bad = ids.copy()
+    bad[::97] = V + 5
+    dx = synth.round_to_bf16(r.standard_normal((n, C), dtype=np.float32))
+    print(f"scatter of {n} positions, {distinct} ids", flush=True)
+    m.embedding_backward(torch.from_numpy(bad), torch.from_numpy(dx).cuda().to(torch.bfloat16))
+    g = m.to_dict("grads")["wte"]
+    m.close()
+    ok = bad < V
+    ref, mag = np.zeros((5056, C)), np.zeros((5056, C))
+    np.add.at(ref, bad[ok], dx[ok].astype(np.float64))
+    np.add.at(mag, bad[ok], np.abs(dx[ok]).astype(np.float64))
+    # an n-term fp32 sum in any order is within n ulps of the sum of magnitudes
+    assert np.all(np.abs(g - ref) <= n * 2.0 ** -24 * mag)
