@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
     };
     if (diag) mask_max(std::true_type{});
     else mask_max(std::false_type{});
-    mt = fmaxf(mt, __shfl_xor(mt, 32, WAVE)) * sc;
+    mt = max32(mt) * sc;
     // key 0 is visible to every query, so after tile 0 the shift is finite
     const bool grow = mt > m_run + RESCALE_SLACK;
     if (__ballot(grow) != 0) {
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
         s[t][r] = p;
         rsum += p;
       }
-    l_run += rsum + __shfl_xor(rsum, 32, WAVE);
+    l_run += sum32(rsum);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnArgs a) {
   const float lse2 = q < T ? lse_q * LOG2E : 0.0f;
   // D = rowsum(dO * O) of query q: lanes lq and lq + 32 hold the two halves of
   // its row. Stored for the dK/dV kernel, which runs after this one.
-  const float dsum = dpart + __shfl_xor(dpart, 32);
+  const float dsum = sum32(dpart);
   if (g == 0 && q < T) a.dsum[(size_t)bh * T + q] = dsum;
   floatx16 dq[S::DT];
 #pragma unroll

@@ -58,15 +58,78 @@ DEV void st_stream(float4* p, float4 v) {
   __builtin_nontemporal_store(t, reinterpret_cast<f32x4_t*>(p));
 }
 
-DEV float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, WAVE);
+// Reductions over the lanes of a wave, as the butterfly over distances 32, 16,
+// 8, 4, 2, 1 computes them, without its round trips through the LDS pipeline
+// (ds_bpermute, over 100 cycles each; these are a few): v_permlane32_swap and
+// v_permlane16_swap pair the halves and the odd with the even rows of 16 lanes
+// (both results hold one side each, so combining the two is the exchange), and
+// rotations within a row of 16 do the rest: by 8 lanes it is the exchange
+// itself, and after it the values repeat every 8 lanes, so that a rotation by 4
+// is the exchange at distance 4, and so on. The additions are the butterfly's
+// own, hence the same bits.
+DEV float2 halves32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+DEV float2 rows16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int N>
+DEV float row_ror(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xf, 0xf, false));
+}
+// v of the lane at distance 8
+DEV float xor8(float v) { return row_ror<8>(v); }
+
+DEV float group16_sum(float v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
   return v;
 }
+DEV float sum32(float v) {   // v + v of the lane at distance 32
+  const float2 h = halves32(v);
+  return h.x + h.y;
+}
+DEV float max32(float v) {
+  const float2 h = halves32(v);
+  return fmaxf(h.x, h.y);
+}
+DEV float wave_sum(float v) {
+  v = sum32(v);
+  const float2 r = rows16(v);
+  return group16_sum(r.x + r.y);
+}
 DEV float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-  return v;
+  v = max32(v);
+  const float2 r = rows16(v);
+  v = fmaxf(r.x, r.y);
+  v = fmaxf(v, row_ror<8>(v));
+  v = fmaxf(v, row_ror<4>(v));
+  v = fmaxf(v, row_ror<2>(v));
+  return fmaxf(v, row_ror<1>(v));
+}
+
+// Softmax statistics (max m, sum s of exp(x - m)) of two sets merged into (m, s)
+DEV void merge_ms(float& m, float& s, float m2, float s2) {
+  const float mn = fmaxf(m, m2);
+  s = (m == -INFINITY ? 0.0f : s * __expf(m - mn)) + (m2 == -INFINITY ? 0.0f : s2 * __expf(m2 - mn));
+  m = mn;
+}
+// ... over the lanes of a wave, in the butterfly's order
+DEV void wave_merge_ms(float& m, float& s) {
+  float2 a = halves32(m), b = halves32(s);
+  m = a.x; s = b.x;
+  merge_ms(m, s, a.y, b.y);
+  a = rows16(m); b = rows16(s);
+  m = a.x; s = b.x;
+  merge_ms(m, s, a.y, b.y);
+  merge_ms(m, s, row_ror<8>(m), row_ror<8>(s));
+  merge_ms(m, s, row_ror<4>(m), row_ror<4>(s));
+  merge_ms(m, s, row_ror<2>(m), row_ror<2>(s));
+  merge_ms(m, s, row_ror<1>(m), row_ror<1>(s));
 }
 
 DEV floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {

@@ -23,19 +23,24 @@ __global__ void reduce_slices_kernel(const float* __restrict__ src, int nslices,
   *reinterpret_cast<float4*>(dst + i) = acc;
 }
 
-// Several independent reductions in one launch; blockIdx.y picks the segment,
-// whose blocks stride over its elements.
+// Several independent reductions in one launch; blockIdx.y picks the segment
+// (by a chain of selects over the first N: indexing the argument would put a
+// dependent load in front of every block).
+template <int N>
 __global__ __launch_bounds__(256) void reduce_segs_kernel(ReduceSegs r, int accumulate) {
-  const ReduceSeg g = r.s[blockIdx.y];
-  for (long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4; i < g.n; i += (long)gridDim.x * 1024) {
-    float4 acc = accumulate ? *reinterpret_cast<const float4*>(g.dst + i) : make_float4(0, 0, 0, 0);
+  ReduceSeg g = r.s[0];
+#pragma unroll
+  for (int k = 1; k < N; ++k)
+    if (blockIdx.y == k) g = r.s[k];
+  const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= g.n) return;
+  float4 acc = accumulate ? *reinterpret_cast<const float4*>(g.dst + i) : make_float4(0, 0, 0, 0);
 #pragma unroll 16
-    for (int k = 0; k < g.slices; ++k) {
-      float4 v = *reinterpret_cast<const float4*>(g.src + (size_t)k * g.stride + i);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-    *reinterpret_cast<float4*>(g.dst + i) = acc;
+  for (int k = 0; k < g.slices; ++k) {
+    float4 v = *reinterpret_cast<const float4*>(g.src + (size_t)k * g.stride + i);
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
+  *reinterpret_cast<float4*>(g.dst + i) = acc;
 }
 
 // 16 waves per block, 64 columns per block: wave w sums slices w, w+16, ...
@@ -389,13 +394,7 @@ __global__ __launch_bounds__(NT) void cross_entropy_kernel(bf16_t* __restrict__ 
   }
   opaque();
   // combine (m, se) over the wave, then over the waves
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const float m2 = __shfl_xor(m, o, WAVE), s2 = __shfl_xor(se, o, WAVE);
-    const float mn = fmaxf(m, m2);
-    se = (m == -INFINITY ? 0.0f : se * __expf(m - mn)) + (m2 == -INFINITY ? 0.0f : s2 * __expf(m2 - mn));
-    m = mn;
-  }
+  wave_merge_ms(m, se);
   if (lane == 0) {
     shm[w] = m;
     shs[w] = se;
@@ -439,12 +438,6 @@ __global__ __launch_bounds__(NT) void cross_entropy_kernel(bf16_t* __restrict__ 
 // GEMM's statistics epilogue): one wave per row, each lane merging every 64th
 // slice (max, sum of exponentials) pair, then the lanes merged in a fixed
 // butterfly order.
-DEV void merge_ms(float& m, float& s, float m2, float s2) {
-  const float mn = fmaxf(m, m2);
-  s = (m == -INFINITY ? 0.0f : s * __expf(m - mn)) + (m2 == -INFINITY ? 0.0f : s2 * __expf(m2 - mn));
-  m = mn;
-}
-
 __global__ __launch_bounds__(256) void ce_combine_kernel(const float2* __restrict__ stats, int nparts,
                                                          const float* __restrict__ tlogit,
                                                          const int32_t* __restrict__ targets, int V,
@@ -457,11 +450,7 @@ __global__ __launch_bounds__(256) void ce_combine_kernel(const float2* __restric
     const float2 p = stats[(size_t)row * nparts + k];
     merge_ms(m, sum, p.x, p.y);
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const float m2 = __shfl_xor(m, o, WAVE), s2 = __shfl_xor(sum, o, WAVE);
-    merge_ms(m, sum, m2, s2);
-  }
+  wave_merge_ms(m, sum);
   if (lane == 0) {
     const float l = m + logf(sum);
     lse[row] = l;
@@ -510,10 +499,11 @@ __global__ __launch_bounds__(256) void clip_coef_kernel(const float* __restrict_
 // Segments (parameter kinds) are walked in order, uniformly across the grid,
 // so each one's bounds and decay flag are scalars; within a segment every
 // thread updates 4-element chunks in a grid-stride loop, two chunks in
-// flight at a time. A segment starts on the block that its offset in the flat
-// buffer falls to, so that the short segments of a small model go to different
-// blocks instead of one block after another (135 K parameters in 16 segments:
-// 15.4 -> 7.5 us). Segment ends are multiples of 4 (checked at launch).
+// flight at a time. A segment shorter than the grid starts on the block that
+// its offset in the flat buffer falls to, so that the segments of a small model
+// go to different blocks instead of one block after another (135 K parameters
+// in 16 segments: 15.4 -> 7.5 us; the long segments of the 124M model ran
+// 669 -> 728 us when they were shifted too). Segment ends are multiples of 4 (checked at launch).
 __global__ __launch_bounds__(256) void adamw_kernel(AdamArgs a) {
   const float coef = a.norm_coef[1];
   const long stride = (long)gridDim.x * 256 * 4;
@@ -547,7 +537,7 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamArgs a) {
   for (int sg = 0; sg < a.seg.count; ++sg) {
     const long hi = a.seg.end[sg];
     const float wd = a.seg.decay[sg] ? a.weight_decay : 0.0f;
-    const unsigned first = (unsigned)((lo >> 10) % gridDim.x);
+    const unsigned first = hi - lo < stride ? (unsigned)((lo >> 10) % gridDim.x) : 0u;
     const unsigned vb = blockIdx.x >= first ? blockIdx.x - first : blockIdx.x + gridDim.x - first;
     long i = lo + ((long)vb * 256 + threadIdx.x) * 4;
     for (; i + stride < hi; i += 2 * stride) {
@@ -626,10 +616,9 @@ hipError_t launch_reduce_segs(const ReduceSegs& r, int accumulate, hipStream_t s
     if (r.s[i].n % 4 || r.s[i].n < 4 || r.s[i].stride % 4) return hipErrorInvalidValue;
     nmax = r.s[i].n > nmax ? r.s[i].n : nmax;
   }
-  // up to 2048 blocks per segment, eight on each CU
-  const unsigned blocks = blocks_for(nmax / 4, 256);
-  hipLaunchKernelGGL(reduce_segs_kernel, dim3(blocks < 2048 ? blocks : 2048, (unsigned)r.count), dim3(256), 0, s, r,
-                     accumulate);
+  const dim3 grid(blocks_for(nmax / 4, 256), (unsigned)r.count);
+  if (r.count <= 2) hipLaunchKernelGGL(reduce_segs_kernel<2>, grid, dim3(256), 0, s, r, accumulate);
+  else hipLaunchKernelGGL(reduce_segs_kernel<REDUCE_SEGS>, grid, dim3(256), 0, s, r, accumulate);
   return hipGetLastError();
 }
 

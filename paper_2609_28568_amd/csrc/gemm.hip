@@ -425,7 +425,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
       const size_t slot = ((size_t)split * ntn + tn) * 2 + wn;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const float v = bs[i] + __shfl_xor(bs[i], 32);
+        const float v = sum32(bs[i]);
         const int m = m0 + wm * WTM + 32 * i + (lane & 31);
         if (lane < 32 && m < g.M) g.bsum[slot * (g.bsum_ld ? g.bsum_ld : g.M) + m] = v;
       }
@@ -461,12 +461,13 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
             if (n < g.ce_V) se += __expf(acc[i][j][r] - mx);
             if (n == t && row_ok) g.ce_tlogit[mrow] = acc[i][j][r];
           }
-        const float m2 = __shfl_xor(mx, 32, WAVE), s2 = __shfl_xor(se, 32, WAVE);
-        const float mn = fmaxf(mx, m2);
-        se = (mx == -INFINITY ? 0.0f : se * __expf(mx - mn)) + (m2 == -INFINITY ? 0.0f : s2 * __expf(m2 - mn));
+        const float2 m2 = halves32(mx), s2 = halves32(se);
+        mx = m2.x;
+        se = s2.x;
+        merge_ms(mx, se, m2.y, s2.y);
         if (lg == 0 && row_ok) {
           const int parts = ((g.N + BN - 1) / BN) * 2;
-          reinterpret_cast<float2*>(g.ce_stats)[(size_t)mrow * parts + (n0 / BN) * 2 + wn] = make_float2(mn, se);
+          reinterpret_cast<float2*>(g.ce_stats)[(size_t)mrow * parts + (n0 / BN) * 2 + wn] = make_float2(mx, se);
         }
       } else {
         const float lse = row_ok ? g.ce_lse[mrow] : 0.0f;

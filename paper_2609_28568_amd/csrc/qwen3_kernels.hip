@@ -166,14 +166,6 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
 // every shuffle stays inside a group.
 constexpr int QK_HD = 128;
 
-DEV float group16_sum(float v) {
-  v += __shfl_xor(v, 8);
-  v += __shfl_xor(v, 4);
-  v += __shfl_xor(v, 2);
-  v += __shfl_xor(v, 1);
-  return v;
-}
-
 DEV void unpack8(const uint4& u, float* v) {
   v[0] = lo_f(u.x); v[1] = hi_f(u.x); v[2] = lo_f(u.y); v[3] = hi_f(u.y);
   v[4] = lo_f(u.z); v[5] = hi_f(u.z); v[6] = lo_f(u.w); v[7] = hi_f(u.w);
@@ -230,7 +222,7 @@ __global__ __launch_bounds__(256) void qknorm_rope_fwd_kernel(const bf16_t* __re
   const float sgn = sub < 8 ? -1.0f : 1.0f;
   float y[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = x[e] * c[e] + sgn * __shfl_xor(x[e], 8) * sn[e];
+  for (int e = 0; e < 8; ++e) y[e] = x[e] * c[e] + sgn * xor8(x[e]) * sn[e];
   *reinterpret_cast<uint4*>(packed + off) = pack8(y);
   if (sub == 0) {
     if (isq) rq[(size_t)tok * H + hs] = rstd;
@@ -268,7 +260,7 @@ __global__ __launch_bounds__(256) void qknorm_rope_bwd_kernel(const bf16_t* __re
   const float sgn = sub < 8 ? 1.0f : -1.0f;
   float n[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) n[e] = d[e] * c[e] + sgn * __shfl_xor(d[e], 8) * sn[e];
+  for (int e = 0; e < 8; ++e) n[e] = d[e] * c[e] + sgn * xor8(d[e]) * sn[e];
   // RMSNorm backward over the head (gain frozen)
   const bool isq = hs < H;
   float x[8], w[8];
