@@ -238,6 +238,9 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
         g.ldc = gr.N;
         g.bsum = gr.bsum ? gr.bsum + (size_t)pidx * gr.M : nullptr;
         g.bsum_ld = gr.count * gr.M;
+        g.b_bound[0] = gr.b_bound[0];
+        g.b_bound[1] = gr.b_bound[1];
+        g.b_step = gr.b_step;
         if (sp > 1) {
           g.k_chunk = gr.k_chunk;
           g.split_stride = gr.split_stride;
@@ -1035,6 +1038,9 @@ hipError_t launch_gemm_grouped(const GemmGroupedArgs& gg, hipStream_t s) {
         return hipErrorInvalidValue;
     }
     const int bm = g192 ? 192 : 128;
+    if (gr.b_step != 0 && (gr.b_step < 0 || gr.b_bound[0] < 0 || gr.b_bound[1] < 0 || gr.b_bound[0] % bm ||
+                           gr.b_bound[1] % bm))
+      return hipErrorInvalidValue;
     last = (long)((gr.M + bm - 1) / bm) * ((gr.N + bm - 1) / bm) * gr.count * (gr.splits > 1 ? gr.splits : 1);
     tiles += last;
     if ((size_t)(gg.K + 256) * gr.lda * 2 >= (1ull << 32) || (size_t)(gg.K + 256) * gr.ldb * 2 >= (1ull << 32))

@@ -104,7 +104,7 @@ struct GemmArgs {
 // one hold nfull tiles and the last one the rest (both multiples of 8), and
 // each of the 8 XCDs takes an equal share of both (the last group's tiles
 // filling the final round).
-constexpr int GEMM_GROUPS = 5;
+constexpr int GEMM_GROUPS = 8;
 struct GemmGroup {
   const bf16_t* A;
   const bf16_t* B;
@@ -115,6 +115,7 @@ struct GemmGroup {
   int count;
   int splits, k_chunk;   // contraction split (splits <= 1: none)
   long split_stride;
+  int b_bound[2], b_step;   // as in GemmArgs (128 x 128 tiles only)
 };
 struct GemmGroupedArgs {
   GemmGroup grp[GEMM_GROUPS];
@@ -278,11 +279,12 @@ hipError_t launch_rmsnorm_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, float
 // stored to xsum; with w == nullptr xsum only
 hipError_t launch_slices_rmsnorm_fwd(const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w, bf16_t* y,
                                      float* rstd, int rows, int C, float eps, hipStream_t s);
-// dres (=|+=) the RMSNorm input gradient (the gain is frozen) over all rows of
-// x; dy (a bf16 array, or with slices.n > 0 fp32 slices) and rstd hold only the rows of positions t >= mask_from, compacted as
+// dres_out = (accumulate ? dres_in : 0) + the RMSNorm input gradient (the gain
+// is frozen) over all rows of x (dres_in may be dres_out); dy (a bf16 array, or with slices.n > 0 fp32 slices) and rstd hold only the rows of positions t >= mask_from, compacted as
 // launch_rmsnorm_fwd writes them; the other rows get a zero gradient
-hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* rstd, const bf16_t* w, bf16_t* dres,
-                              int accumulate, int rows, int C, int T, int mask_from, hipStream_t s);
+hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* rstd, const bf16_t* w,
+                              const bf16_t* dres_in, bf16_t* dres_out, int accumulate, int rows, int C, int T,
+                              int mask_from, hipStream_t s);
 // raw q|k|v [BT][(H + 2 Hkv) hd] -> packed q|k|v in the same layout for the
 // grouped-query attention kernels: query and key heads RMS-normalised and
 // rotated, value heads copied; rstd of every q and k head saved

@@ -9,7 +9,8 @@
 // one pass over x or dy each (lora.hip, n*RP columns with the rank padding
 // written as zeros); the up products ride on the base projections' GEMMs as
 // a second contraction segment, y += u B^T and dx += du A; dA = du^T x and
-// dB = dy^T u contract over the tokens, split and reduced.
+// dB = dy^T u contract over the tokens, all layers' in one grouped launch at
+// the end of the backward pass, from the layers' kept gradients.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -173,7 +174,26 @@ ActLayout act_layout(const Dims& d) {
   return a;
 }
 
-constexpr int DW_SPLITS = 16;   // token-contraction split of the adapter gradients
+// The grouped launch of the adapter gradients: every group's dB [out, RP] and
+// dA [n RP, in] over all layers, in 128 x 128 tiles. Deep models fill the chip
+// with whole contractions (28 layers of the 0.6B shape with q|k|v and o
+// adapted: 2,016 tiles); when the tiles number less than one round of 512, each
+// product splits its tokens (at least 512 to a split) to fill that round, and
+// the slices are reduced afterwards. As two products and a reduction per layer
+// and group the full-size step spent 112 x 16.6 + 56 x 5.4 us on them.
+struct AdapterPlan { int splits, chunk; };
+AdapterPlan adapter_plan(const Dims& d) {
+  long tiles = 0;
+  for (int g = 0; g < G_N; ++g) {
+    if (!(d.groups & (1 << g))) continue;
+    const GroupGeom gg = group_geom(d, g);
+    tiles += (long)d.L * ((gg.out_total + 127) / 128 + (long)((gg.n * RP + 127) / 128) * ((gg.in + 127) / 128));
+  }
+  const long want = std::min({512 / tiles, d.BT / 512, 16L});
+  AdapterPlan p{1, 0};
+  p.splits = gemm_split_plan((int)d.BT, (int)std::max(want, 1L), &p.chunk);
+  return p;
+}
 // vocabulary-contraction split of the LM head's input gradient: at least 4 (its
 // output tiles are few at every batch size), more for few rows
 int head_splits(const Dims& d, int* chunk) {
@@ -184,23 +204,25 @@ constexpr int BT_ROWS = 32;     // rows of the transposed B copies: the largest 
 
 struct WsLayout {
   size_t xsl;   // fp32 slices of the split products into the residual stream
-  size_t dres, dh, datt, dpacked, draw, dgu, dm, du, dsum, cosT, sinT, part, part2, sumsq, normcoef, total;
+  size_t dh, datt, dpacked, dm, dsum, cosT, sinT, part, sumsq, normcoef, total;
+  // kept for the adapter gradients, one buffer per layer where a group that
+  // reads it is adapted (stride 0: one buffer for all layers): residual-stream
+  // gradients (slot 2l+2 enters layer l, 2l+1 is after its MLP, 2l leaves it),
+  // gradients of the raw q|k|v and of gate|up, and the adapters' du
+  size_t dres, draw, dgu, du[G_N];
+  size_t s_dres, s_draw, s_dgu, s_du[G_N];
   size_t bt[G_N];   // per adapted group: B transposed, [L][BT_ROWS][out_total] bf16
 };
 
 WsLayout ws_layout(const Dims& d) {
   WsLayout w{};
   const size_t BT = d.BT;
-  // split partial slices: adapter B gradients [split][out][RP] (or the LM
-  // head's input gradient [split][BTL][C]) and adapter A gradients
-  // [split][n RP][in]
-  size_t part = (size_t)d.BTL * d.C * head_splits(d, nullptr), part2 = 0;
-  for (int g = 0; g < G_N; ++g) {
-    if (!(d.groups & (1 << g))) continue;
-    const GroupGeom gg = group_geom(d, g);
-    part = std::max(part, (size_t)DW_SPLITS * gg.out_total * RP);
-    part2 = std::max(part2, (size_t)DW_SPLITS * gg.n * RP * gg.in);
-  }
+  // split partial slices: the LM head's input gradient [split][BTL][C], or the
+  // adapter gradients'
+  size_t part = (size_t)d.BTL * d.C * head_splits(d, nullptr), nl = 0;
+  lora_layout(d, &nl);
+  const AdapterPlan ap = adapter_plan(d);
+  if (ap.splits > 1) part = std::max(part, ap.splits * nl);
   // the o and down projections (with their adapters as a second segment), and
   // the input gradients of q|k|v and gate|up
   size_t xs = 0;
@@ -213,19 +235,25 @@ WsLayout ws_layout(const Dims& d) {
   }
   size_t o = 0;
   w.xsl = o; o += align_up(xs * 4);
-  w.dres = o; o += align_up(BT * d.C * 2);
+  const bool keep_res = d.groups & ((1 << G_O) | (1 << G_DN));
+  w.s_dres = keep_res ? align_up(BT * d.C * 2) : 0;
+  w.s_draw = (d.groups & (1 << G_QKV)) ? align_up(BT * d.QKVD * 2) : 0;
+  w.s_dgu = (d.groups & (1 << G_GU)) ? align_up(BT * 2 * d.F * 2) : 0;
+  w.dres = o; o += keep_res ? (2 * (size_t)d.L + 1) * w.s_dres : align_up(BT * d.C * 2);
+  w.draw = o; o += w.s_draw ? d.L * w.s_draw : align_up(BT * d.QKVD * 2);
+  w.dgu = o; o += w.s_dgu ? d.L * w.s_dgu : align_up(BT * 2 * d.F * 2);
+  for (int g = 0; g < G_N; ++g) {
+    w.s_du[g] = (d.groups & (1 << g)) ? align_up(BT * group_geom(d, g).n * RP * 2) : 0;
+    w.du[g] = o; o += d.L * w.s_du[g];
+  }
   w.dh = o; o += align_up(BT * d.C * 2);
   w.datt = o; o += align_up(BT * d.QD * 2);
   w.dpacked = o; o += align_up(BT * d.QKVD * 2);
-  w.draw = o; o += align_up(BT * d.QKVD * 2);
-  w.dgu = o; o += align_up(BT * 2 * d.F * 2);
   w.dm = o; o += align_up(BT * d.F * 2);
-  w.du = o; o += align_up(BT * 3 * RP * 2);
   w.dsum = o; o += align_up((size_t)d.B * d.H * d.T * 4);
   w.cosT = o; o += align_up((size_t)d.T * (d.hd / 2) * 4);
   w.sinT = o; o += align_up((size_t)d.T * (d.hd / 2) * 4);
   w.part = o; o += align_up(part * 4);
-  w.part2 = o; o += align_up(part2 * 4);
   w.sumsq = o; o += align_up((size_t)sumsq_parts() * 4);
   w.normcoef = o; o += ALIGN;
   for (int g = 0; g < G_N; ++g) {
@@ -395,15 +423,13 @@ hipError_t proj_fwd(qwen3_model* m, int g, int l, const bf16_t* x, const bf16_t*
   return run_gemm(m, QWEN3_K_GEMM_FWD, fl, a, 0, 0, EPI_BF16);
 }
 
-// Backward of proj_fwd given the output gradient dy (row stride ldy) and the
-// input x: the adapter gradients (when adapted) and, unless dx is null,
-// dx = dy W (+ du A with du = s dy_j B_j per projection, as a second
-// contraction segment of the same GEMM). The adapter gradients contract over
-// the tokens, split DW_SPLITS ways into the partial areas and summed by one
-// launch: dB_j = dy_j^T u_j, dA = du^T x. With sl, dx may be left as slices as
+// Backward of proj_fwd given the output gradient dy (row stride ldy): the
+// adapters' du = s dy_j B_j per projection (when adapted, kept for
+// adapter_grads) and, unless dx is null, dx = dy W (+ du A as a second
+// contraction segment of the same GEMM). With sl, dx may be left as slices as
 // in proj_fwd.
-hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, const bf16_t* x, const bf16_t* W,
-                    bf16_t* dx, Slices* sl = nullptr) {
+hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, const bf16_t* W, bf16_t* dx,
+                    Slices* sl = nullptr) {
   const Dims& d = m->d;
   const GroupGeom gg = group_geom(d, g);
   const int BT = (int)d.BT, nu = gg.n * RP;
@@ -412,62 +438,22 @@ hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, con
   a.C = dx; a.ldc = gg.in;
   double fl = mnk2(d.BT, gg.in, gg.out_total);
   if (m->has(g)) {
-    const int AD = QWEN3_K_GEMM_ADAPTER;
-    const LoraTensor* ta = m->lora_t(g, false);
-    const LoraTensor* tb = m->lora_t(g, true);
-    const size_t oa = ta->off + (size_t)l * gg.n * RP * gg.in, ob = tb->off + (size_t)l * gg.out_total * RP;
-    const bf16_t* wa = static_cast<const bf16_t*>(m->buf.lora_bf16) + oa;
-    const bf16_t* u = m->ab(m->act.u[g] + l * m->act.s_u[g]);
-    bf16_t* du = m->wb(m->ws.du);
-    float* pb = m->wf(m->ws.part);
-    float* pa = m->wf(m->ws.part2);
-    hipError_t e;
+    const bf16_t* wa = static_cast<const bf16_t*>(m->buf.lora_bf16) + m->lora_t(g, false)->off + (size_t)l * nu * gg.in;
+    bf16_t* du = m->wb(m->ws.du[g] + l * m->ws.s_du[g]);
     // du_j = s dy_j B_j ([BT, RP] blocks of du), all projections in one
     // pass over dy: segment j contracts dy's columns of projection j with the
     // transposed copy of B_j (rows = rank, contraction index contiguous)
-    {
-      const int ntp = (d.r + 15) / 16;
-      const bf16_t* bt = m->wb(m->ws.bt[g]) + (size_t)l * BT_ROWS * gg.out_total;
-      LoraRowArgs ra{};
-      ra.x = dy; ra.ldx = ldy; ra.M = BT; ra.nseg = gg.n; ra.nts = ntp; ra.ntp = ntp; ra.tstride = RP;
-      ra.ldw = gg.out_total; ra.s = d.s; ra.y = du; ra.ldy = nu;
-      double dfl = 0.0;
-      for (int j = 0, col = 0; j < gg.n; col += gg.out[j], ++j) {
-        ra.k0[j] = col; ra.klen[j] = gg.out[j]; ra.col[j] = j * RP; ra.w[j] = bt + col;
-        dfl += mnk2(d.BT, d.r, gg.out[j]);
-      }
-      e = m->run(AD, dfl, 0.0, [&] { return launch_lora_rows(ra, m->stream); });
-      if (e != hipSuccess) return e;
+    const int ntp = (d.r + 15) / 16;
+    const bf16_t* bt = m->wb(m->ws.bt[g]) + (size_t)l * BT_ROWS * gg.out_total;
+    LoraRowArgs ra{};
+    ra.x = dy; ra.ldx = ldy; ra.M = BT; ra.nseg = gg.n; ra.nts = ntp; ra.ntp = ntp; ra.tstride = RP;
+    ra.ldw = gg.out_total; ra.s = d.s; ra.y = du; ra.ldy = nu;
+    double dfl = 0.0;
+    for (int j = 0, col = 0; j < gg.n; col += gg.out[j], ++j) {
+      ra.k0[j] = col; ra.klen[j] = gg.out[j]; ra.col[j] = j * RP; ra.w[j] = bt + col;
+      dfl += mnk2(d.BT, d.r, gg.out[j]);
     }
-    int kc = 0;
-    const int splits = gemm_split_plan(BT, DW_SPLITS, &kc);
-    {
-      // dB_j = dy_j^T u_j for every projection in one product over all
-      // out_total rows: projection j's rows read u's j-th block of RP columns
-      GemmArgs r{};
-      r.A = dy; r.lda = ldy; r.B = u; r.ldb = nu; r.M = gg.out_total; r.N = RP; r.K = BT;
-      r.C = pb; r.ldc = RP; r.splits = splits; r.k_chunk = kc; r.split_stride = (long)gg.out_total * RP;
-      r.b_step = RP;
-      int bound = 0;
-      for (int j = 0; j + 1 < gg.n; ++j) {
-        bound += gg.out[j];
-        r.b_bound[j] = bound;
-      }
-      e = run_gemm(m, AD, mnk2(gg.out_total, d.r, d.BT), r, 1, 1, EPI_F32);
-      if (e != hipSuccess) return e;
-    }
-    // dA = du^T x
-    GemmArgs r{};
-    r.A = du; r.lda = nu; r.B = x; r.ldb = gg.in; r.M = nu; r.N = gg.in; r.K = BT;
-    r.C = pa; r.ldc = gg.in; r.splits = splits; r.k_chunk = kc; r.split_stride = (long)nu * gg.in;
-    e = run_gemm(m, AD, mnk2(gg.n * d.r, gg.in, d.BT), r, 1, 1, EPI_F32);
-    if (e != hipSuccess) return e;
-    const long nb = (long)gg.out_total * RP, na = (long)nu * gg.in;
-    ReduceSegs rs{};
-    rs.add(pb, splits, nb, static_cast<float*>(m->buf.lora_grads) + ob, nb);
-    rs.add(pa, splits, na, static_cast<float*>(m->buf.lora_grads) + oa, na);
-    e = m->run(QWEN3_K_OTHER, 0.0, 4.0 * (double)(nb + na) * (splits + 1),
-               [&] { return launch_reduce_segs(rs, 0, m->stream); });
+    hipError_t e = m->run(QWEN3_K_GEMM_ADAPTER, dfl, 0.0, [&] { return launch_lora_rows(ra, m->stream); });
     if (e != hipSuccess || !dx) return e;
     a.A2 = du; a.lda2 = nu; a.B2 = wa; a.ldb2 = gg.in; a.K2 = nu;
     fl += mnk2(d.BT, gg.in, gg.n * d.r);
@@ -475,6 +461,55 @@ hipError_t proj_bwd(qwen3_model* m, int g, int l, const bf16_t* dy, int ldy, con
   if (!dx) return hipSuccess;
   if (sl && sliced(m, a, 1, sl)) return run_gemm(m, QWEN3_K_GEMM_DX, fl, a, 0, 1, EPI_F32);
   return run_gemm(m, QWEN3_K_GEMM_DX, fl, a, 0, 1, EPI_BF16);
+}
+
+// Every adapter gradient of the backward pass in one grouped launch (see
+// adapter_plan): dB_j = dy_j^T u_j for every projection of a group in one
+// product over all its out_total rows (projection j's rows read u's j-th block
+// of RP columns), dA = du^T x. Each group's operands sit one layer apart.
+hipError_t adapter_grads(qwen3_model* m) {
+  const Dims& d = m->d;
+  const ActLayout& act = m->act;
+  const WsLayout& ws = m->ws;
+  float* grads = static_cast<float*>(m->buf.lora_grads);
+  const AdapterPlan plan = adapter_plan(d);
+  GemmGroupedArgs gr{};
+  gr.K = (int)d.BT;
+  ReduceSegs rs{};
+  float* part = m->wf(ws.part);
+  double fl = 0.0;
+  auto product = [&](const bf16_t* A, size_t sa, int M, int lda, const bf16_t* B, size_t sb, int N, int ldb, float* C) {
+    GemmGroup& p = gr.grp[gr.ngroups++];
+    p.A = A; p.a_stride = (long)(sa / 2); p.lda = lda;
+    p.B = B; p.b_stride = (long)(sb / 2); p.ldb = ldb;
+    p.M = M; p.N = N; p.C = C; p.c_stride = (long)M * N; p.count = d.L;
+    if (plan.splits > 1) {
+      const long n = (long)d.L * M * N;
+      rs.add(part, plan.splits, n, C, n);
+      p.C = part; p.splits = plan.splits; p.k_chunk = plan.chunk; p.split_stride = n;
+      part += (size_t)plan.splits * n;
+    }
+    return &p;
+  };
+  for (int g = 0; g < G_N; ++g) {
+    if (!m->has(g)) continue;
+    const GroupGeom gg = group_geom(d, g);
+    const int nu = gg.n * RP;
+    // the group's output gradients dy and inputs x, layer 0's and the strides
+    const size_t dy0[G_N] = {ws.draw, ws.dres + ws.s_dres, ws.dgu, ws.dres + 2 * ws.s_dres};
+    const size_t sdy[G_N] = {ws.s_draw, 2 * ws.s_dres, ws.s_dgu, 2 * ws.s_dres};
+    const size_t x0[G_N] = {act.h, act.att, act.h2, act.m}, sx[G_N] = {act.s_act, act.s_att, act.s_act, act.s_m};
+    GemmGroup* b = product(m->wb(dy0[g]), sdy[g], gg.out_total, gg.out_total, m->ab(act.u[g]), act.s_u[g], RP, nu,
+                           grads + m->lora_t(g, true)->off);
+    b->b_step = RP;
+    for (int j = 0, bound = 0; j + 1 < gg.n; ++j) b->b_bound[j] = bound += gg.out[j];
+    product(m->wb(ws.du[g]), ws.s_du[g], nu, nu, m->ab(x0[g]), sx[g], gg.in, gg.in, grads + m->lora_t(g, false)->off);
+    fl += d.L * (mnk2(gg.out_total, d.r, d.BT) + mnk2(gg.n * d.r, gg.in, d.BT));
+  }
+  hipError_t e = m->run(QWEN3_K_GEMM_ADAPTER, fl, 0.0, [&] { return launch_gemm_grouped(gr, m->stream); });
+  if (e != hipSuccess || plan.splits <= 1) return e;
+  return m->run(QWEN3_K_OTHER, 0.0, 4.0 * m->n_lora * (plan.splits + 1),
+                [&] { return launch_reduce_segs(rs, 0, m->stream); });
 }
 
 AttnArgs attn_args(qwen3_model* m, int l) {
@@ -700,7 +735,8 @@ gpt2_status qwen3_backward(qwen3_model* m) {
   const int BT = (int)d.BT, BTL = (int)d.BTL;
   const int DX = QWEN3_K_GEMM_DX, NORM = QWEN3_K_NORM;
   const double rowb = 2.0 * d.BT * d.C;
-  bf16_t* dres = m->wb(m->ws.dres);
+  // residual-stream gradient slots (one and the same when none is kept)
+  auto dres = [&](int slot) { return m->wb(m->ws.dres + (size_t)slot * m->ws.s_dres); };
   bf16_t* dh = m->wb(m->ws.dh);
   // transposed copies of every adapted group's B (all layers), read by the
   // du products
@@ -721,46 +757,44 @@ gpt2_status qwen3_backward(qwen3_model* m) {
     TRY(gemm(m, DX, mnk2(BTL, d.C, d.V), BTL, d.C, d.V, m->ab(m->act.logits), d.V, 0, m->base(B_EMBED), d.C, 1,
              EPI_F32, part, d.C, nullptr, splits, kc, (long)d.BTL * d.C));
     TRY(m->run(NORM, 0.0, 2.0 * rowb + (2.0 + 4.0 * splits) * d.BTL * d.C + 4.0 * d.BTL, [&] {
-      return launch_rmsnorm_bwd(nullptr, {part, splits}, m->res(d.L), m->af(m->act.rf), m->base(B_FINAL_NORM), dres, 0,
-                                BT, d.C, d.T, d.mask_from, m->stream);
+      return launch_rmsnorm_bwd(nullptr, {part, splits}, m->res(d.L), m->af(m->act.rf), m->base(B_FINAL_NORM),
+                                dres(2 * d.L), dres(2 * d.L), 0, BT, d.C, d.T, d.mask_from, m->stream);
     }));
   }
   for (int l = d.L - 1; l >= 0; --l) {
-    const bf16_t* h = m->ab(m->act.h + l * m->act.s_act);
     const float* r1 = m->af(m->act.r1 + l * m->act.s_row);
     const bf16_t* raw = m->ab(m->act.raw + l * m->act.s_raw);
     const bf16_t* xmid = m->ab(m->act.xmid + l * m->act.s_act);
-    const bf16_t* h2 = m->ab(m->act.h2 + l * m->act.s_act);
     const float* r2 = m->af(m->act.r2 + l * m->act.s_row);
     const bf16_t* gu = m->ab(m->act.gu + l * m->act.s_gu);
-    const bf16_t* mm = m->ab(m->act.m + l * m->act.s_m);
     bf16_t* dm = m->wb(m->ws.dm);
-    bf16_t* dgu = m->wb(m->ws.dgu);
+    bf16_t* dgu = m->wb(m->ws.dgu + l * m->ws.s_dgu);
+    bf16_t *res_out = dres(2 * l + 2), *res_mid = dres(2 * l + 1), *res_in = dres(2 * l);
     // down projection: res(l+1) = xmid + m down^T (+ adapter)
     if (m->swiglu_fused && !m->has(G_DN)) {
       // no adapter: only its input gradient, with the SwiGLU backward in the
       // epilogue (dgu from the gradient of m and the saved pre-activation)
       GemmArgs a{};
-      a.A = dres; a.lda = d.C; a.B = m->base(B_DOWN) + (size_t)l * d.C * d.F; a.ldb = d.F;
+      a.A = res_out; a.lda = d.C; a.B = m->base(B_DOWN) + (size_t)l * d.C * d.F; a.ldb = d.F;
       a.M = BT; a.N = d.F; a.K = d.C; a.C = dgu; a.ldc = 2 * d.F; a.aux = gu;
       TRY(run_gemm(m, DX, mnk2(d.BT, d.F, d.C), a, 0, 1, EPI_SWIGLU_BWD));
     } else {
-      TRY(proj_bwd(m, G_DN, l, dres, d.C, mm, m->base(B_DOWN) + (size_t)l * d.C * d.F, dm));
+      TRY(proj_bwd(m, G_DN, l, res_out, d.C, m->base(B_DOWN) + (size_t)l * d.C * d.F, dm));
       TRY(m->run(QWEN3_K_OTHER, 0.0, 10.0 * d.BT * d.F,
                  [&] { return launch_swiglu_bwd(dm, gu, dgu, d.BT, d.F, m->stream); }));
     }
     Slices sl{nullptr, 0};
-    TRY(proj_bwd(m, G_GU, l, dgu, 2 * d.F, h2, m->base(B_GU) + (size_t)l * 2 * d.F * d.C, dh, &sl));
+    TRY(proj_bwd(m, G_GU, l, dgu, 2 * d.F, m->base(B_GU) + (size_t)l * 2 * d.F * d.C, dh, &sl));
     TRY(m->run(NORM, 0.0, 4.0 * rowb + 4.0 * d.BT, [&] {
-      return launch_rmsnorm_bwd(dh, sl, xmid, r2, m->base(B_POST_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
-                                m->stream);
+      return launch_rmsnorm_bwd(dh, sl, xmid, r2, m->base(B_POST_NORM) + (size_t)l * d.C, res_out,
+                                res_mid, 1, BT, d.C, 1, 0, m->stream);
     }));
     // attention output projection: xmid = res(l) + att o^T (+ adapter)
     AttnArgs aa = attn_args(m, l);
     bf16_t* datt = m->wb(m->ws.datt);
-    TRY(proj_bwd(m, G_O, l, dres, d.C, aa.out, m->base(B_O) + (size_t)l * d.C * d.QD, datt));
+    TRY(proj_bwd(m, G_O, l, res_mid, d.C, m->base(B_O) + (size_t)l * d.C * d.QD, datt));
     TRY(m->run(QWEN3_K_ATTN_BWD, 2.0 * attn_fwd_flops(d), 0.0, [&] { return launch_attention_bwd(aa, m->stream); }));
-    bf16_t* draw = m->wb(m->ws.draw);
+    bf16_t* draw = m->wb(m->ws.draw + l * m->ws.s_draw);
     TRY(m->run(NORM, 0.0, 6.0 * d.BT * d.QKVD + 4.0 * d.BT * (d.H + d.Hkv), [&] {
       return launch_qknorm_rope_bwd(m->wb(m->ws.dpacked), raw, m->base(B_QNORM) + (size_t)l * d.hd,
                                     m->base(B_KNORM) + (size_t)l * d.hd, m->wf(m->ws.cosT), m->wf(m->ws.sinT),
@@ -770,14 +804,15 @@ gpt2_status qwen3_backward(qwen3_model* m) {
     // the first layer's input gradient would only reach the frozen token
     // table: its q|k|v input gradient and the norm behind it are skipped
     const bool need_dx = l > 0;
-    TRY(proj_bwd(m, G_QKV, l, draw, d.QKVD, h, m->base(B_QKV) + (size_t)l * d.QKVD * d.C, need_dx ? dh : nullptr,
+    TRY(proj_bwd(m, G_QKV, l, draw, d.QKVD, m->base(B_QKV) + (size_t)l * d.QKVD * d.C, need_dx ? dh : nullptr,
                  &sl));
     if (need_dx)
       TRY(m->run(NORM, 0.0, 4.0 * rowb + 4.0 * d.BT, [&] {
-        return launch_rmsnorm_bwd(dh, sl, m->res(l), r1, m->base(B_IN_NORM) + (size_t)l * d.C, dres, 1, BT, d.C, 1, 0,
-                                  m->stream);
+        return launch_rmsnorm_bwd(dh, sl, m->res(l), r1, m->base(B_IN_NORM) + (size_t)l * d.C, res_mid,
+                                  res_in, 1, BT, d.C, 1, 0, m->stream);
       }));
   }
+  TRY(adapter_grads(m));
   m->have_grads = true;
   return GPT2_OK;
 }

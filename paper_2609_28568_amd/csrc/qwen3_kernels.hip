@@ -89,24 +89,26 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restri
   if (lane == 0) rstd_out[row] = rstd;
 }
 
-// dres (=|+=) rstd (g - xhat mean(g xhat)), g = dy w, xhat = x rstd (gain frozen).
-// dy and rstd hold compact rows (loss_index); rows p with p % T < mask_from
-// have no upstream gradient: dres is left as is (accumulate) or zeroed.
+// dres_out = (accumulate ? dres_in : 0) + rstd (g - xhat mean(g xhat)), g = dy w,
+// xhat = x rstd (gain frozen). dy and rstd hold compact rows (loss_index); rows
+// p with p % T < mask_from have no upstream gradient. dres_in may be dres_out:
+// each row is read before it is written, by the same lanes.
 // With SL dy comes as fp32 slices of dy_rows rows each; their sum is rounded to
 // bf16, as the product stored whole is.
 template <int MAXCH, bool SL>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restrict__ dy, Slices sl, int dy_rows,
                                                           const bf16_t* __restrict__ x,
                                                           const float* __restrict__ rstd_in,
-                                                          const bf16_t* __restrict__ w, bf16_t* __restrict__ dres,
-                                                          int accumulate, int rows, int C, int T, int mask_from) {
+                                                          const bf16_t* __restrict__ w, const bf16_t* dres_in,
+                                                          bf16_t* dres_out, int accumulate, int rows, int C, int T, int mask_from) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  bf16_t* rr = dres + (size_t)row * C;
+  bf16_t* rr = dres_out + (size_t)row * C;
+  const bf16_t* ri = dres_in + (size_t)row * C;
   if (row % T < mask_from) {
-    if (!accumulate)
-      for (int c = 4 * lane; c < C; c += 256) *reinterpret_cast<uint2*>(rr + c) = make_uint2(0, 0);
+    for (int c = 4 * lane; c < C; c += 256)
+      *reinterpret_cast<uint2*>(rr + c) = accumulate ? *reinterpret_cast<const uint2*>(ri + c) : make_uint2(0, 0);
     return;
   }
   const int ci = loss_index(row, T, mask_from);
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
       du[i] = make_uint2(pack2(t.x, t.y), pack2(t.z, t.w));
     } else du[i] = *reinterpret_cast<const uint2*>(dr + c);
     wu[i] = *reinterpret_cast<const uint2*>(w + c);
-    ru[i] = accumulate ? *reinterpret_cast<const uint2*>(rr + c) : make_uint2(0, 0);
+    ru[i] = accumulate ? *reinterpret_cast<const uint2*>(ri + c) : make_uint2(0, 0);
   }
   const float rstd = rstd_in[ci];
   float xh[MAXCH][4], g[MAXCH][4];
@@ -376,24 +378,26 @@ hipError_t launch_slices_rmsnorm_fwd(const Slices& sl, const bf16_t* res, bf16_t
 
 template <int MAXCH>
 static void rms_bwd_t(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* rstd, const bf16_t* w,
-                      bf16_t* dres, int accumulate, int rows, int C, int T, int mask_from, hipStream_t s) {
+                      const bf16_t* dres_in, bf16_t* dres_out, int accumulate, int rows, int C, int T, int mask_from,
+                      hipStream_t s) {
   const dim3 g((rows + 3) / 4), b(256);
   const int dy_rows = rows / T * (T - mask_from);
   if (sl.n > 0)
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, true>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres, accumulate,
-                       rows, C, T, mask_from);
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, true>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres_in, dres_out,
+                       accumulate, rows, C, T, mask_from);
   else
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, false>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres, accumulate,
-                       rows, C, T, mask_from);
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXCH, false>), g, b, 0, s, dy, sl, dy_rows, x, rstd, w, dres_in, dres_out,
+                       accumulate, rows, C, T, mask_from);
 }
 
 hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* rstd, const bf16_t* w,
-                              bf16_t* dres, int accumulate, int rows, int C, int T, int mask_from, hipStream_t s) {
+                              const bf16_t* dres_in, bf16_t* dres_out, int accumulate, int rows, int C, int T,
+                              int mask_from, hipStream_t s) {
   if (C % 4 || T < 1 || mask_from < 0 || mask_from >= T || rows % T) return hipErrorInvalidValue;
-  if (C <= 256) rms_bwd_t<1>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
-  else if (C <= 512) rms_bwd_t<2>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
-  else if (C <= 1024) rms_bwd_t<4>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
-  else if (C <= 2048) rms_bwd_t<8>(dy, sl, x, rstd, w, dres, accumulate, rows, C, T, mask_from, s);
+  if (C <= 256) rms_bwd_t<1>(dy, sl, x, rstd, w, dres_in, dres_out, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 512) rms_bwd_t<2>(dy, sl, x, rstd, w, dres_in, dres_out, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 1024) rms_bwd_t<4>(dy, sl, x, rstd, w, dres_in, dres_out, accumulate, rows, C, T, mask_from, s);
+  else if (C <= 2048) rms_bwd_t<8>(dy, sl, x, rstd, w, dres_in, dres_out, accumulate, rows, C, T, mask_from, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
