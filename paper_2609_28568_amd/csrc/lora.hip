@@ -138,23 +138,24 @@ __global__ __launch_bounds__(256, 2) void lora_rows_kernel(LoraRowArgs a) {
     const int rr = idx / nq, c = (idx - rr * nq) * 4;
     const long m = m0 + rr;
     if (m >= a.M) continue;
-    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int tile = -1, cc = 0;   // the tile that covers the columns, and where
 #pragma unroll
     for (int q = 0; q < NSEG; ++q)
 #pragma unroll
       for (int t = 0; t < NTS; ++t) {
         const int c0 = a.col[q] + tile_row(a, t);
         if (c >= c0 && c < c0 + 16) {
-          const int cc = c - c0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int j = q * NTS + t;
-            const float sum = ((red[0][j][rr][cc + e] + red[1][j][rr][cc + e]) + red[2][j][rr][cc + e]) +
-                              red[3][j][rr][cc + e];
-            v[e] = sum * a.s;
-          }
+          tile = q * NTS + t;
+          cc = c - c0;
         }
       }
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (tile >= 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = (((red[0][tile][rr][cc + e] + red[1][tile][rr][cc + e]) + red[2][tile][rr][cc + e]) +
+                red[3][tile][rr][cc + e]) * a.s;
+    }
     *reinterpret_cast<uint2*>(a.y + m * a.ldy + c) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
   }
 }
