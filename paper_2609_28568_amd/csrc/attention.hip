@@ -766,21 +766,473 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv8_kernel(AttnArgs a) {
     }
 }
 
+// ------------------------------------------------------------ short grids
+//
+// With few heads and rows the kernels above leave most CUs idle, and their time
+// is one workgroup's walk: a tile every 0.9 us or so, however few there are.
+// The kernels below give a workgroup 32 rows (queries, or keys for dK/dV) and
+// deal the tiles it walks to its four waves, tile w, w + 4, ... to wave w, each
+// with tiles of its own in LDS and no barrier until the end, where the waves'
+// partial results are added up through LDS: four times the workgroups, a
+// quarter of the walk. They pay with a fourth of the operand reuse, their LDS
+// allows one workgroup per CU, and the partial results cost a round trip
+// through LDS. Forward and dQ take them for walks of three tiles or more while
+// every workgroup has a CU to itself; dK/dV, whose partial results replace more
+// work per tile, for two tiles or more and up to two workgroups per CU.
+// Measured against the kernels above (us): forward, 203 tokens, 12 heads of 64
+// (84 workgroups) 6.9 -> 5.0, but 6.9 -> 8.1 at 4 x 256 tokens (384) and 6.8 ->
+// 7.0 for two tiles (24); dQ 10.2 -> 11.3 at 384; dK/dV 12.7 -> 11.6 at 384,
+// 16.6 -> 14.4 at 3 x 333 tokens (396), 13.1 -> 10.8 for 2 x 96 tokens of head
+// size 128 (12).
+
+constexpr int SB = 32;   // rows owned by one workgroup
+
+// Loads the 64 rows of a tile for one wave. off: byte offset in the buffer of
+// the tile's first row of the head's slice.
+template <int HD>
+DEV void issue_rows_w(v4i32 rs, uint32_t off, int ld, lds_char_t* dst, int lane) {
+  constexpr int U = HD / 8, UNITS = TILE * U, INSTR = UNITS / 64;
+  static_assert(UNITS % 64 == 0, "whole instructions");
+#pragma unroll
+  for (int ins = 0; ins < INSTR; ++ins) {
+    const int u = ins * 64 + lane;
+    const int row = u / U, p = u % U;
+    const int c = unit<HD>(row, p) - row * U;   // the XOR is its own inverse
+    dma16(rs, off + ((uint32_t)row * (uint32_t)ld + (uint32_t)(c * 8)) * 2u, lds_addr(dst + ins * 1024));
+  }
+}
+
+// A wave's walk over its tiles it = wave, wave + 4, ... < ntiles, NSTG tiles of
+// LDS in turn, LOADS load instructions per tile: body(it, stage) runs with
+// tile it landed. A wave waits only for its own loads and reads.
+template <int NSTG, int LOADS, class Issue, class Body>
+DEV void walk_tiles(int wave, int ntiles, Issue issue, Body body) {
+  if constexpr (NSTG == 2) {
+    if (wave < ntiles) issue(wave, 0);
+  }
+  int st = 0;
+  for (int it = wave; it < ntiles; it += 4) {
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // this wave's reads of the stage loaded next are done
+    if constexpr (NSTG == 2) {
+      if (it + 4 < ntiles) {
+        issue(it + 4, st ^ 1);
+        wait_vmcnt<LOADS>();
+      } else {
+        wait_vmcnt<0>();
+      }
+    } else {
+      issue(it, 0);
+      wait_vmcnt<0>();
+    }
+    asm volatile("" ::: "memory");
+    body(it, st);
+    if constexpr (NSTG == 2) st ^= 1;
+  }
+}
+
+template <int HD>
+struct SplitShape {
+  using S = Shape<HD>;
+  static constexpr int NSTG = HD <= 64 ? 2 : 1;
+  static constexpr int INSTR = TILE * HD / 8 / 64;
+  static constexpr int NCH = S::DT * 4;            // 4-register chunks of a [32][HD] accumulator
+  static constexpr int ACC = NCH * 64 * 16;        // its bytes
+  static constexpr int smem(int wave_bytes, int accs) {
+    return 4 * wave_bytes > 4 * accs * ACC + 1024 ? 4 * wave_bytes : 4 * accs * ACC + 1024;
+  }
+};
+
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_fwd_split_kernel(AttnArgs a) {
+  using S = Shape<HD>;
+  using P = SplitShape<HD>;
+  constexpr int STAGE = 2 * S::TBA;
+  __shared__ __attribute__((aligned(1024))) char smem_raw[P::smem(P::NSTG * STAGE, 1)];
+  lds_char_t* smem = (lds_char_t*)smem_raw;
+  const int T = a.T, H = a.H, C = H * HD, Hkv = a.Hkv > 0 ? a.Hkv : H, ld = (H + 2 * Hkv) * HD;
+  const int BH = a.B * H, nqb = (T + SB - 1) / SB;
+  const int bh = blockIdx.x % BH, b = bh / H, h = bh % H;
+  const int q0 = (nqb - 1 - (int)(blockIdx.x / BH)) * SB;   // heaviest blocks first
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, g = lane >> 5;
+  const int q = q0 + lq;
+  const bf16_t* base = a.qkv + (size_t)b * T * ld + h * HD;
+  const v4i32 rs = make_rsrc(a.qkv, (uint32_t)((size_t)a.B * T * ld * 2));
+  const uint32_t koff = (uint32_t)(((size_t)b * T * ld + (H + h / (H / Hkv)) * HD) * 2);
+  const uint32_t voff = koff + (uint32_t)(Hkv * HD * 2);
+
+  bf16x8 qf[S::KS];
+#pragma unroll
+  for (int s = 0; s < S::KS; ++s)
+    qf[s] = as_bf16x8(*reinterpret_cast<const uint4*>(base + (size_t)min(q, T - 1) * ld + 16 * s + 8 * g));
+  floatx16 o[S::DT];
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d) zero(o[d]);
+  float m_run = -INFINITY, l_run = 0.0f;
+  const float sc = LOG2E / sqrtf((float)HD);
+  const int ntiles = (min(T, q0 + SB) + TILE - 1) / TILE;
+  lds_char_t* mine = smem + wave * P::NSTG * STAGE;
+  auto issue = [&](int it, int st) {
+    const uint32_t r = (uint32_t)(it * TILE) * (uint32_t)ld * 2u;
+    issue_rows_w<HD>(rs, koff + r, ld, mine + st * STAGE, lane);
+    issue_rows_w<HD>(rs, voff + r, ld, mine + st * STAGE + S::TBA, lane);
+  };
+  walk_tiles<P::NSTG, 2 * P::INSTR>(wave, ntiles, issue, [&](int it, int st) {
+    const int kv0 = it * TILE;
+    const lds_char_t* Ks = mine + st * STAGE;
+    const lds_char_t* Vs = Ks + S::TBA;
+    floatx16 s[2];
+    float mt = -INFINITY;
+    const int jmax = min(q, T - 1) - kv0 - 4 * g;   // key kv0 + 4g + offset is kept if offset <= jmax
+    const bool diag = kv0 + TILE - 1 > q0 || kv0 + TILE > T;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      zero(s[t]);
+#pragma unroll
+      for (int k = 0; k < S::KS; ++k) s[t] = mfma32(read_row<HD>(Ks, 32 * t + lq, 2 * k + g), qf[k], s[t]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (diag) s[t][r] = (32 * t + acc_row(r, 0) <= jmax) ? s[t][r] : -INFINITY;
+        mt = fmaxf(mt, s[t][r]);
+      }
+    }
+    mt = max32(mt) * sc;
+    const bool grow = mt > m_run + RESCALE_SLACK;
+    if (__ballot(grow) != 0) {
+      const float alpha = grow ? fast_exp2(m_run - mt) : 1.0f;
+      m_run = grow ? mt : m_run;
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < S::DT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+    }
+    // a wave's first tile may hide every key from a query: its shift is still
+    // -inf, and its probabilities come out 0 with any finite one
+    const float shift = m_run == -INFINITY ? 0.0f : m_run;
+    float rsum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = fast_exp2(fmaf(s[t][r], sc, -shift));
+        s[t][r] = p;
+        rsum += p;
+      }
+    l_run += sum32(rsum);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const bf16x8 pf = acc_slots(s[t], hh);
+#pragma unroll
+        for (int d = 0; d < S::DT; ++d) o[d] = mfma32(read_tr<HD>(Vs, 32 * d, 32 * t + 16 * hh, lane), pf, o[d]);
+      }
+  });
+
+  // combine: shifts and sums first, then the waves' outputs scaled to the
+  // common shift (key 0 is visible to every query, so it is finite)
+  typedef LDS_AS float lds_f_t;
+  lds_f_t* ml = (lds_f_t*)smem_raw;
+  lds_v4f32_t* red = (lds_v4f32_t*)(smem + 1024);
+  __syncthreads();
+  if (lane < 32) {
+    ml[wave * 32 + lq] = m_run;
+    ml[128 + wave * 32 + lq] = l_run;
+  }
+  __syncthreads();
+  float M = ml[lq], L = 0.0f;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) M = fmaxf(M, ml[w * 32 + lq]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) L += ml[128 + w * 32 + lq] * fast_exp2(ml[w * 32 + lq] - M);
+  const float alpha = fast_exp2(m_run - M);
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      red[(wave * P::NCH + 4 * d + c) * 64 + lane] =
+          v4f32{o[d][4 * c] * alpha, o[d][4 * c + 1] * alpha, o[d][4 * c + 2] * alpha, o[d][4 * c + 3] * alpha};
+  __syncthreads();
+  if (q >= T) return;
+  const float inv = 1.0f / L;
+  bf16_t* out = a.out + ((size_t)b * T + q) * C + h * HD;
+  for (int k = wave; k < P::NCH; k += 4) {
+    v4f32 v = red[k * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += red[(w * P::NCH + k) * 64 + lane];
+    const int dd = 8 * k + 4 * g;
+    if (dd < HD)
+      *reinterpret_cast<uint2*>(out + dd) = make_uint2(pack2(v.x * inv, v.y * inv), pack2(v.z * inv, v.w * inv));
+  }
+  if (wave == 0 && g == 0) a.lse[(size_t)bh * T + q] = (M + log2f(L)) * LN2;
+}
+
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(AttnArgs a) {
+  using S = Shape<HD>;
+  using P = SplitShape<HD>;
+  constexpr int STAGE = 2 * S::TBA;
+  __shared__ __attribute__((aligned(1024))) char smem_raw[P::smem(P::NSTG * STAGE, 1)];
+  lds_char_t* smem = (lds_char_t*)smem_raw;
+  const int T = a.T, H = a.H, C = H * HD, Hkv = a.Hkv > 0 ? a.Hkv : H, ld = (H + 2 * Hkv) * HD;
+  const int BH = a.B * H, nqb = (T + SB - 1) / SB;
+  const int bh = blockIdx.x % BH, b = bh / H, h = bh % H;
+  const int q0 = (nqb - 1 - (int)(blockIdx.x / BH)) * SB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, g = lane >> 5;
+  const int q = q0 + lq, qr = min(q, T - 1);
+  const bf16_t* qp = a.qkv + ((size_t)b * T + qr) * ld + h * HD + 8 * g;
+  const bf16_t* dp = a.dout + ((size_t)b * T + qr) * C + h * HD + 8 * g;
+  const bf16_t* op = a.out + ((size_t)b * T + qr) * C + h * HD + 8 * g;
+  const v4i32 rs = make_rsrc(a.qkv, (uint32_t)((size_t)a.B * T * ld * 2));
+  const uint32_t koff = (uint32_t)(((size_t)b * T * ld + (H + h / (H / Hkv)) * HD) * 2);
+  const uint32_t voff = koff + (uint32_t)(Hkv * HD * 2);
+
+  bf16x8 qf[S::KS], df[S::KS];
+  uint4 o4[S::KS];
+#pragma unroll
+  for (int s = 0; s < S::KS; ++s) {
+    qf[s] = as_bf16x8(*reinterpret_cast<const uint4*>(qp + 16 * s));
+    df[s] = as_bf16x8(*reinterpret_cast<const uint4*>(dp + 16 * s));
+    o4[s] = *reinterpret_cast<const uint4*>(op + 16 * s);
+  }
+  const float lse2 = a.lse[(size_t)bh * T + qr] * LOG2E;
+  float dpart = 0.0f;
+#pragma unroll
+  for (int s = 0; s < S::KS; ++s) {
+    const uint4 dd = __builtin_bit_cast(uint4, df[s]), oo = o4[s];
+    dpart += lo_f(dd.x) * lo_f(oo.x) + hi_f(dd.x) * hi_f(oo.x) + lo_f(dd.y) * lo_f(oo.y) + hi_f(dd.y) * hi_f(oo.y);
+    dpart += lo_f(dd.z) * lo_f(oo.z) + hi_f(dd.z) * hi_f(oo.z) + lo_f(dd.w) * lo_f(oo.w) + hi_f(dd.w) * hi_f(oo.w);
+  }
+  // D = rowsum(dO * O), stored for the dK/dV kernel, which runs after this one
+  const float dsum = sum32(dpart);
+  if (wave == 0 && g == 0 && q < T) a.dsum[(size_t)bh * T + q] = dsum;
+  floatx16 dq[S::DT];
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d) zero(dq[d]);
+  const float scale = 1.0f / sqrtf((float)HD);
+  const float sc = scale * LOG2E;
+  const int ntiles = (min(T, q0 + SB) + TILE - 1) / TILE;
+  lds_char_t* mine = smem + wave * P::NSTG * STAGE;
+  auto issue = [&](int it, int st) {
+    const uint32_t r = (uint32_t)(it * TILE) * (uint32_t)ld * 2u;
+    issue_rows_w<HD>(rs, koff + r, ld, mine + st * STAGE, lane);
+    issue_rows_w<HD>(rs, voff + r, ld, mine + st * STAGE + S::TBA, lane);
+  };
+  walk_tiles<P::NSTG, 2 * P::INSTR>(wave, ntiles, issue, [&](int it, int st) {
+    const int kv0 = it * TILE;
+    const lds_char_t* Ks = mine + st * STAGE;
+    const lds_char_t* Vs = Ks + S::TBA;
+    const int jmax = qr - kv0 - 4 * g;
+    const bool diag = kv0 + TILE - 1 > q0 || kv0 + TILE > T;
+    floatx16 p[2], ds[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      zero(p[t]);
+      zero(ds[t]);
+#pragma unroll
+      for (int k = 0; k < S::KS; ++k) {
+        p[t] = mfma32(read_row<HD>(Ks, 32 * t + lq, 2 * k + g), qf[k], p[t]);
+        ds[t] = mfma32(read_row<HD>(Vs, 32 * t + lq, 2 * k + g), df[k], ds[t]);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float pv = fast_exp2(p[t][r] * sc - lse2);
+        if (diag) pv = (32 * t + acc_row(r, 0) <= jmax) ? pv : 0.0f;
+        ds[t][r] = pv * (ds[t][r] - dsum);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const bf16x8 sf = acc_slots(ds[t], hh);
+#pragma unroll
+        for (int d = 0; d < S::DT; ++d) dq[d] = mfma32(read_tr<HD>(Ks, 32 * d, 32 * t + 16 * hh, lane), sf, dq[d]);
+      }
+  });
+
+  lds_v4f32_t* red = (lds_v4f32_t*)smem_raw;
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      red[(wave * P::NCH + 4 * d + c) * 64 + lane] =
+          v4f32{dq[d][4 * c], dq[d][4 * c + 1], dq[d][4 * c + 2], dq[d][4 * c + 3]};
+  __syncthreads();
+  if (q >= T) return;
+  bf16_t* dst = a.dqkv + ((size_t)b * T + q) * ld + h * HD;
+  for (int k = wave; k < P::NCH; k += 4) {
+    v4f32 v = red[k * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += red[(w * P::NCH + k) * 64 + lane];
+    const int dd = 8 * k + 4 * g;
+    if (dd < HD)
+      *reinterpret_cast<uint2*>(dst + dd) =
+          make_uint2(pack2(v.x * scale, v.y * scale), pack2(v.z * scale, v.w * scale));
+  }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_split_kernel(AttnArgs a) {
+  using S = Shape<HD>;
+  using P = SplitShape<HD>;
+  constexpr int STAGE = 2 * S::TBA + 1024;   // Q tile, dO tile, lse and D rows
+  __shared__ __attribute__((aligned(1024))) char smem_raw[P::smem(P::NSTG * STAGE, 2)];
+  lds_char_t* smem = (lds_char_t*)smem_raw;
+  const int T = a.T, H = a.H, C = H * HD, Hkv = a.Hkv > 0 ? a.Hkv : H, ld = (H + 2 * Hkv) * HD;
+  const int G = H / Hkv;
+  const int BH = a.B * Hkv;
+  const int bj = blockIdx.x % BH, b = bj / Hkv, j = bj % Hkv;
+  const int kv0 = (int)(blockIdx.x / BH) * SB;   // heaviest (first) key blocks first
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lk = lane & 31, g = lane >> 5;
+  const int kv = kv0 + lk;
+  const bf16_t* kp = a.qkv + ((size_t)b * T + min(kv, T - 1)) * ld + (H + j) * HD + 8 * g;
+  const v4i32 rq = make_rsrc(a.qkv, (uint32_t)((size_t)a.B * T * ld * 2));
+  const v4i32 rd = make_rsrc(a.dout, (uint32_t)((size_t)a.B * T * C * 2));
+  const v4i32 rl = make_rsrc(a.lse, (uint32_t)((size_t)a.B * H * T * 4));
+  const v4i32 rD = make_rsrc(a.dsum, (uint32_t)((size_t)a.B * H * T * 4));
+  bf16x8 kf[S::KS], vf[S::KS];
+#pragma unroll
+  for (int s = 0; s < S::KS; ++s) {
+    kf[s] = as_bf16x8(*reinterpret_cast<const uint4*>(kp + 16 * s));
+    vf[s] = as_bf16x8(*reinterpret_cast<const uint4*>(kp + Hkv * HD + 16 * s));
+  }
+  floatx16 dk[S::DT], dv[S::DT];
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d) {
+    zero(dk[d]);
+    zero(dv[d]);
+  }
+  const float scale = 1.0f / sqrtf((float)HD);
+  const float sc = scale * LOG2E;
+  // query tiles from the diagonal to the end, of each query head of the group
+  // in turn
+  const int nt = (T - kv0 + TILE - 1) / TILE;
+  lds_char_t* mine = smem + wave * P::NSTG * STAGE;
+  auto issue = [&](int it, int st) {
+    lds_char_t* dst = mine + st * STAGE;
+    const int h = j * G + it / nt, q0 = kv0 + (it % nt) * TILE;
+    issue_rows_w<HD>(rq, (uint32_t)((((size_t)b * T + q0) * ld + h * HD) * 2), ld, dst, lane);
+    issue_rows_w<HD>(rd, (uint32_t)((((size_t)b * T + q0) * C + h * HD) * 2), C, dst + S::TBA, lane);
+    // the tile's 64 log-sum-exp and D values (256 bytes each): 16 lanes
+    if (lane < 16) {
+      const uint32_t off = ((uint32_t)(b * H + h) * (uint32_t)T + (uint32_t)q0) * 4u + 16u * lane;
+      dma16(rl, off, lds_addr(dst + 2 * S::TBA));
+      dma16(rD, off, lds_addr(dst + 2 * S::TBA + 256));
+    }
+  };
+  walk_tiles<P::NSTG, 2 * P::INSTR + 2>(wave, nt * G, issue, [&](int it, int st) {
+    const int q0 = kv0 + (it % nt) * TILE;
+    const lds_char_t* Qs = mine + st * STAGE;
+    const lds_char_t* Ds = Qs + S::TBA;
+    const lds_char_t* lr = Qs + 2 * S::TBA;
+    const bool diag = q0 < kv0 + SB || q0 + TILE > T || kv0 + SB > T;
+#pragma unroll 1
+    for (int t = 0; t < 2; ++t) {
+      floatx16 p, ds;
+      zero(p);
+      zero(ds);
+#pragma unroll
+      for (int k = 0; k < S::KS; ++k) {
+        p = mfma32(read_row<HD>(Qs, 32 * t + lk, 2 * k + g), kf[k], p);
+        ds = mfma32(read_row<HD>(Ds, 32 * t + lk, 2 * k + g), vf[k], ds);
+      }
+#pragma unroll
+      for (int c4 = 0; c4 < 4; ++c4) {
+        const int qi = 32 * t + 8 * c4 + 4 * g;   // 4 consecutive queries of the tile
+        const v4f32 l4 = *reinterpret_cast<const lds_v4f32_t*>(lr + 4 * qi);
+        const v4f32 d4 = *reinterpret_cast<const lds_v4f32_t*>(lr + 256 + 4 * qi);
+        // query q0 + qi + e sees key kv if kv <= query < T (and kv < T)
+        const int qlo = kv - q0 - qi, qhi = T - q0 - qi;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = 4 * c4 + e;
+          float pv = fast_exp2(p[r] * sc - l4[e] * LOG2E);
+          float dd = ds[r] - d4[e];
+          if (diag) {
+            // rows past T hold no log-sum-exp or D of this head: both factors go
+            const bool in = e >= qlo && e < qhi && kv < T;
+            pv = in ? pv : 0.0f;
+            dd = in ? dd : 0.0f;
+          }
+          p[r] = pv;
+          ds[r] = pv * dd;
+        }
+      }
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const bf16x8 pf = acc_slots(p, hh), sf = acc_slots(ds, hh);
+#pragma unroll
+        for (int d = 0; d < S::DT; ++d) {
+          dv[d] = mfma32(read_tr<HD>(Ds, 32 * d, 32 * t + 16 * hh, lane), pf, dv[d]);
+          dk[d] = mfma32(read_tr<HD>(Qs, 32 * d, 32 * t + 16 * hh, lane), sf, dk[d]);
+        }
+      }
+    }
+  });
+
+  lds_v4f32_t* red = (lds_v4f32_t*)smem_raw;
+  constexpr int NC2 = 2 * P::NCH;   // dK's chunks, then dV's
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < S::DT; ++d)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      red[(wave * NC2 + 4 * d + c) * 64 + lane] =
+          v4f32{dk[d][4 * c], dk[d][4 * c + 1], dk[d][4 * c + 2], dk[d][4 * c + 3]};
+      red[(wave * NC2 + P::NCH + 4 * d + c) * 64 + lane] =
+          v4f32{dv[d][4 * c], dv[d][4 * c + 1], dv[d][4 * c + 2], dv[d][4 * c + 3]};
+    }
+  __syncthreads();
+  if (kv >= T) return;
+  bf16_t* dst = a.dqkv + ((size_t)b * T + kv) * ld + (H + j) * HD;
+  for (int k = wave; k < NC2; k += 4) {
+    v4f32 v = red[k * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += red[(w * NC2 + k) * 64 + lane];
+    const bool is_v = k >= P::NCH;
+    const float f = is_v ? 1.0f : scale;
+    const int dd = 8 * (is_v ? k - P::NCH : k) + 4 * g;
+    if (dd < HD)
+      *reinterpret_cast<uint2*>(dst + (is_v ? Hkv * HD : 0) + dd) =
+          make_uint2(pack2(v.x * f, v.y * f), pack2(v.z * f, v.w * f));
+  }
+}
+
+// Whether `heads` heads with walks of up to `tiles` tiles take the kernels for
+// short grids: at least min_tiles, at most max_blocks workgroups of 32 rows
+bool split_walk(const AttnArgs& a, int heads, int tiles, int min_tiles, int max_blocks) {
+  return tiles >= min_tiles && (long)heads * ((a.T + SB - 1) / SB) <= max_blocks;
+}
+
 template <int HD>
 hipError_t fwd_t(const AttnArgs& a, hipStream_t s) {
-  dim3 grid(((a.T + BQ - 1) / BQ) * a.B * a.H);
-  hipLaunchKernelGGL(attn_fwd_kernel<HD>, grid, dim3(256), 0, s, a);
+  const int BH = a.B * a.H, tiles = (a.T + TILE - 1) / TILE;
+  if (split_walk(a, BH, tiles, 3, 256))
+    hipLaunchKernelGGL(attn_fwd_split_kernel<HD>, dim3((a.T + SB - 1) / SB * BH), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(attn_fwd_kernel<HD>, dim3((a.T + BQ - 1) / BQ * BH), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 template <int HD>
 hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   // dQ first: it also computes D = rowsum(dO * O), which dK/dV reads
-  const int nb = (a.T + BQ - 1) / BQ, Hkv = a.Hkv > 0 ? a.Hkv : a.H;
-  hipLaunchKernelGGL(attn_bwd_dq_kernel<HD>, dim3(nb * a.B * a.H), dim3(256), 0, s, a);
+  const int nb = (a.T + BQ - 1) / BQ, ns = (a.T + SB - 1) / SB, Hkv = a.Hkv > 0 ? a.Hkv : a.H;
+  const int tiles = (a.T + TILE - 1) / TILE;
+  if (split_walk(a, a.B * a.H, tiles, 3, 256))
+    hipLaunchKernelGGL(attn_bwd_dq_split_kernel<HD>, dim3(ns * a.B * a.H), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<HD>, dim3(nb * a.B * a.H), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if constexpr (HD == 128)
+  if (split_walk(a, a.B * Hkv, tiles * (a.H / Hkv), 2, 512))
+    hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<HD>, dim3(ns * a.B * Hkv), dim3(256), 0, s, a);
+  else if constexpr (HD == 128)
     hipLaunchKernelGGL(attn_bwd_dkdv8_kernel<HD>, dim3(nb * a.B * Hkv), dim3(512), 0, s, a);
   else
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<HD>, dim3(nb * a.B * Hkv), dim3(256), 0, s, a);

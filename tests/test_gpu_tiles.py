@@ -20,7 +20,7 @@ def _np(t):
 # (B, T): 1 row, 63..65 (one 64-row tile and its edges), 203, 705 and 1089
 # (64 x 128 and 128-row tiles with a one-row tail), 2050, and 16 x 1009 (the
 # 256-row tiles, ragged; only the last sequence goes through the oracle)
-@pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (1, 64), (5, 13), (1, 203), (1, 705), (3, 363), (2, 1025), (16, 1009)])
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (1, 64), (1, 65), (5, 13), (1, 203), (1, 705), (3, 363), (2, 1025), (16, 1009)])
 def test_block_against_oracle(B, T):
     from paper_2609_28568_amd import binding
     w = workload("tiny", n_layer=1, n_head=12, d_model=768, d_ff=3072, vocab=64, vocab_padded=64, max_seq_len=T, B=B,
@@ -52,6 +52,37 @@ def test_block_against_oracle(B, T):
         # with one token the softmax is constant: its query and key gradients are exactly 0
         e = rel_l2(g[k], grads[k])
         assert e < REL_L2, (k, e)
+
+
+# The attention kernels for short grids (32 rows a workgroup, tiles dealt to its
+# waves) at every head size: sequences of two and more tiles with one-row tails,
+# up to and past the largest grids they take (256 and 512 workgroups)
+@pytest.mark.parametrize("H,C", [(4, 64), (4, 128), (2, 128), (1, 128)])
+@pytest.mark.parametrize("B,T", [(1, 65), (2, 130), (1, 257), (3, 300), (32, 129)])
+def test_short_grid_attention(H, C, B, T):
+    from paper_2609_28568_amd import binding
+    w = workload("tiny", n_layer=1, n_head=H, d_model=C, d_ff=4 * C, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=75), seed=76)
+    p["qkvw"] *= 8.0   # scores far from uniform
+    x, dy = synth.block_inputs(w, seed=77)
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    tx, tdy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, dy))
+    out, dx = torch.empty_like(tx), torch.empty_like(tx)
+    print(f"attention {B} x {T}, {H} heads of {C // H}", flush=True)
+    m.block_forward(0, tx, out)
+    m.block_backward(0, tdy, dx)
+    g = m.to_dict("grads")
+    att, out, dx = _np(m.activation("att", 0)), _np(out), _np(dx)
+    m.close()
+    ocfg = oracle_config(w)
+    y, cache = oracle.block_forward(x.reshape(B, T, C), p, 0, ocfg)
+    grads = oracle.zero_grads(p)
+    ref = oracle.block_backward(dy.reshape(B, T, C), cache, p, 0, ocfg, grads)
+    assert rel_l2(att, cache["att"]) < REL_L2
+    assert rel_l2(out, y) < REL_L2 and rel_l2(dx, ref) < REL_L2
+    for k in ("qkvw", "qkvb", "attprojw", "ln1w"):
+        assert rel_l2(g[k], grads[k]) < REL_L2, (k, rel_l2(g[k], grads[k]))
 
 
 # The caller's buffers stand in for copies unless they are misaligned, overlap
