@@ -140,11 +140,12 @@ __global__ __launch_bounds__(1024) void mean_kernel(const float* __restrict__ x,
 
 __global__ void embed_fwd_kernel(const int32_t* __restrict__ ids, const float* __restrict__ wte,
                                  const float* __restrict__ wpe, bf16_t* __restrict__ x, int BT, int T, int C, int V,
-                                 uint32_t* __restrict__ bad) {
+                                 uint32_t* __restrict__ bad, int32_t* __restrict__ ids_copy) {
   long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i >= (long)BT * C) return;
   const int row = i / C, c = i % C, t = row % T;
   int id = ids[row];
+  if (ids_copy && c == 0) ids_copy[row] = id;   // as given: the backward skips the bad ones itself
   if ((unsigned)id >= (unsigned)V) {
     // contract violation: reported, and row 0 read in its place
     if (bad && c == 0) atomicOr(bad, ID_BAD_INPUT);
@@ -170,10 +171,30 @@ __global__ void embed_fwd_kernel(const int32_t* __restrict__ ids, const float* _
 // us; 1024 positions: 44 -> 6.5 us; 64 positions of 64: 23.7 -> 4.6 us.
 constexpr int EMB_C = 64, EMB_LARGE = 4096;
 constexpr float LOG2E_F = 1.4426950408889634f;
+//
+// Position table (the workgroups after the token table's, in the same launch):
+// dwpe[t] (=|+=) the sum over the batch, in batch order; rows t >= T get no
+// gradient. On its own it took 7 of 47 us at 16 x 1024 x 768.
 template <int P>
-__global__ __launch_bounds__(1024) void embed_bwd_wte_kernel(const int32_t* __restrict__ ids,
-                                                             const bf16_t* __restrict__ dx, float* __restrict__ dwte,
-                                                             int BT, int C, int V) {
+__global__ __launch_bounds__(1024) void embed_bwd_kernel(const int32_t* __restrict__ ids, const bf16_t* __restrict__ dx,
+                                                         float* __restrict__ dwte, float* __restrict__ dwpe, int B,
+                                                         int T, int Tmax, int C, int V, int accumulate, int pos_blocks,
+                                                         int wte_blocks) {
+  const int BT = B * T;
+  if ((int)blockIdx.x >= wte_blocks) {
+    const long i = ((long)(blockIdx.x - wte_blocks) * 1024 + threadIdx.x) * 4;
+    if (i >= (long)Tmax * C) return;
+    const int t = i / C;
+    float4 acc = accumulate ? *reinterpret_cast<const float4*>(dwpe + i) : make_float4(0, 0, 0, 0);
+    if (t < T) {
+      for (int b = 0; b < B; ++b) {
+        uint2 u = *reinterpret_cast<const uint2*>(dx + (size_t)b * T * C + i);
+        acc.x += lo_f(u.x); acc.y += hi_f(u.x); acc.z += lo_f(u.y); acc.w += hi_f(u.y);
+      }
+    }
+    *reinterpret_cast<float4*>(dwpe + i) = acc;
+    return;
+  }
   constexpr int W = P / 32, Q = 1024 / P;   // positions per half-wave; threads per position in the sort
   // key = id * 1024 + position: ids are below 65536, so keys are unique and
   // sort by (id, position); positions past the end and ids outside [0, V) (a
@@ -186,7 +207,7 @@ __global__ __launch_bounds__(1024) void embed_bwd_wte_kernel(const int32_t* __re
   __shared__ float2 head[32][32];
   __shared__ int cont[32];
   const int tid = threadIdx.x;
-  const int p0 = blockIdx.x * P;
+  const int slice = blockIdx.x / pos_blocks, p0 = (blockIdx.x - slice * pos_blocks) * P;
   if (tid < P) {
     const int p = p0 + tid;
     const int id = p < BT ? ids[p] : -1;
@@ -213,7 +234,7 @@ __global__ __launch_bounds__(1024) void embed_bwd_wte_kernel(const int32_t* __re
     }
   }
   __syncthreads();
-  const int hw = tid >> 5, c = min((int)blockIdx.y * EMB_C + 2 * (tid & 31), C - 2);
+  const int hw = tid >> 5, c = min(slice * EMB_C + 2 * (tid & 31), C - 2);
   // A run that reaches into the next half-waves is added whole by the half-wave
   // it starts in: the others leave their share of it in LDS (head), and say in
   // cont whether it goes on past them.
@@ -226,7 +247,7 @@ __global__ __launch_bounds__(1024) void embed_bwd_wte_kernel(const int32_t* __re
   auto add_row = [&](uint32_t id, float2 v) {
     const float a0 = __shfl(v.x, l >> 1, 32), a1 = __shfl(v.y, l >> 1, 32);
     const float b0 = __shfl(v.x, 16 + (l >> 1), 32), b1 = __shfl(v.y, 16 + (l >> 1), 32);
-    const int c0 = blockIdx.y * EMB_C + l;
+    const int c0 = slice * EMB_C + l;
     float* d = dwte + (size_t)id * C + c0;
     if (c0 < C) atomicAdd(d, (l & 1) ? a1 : a0);
     if (c0 + 32 < C) atomicAdd(d + 32, (l & 1) ? b1 : b0);
@@ -279,23 +300,6 @@ __global__ __launch_bounds__(1024) void embed_bwd_wte_kernel(const int32_t* __re
     }
     add_row(sorted[hw * W + W - 1] >> 10, acc);
   }
-}
-
-// position table: dwpe[t] = sum over the batch, in batch order; rows t >= T
-// get no gradient
-__global__ void embed_bwd_wpe_kernel(const bf16_t* __restrict__ dx, float* __restrict__ dwpe, int B, int T, int Tmax,
-                                     int C, int accumulate) {
-  long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i >= (long)Tmax * C) return;
-  const int t = i / C;
-  float4 acc = accumulate ? *reinterpret_cast<const float4*>(dwpe + i) : make_float4(0, 0, 0, 0);
-  if (t < T) {
-    for (int b = 0; b < B; ++b) {
-      uint2 u = *reinterpret_cast<const uint2*>(dx + (size_t)b * T * C + i);
-      acc.x += lo_f(u.x); acc.y += hi_f(u.x); acc.z += lo_f(u.y); acc.w += hi_f(u.y);
-    }
-  }
-  *reinterpret_cast<float4*>(dwpe + i) = acc;
 }
 
 // ------------------------------------------------------------ cross-entropy
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const float* __restrict__ g,
 }
 
 __global__ __launch_bounds__(256) void clip_coef_kernel(const float* __restrict__ parts, int nparts, float clip,
-                                                        float* __restrict__ norm_coef) {
+                                                        float* __restrict__ norm_coef, float* __restrict__ norm_out) {
   __shared__ float sh[4];
   float s = 0.0f;
   for (int i = threadIdx.x; i < nparts; i += 256) s += parts[i];
@@ -492,6 +496,7 @@ __global__ __launch_bounds__(256) void clip_coef_kernel(const float* __restrict_
   if (threadIdx.x == 0) {
     float norm = sqrtf(s);
     norm_coef[0] = norm;
+    if (norm_out) norm_out[0] = norm;
     norm_coef[1] = norm > clip ? clip / norm : 1.0f;
   }
 }
@@ -641,34 +646,26 @@ hipError_t launch_sum_scaled(const float* x, int n, float scale, float* out, hip
 }
 
 hipError_t launch_embed_fwd(const int32_t* ids, const float* wte, const float* wpe, bf16_t* x, int B, int T, int C,
-                            int V, uint32_t* bad, hipStream_t s) {
+                            int V, uint32_t* bad, hipStream_t s, int32_t* ids_copy) {
   if (C % 4) return hipErrorInvalidValue;
   long n4 = (long)B * T * C / 4;
   hipLaunchKernelGGL(embed_fwd_kernel, dim3(blocks_for(n4, 256)), dim3(256), 0, s, ids, wte, wpe, x, B * T, T, C, V,
-                     bad);
+                     bad, ids_copy);
   return hipGetLastError();
 }
 
-hipError_t launch_embed_bwd(const int32_t* ids, const bf16_t* dx, float* dwte, int B, int T, int C, int V,
-                            hipStream_t s) {
-  if (C % 4) return hipErrorInvalidValue;
-  const int BT = B * T;
-  if (V > 65536) return hipErrorInvalidValue;   // 16-bit ids in the sort keys
-  const unsigned cols = (unsigned)((C + EMB_C - 1) / EMB_C);
-  if (BT >= EMB_LARGE)
-    hipLaunchKernelGGL(embed_bwd_wte_kernel<1024>, dim3((BT + 1023) / 1024, cols), dim3(1024), 0, s, ids, dx, dwte, BT,
-                       C, V);
+hipError_t launch_embed_bwd(const int32_t* ids, const bf16_t* dx, float* dwte, float* dwpe, int B, int T, int Tmax,
+                            int C, int V, int accumulate_pos, hipStream_t s) {
+  if (C % 4 || V > 65536) return hipErrorInvalidValue;   // 16-bit ids in the sort keys
+  const int BT = B * T, P = BT >= EMB_LARGE ? 1024 : 256;
+  const int pos = (BT + P - 1) / P, wte = pos * ((C + EMB_C - 1) / EMB_C);
+  const dim3 grid((unsigned)wte + blocks_for((long)Tmax * C / 4, 1024));
+  if (P == 1024)
+    hipLaunchKernelGGL(embed_bwd_kernel<1024>, grid, dim3(1024), 0, s, ids, dx, dwte, dwpe, B, T, Tmax, C, V,
+                       accumulate_pos, pos, wte);
   else
-    hipLaunchKernelGGL(embed_bwd_wte_kernel<256>, dim3((BT + 255) / 256, cols), dim3(1024), 0, s, ids, dx, dwte, BT, C,
-                       V);
-  return hipGetLastError();
-}
-
-hipError_t launch_embed_bwd_pos(const bf16_t* dx, float* dwpe, int B, int T, int Tmax, int C, int accumulate,
-                                hipStream_t s) {
-  long n4 = (long)Tmax * C / 4;
-  hipLaunchKernelGGL(embed_bwd_wpe_kernel, dim3(blocks_for(n4, 256)), dim3(256), 0, s, dx, dwpe, B, T, Tmax, C,
-                     accumulate);
+    hipLaunchKernelGGL(embed_bwd_kernel<256>, grid, dim3(1024), 0, s, ids, dx, dwte, dwpe, B, T, Tmax, C, V,
+                       accumulate_pos, pos, wte);
   return hipGetLastError();
 }
 
@@ -720,8 +717,9 @@ hipError_t launch_sumsq(const float* g, long n, float* parts, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_clip_coef(const float* parts, int nparts, float clip, float* norm_coef, hipStream_t s) {
-  hipLaunchKernelGGL(clip_coef_kernel, dim3(1), dim3(256), 0, s, parts, nparts, clip, norm_coef);
+hipError_t launch_clip_coef(const float* parts, int nparts, float clip, float* norm_coef, hipStream_t s,
+                            float* norm_out) {
+  hipLaunchKernelGGL(clip_coef_kernel, dim3(1), dim3(256), 0, s, parts, nparts, clip, norm_coef, norm_out);
   return hipGetLastError();
 }
 

@@ -1085,12 +1085,11 @@ gpt2_status gpt2_forward(gpt2_model* m, const int32_t* d_inputs, const int32_t* 
   const int BT = (int)d.BT, C = d.C;
   m->have_dlogits = false;
   m->have_loss = false;
-  // keep the ids for the embedding backward
-  TRY(hipMemcpyAsync(m->ids(), d_inputs, (size_t)BT * 4, hipMemcpyDeviceToDevice, m->stream));
-  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * BT + 8.0 * BT * C + 2.0 * BT * C,
+  // (which also keeps the ids for the embedding backward)
+  TRY(m->run(GPT2_K_OTHER, 0.0, 8.0 * BT + 8.0 * BT * C + 2.0 * BT * C,
              [&] {
                return launch_embed_fwd(d_inputs, m->pf(K_WTE), m->pf(K_WPE), m->res(0), d.B, d.T, C, d.V, m->id_flag(),
-                                       m->stream);
+                                       m->stream, m->ids());
              }));
   bool ln_done = false;
   for (int l = 0; l < d.L; ++l) {
@@ -1168,10 +1167,9 @@ gpt2_status gpt2_backward(gpt2_model* m, int32_t accumulate) {
   }
   const bf16_t* dres = grads_of_layer(m, 0).dres_in;
   // embedding: scatter into the token table (after the head's share), sum into positions
-  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * BT + 2.0 * BT * C + 8.0 * BT * C,
-             [&] { return launch_embed_bwd(m->ids(), dres, m->gf(K_WTE), d.B, d.T, C, d.V, m->stream); }));
-  TRY(m->run(GPT2_K_OTHER, 0.0, 2.0 * BT * C + 4.0 * d.Tmax * C * (1 + acc),
-             [&] { return launch_embed_bwd_pos(dres, m->gf(K_WPE), d.B, d.T, d.Tmax, C, acc, m->stream); }));
+  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * BT + 12.0 * BT * C + 4.0 * d.Tmax * C * (1 + acc), [&] {
+    return launch_embed_bwd(m->ids(), dres, m->gf(K_WTE), m->gf(K_WPE), d.B, d.T, d.Tmax, C, d.V, acc, m->stream);
+  }));
   {
     gpt2_status s = grouped_weight_grads(m, 0, d.L, acc);
     if (s != GPT2_OK) return s;
@@ -1195,9 +1193,7 @@ gpt2_status adamw_step_with(gpt2_model* m, int64_t step, float* lr_out, float* d
   float* grads = static_cast<float*>(m->buf.grads_f32);
   TRY(m->run(GPT2_K_OPTIMIZER, 0.0, 4.0 * n, [&] { return launch_sumsq(grads, n, parts, m->stream); }));
   TRY(m->run(GPT2_K_OPTIMIZER, 0.0, 4.0 * sumsq_parts(),
-             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream); }));
-  if (d_grad_norm_out)
-    TRY(hipMemcpyAsync(d_grad_norm_out, nc, sizeof(float), hipMemcpyDeviceToDevice, m->stream));
+             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, d_grad_norm_out); }));
   const double lr = lr_schedule(c, step);
   AdamArgs a{};
   a.p = static_cast<float*>(m->buf.params_f32);
@@ -1364,10 +1360,9 @@ gpt2_status gpt2_embedding_backward(gpt2_model* m, const int32_t* d_ids, const v
   const int acc = accumulate ? 1 : 0;
   if (!acc)  // zero-slice reduction writes zeros
     TRY(launch_reduce_slices(nullptr, 0, (long)m->kn[K_WTE], m->gf(K_WTE), 0, m->stream));
-  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * d.BT + 10.0 * d.BT * d.C,
-             [&] { return launch_embed_bwd(d_ids, dx, m->gf(K_WTE), d.B, d.T, d.C, d.V, m->stream); }));
-  TRY(m->run(GPT2_K_OTHER, 0.0, 2.0 * d.BT * d.C + 4.0 * d.Tmax * d.C * (1 + acc),
-             [&] { return launch_embed_bwd_pos(dx, m->gf(K_WPE), d.B, d.T, d.Tmax, d.C, acc, m->stream); }));
+  TRY(m->run(GPT2_K_OTHER, 0.0, 4.0 * d.BT + 12.0 * d.BT * d.C + 4.0 * d.Tmax * d.C * (1 + acc), [&] {
+    return launch_embed_bwd(d_ids, dx, m->gf(K_WTE), m->gf(K_WPE), d.B, d.T, d.Tmax, d.C, d.V, acc, m->stream);
+  }));
   return GPT2_OK;
 }
 

@@ -241,13 +241,13 @@ hipError_t launch_reduce_parts_multi(const ReducePartsJobs& J, int S, long strid
 // is not null); the embedding backward skips them.
 constexpr uint32_t ID_BAD_INPUT = 1u, ID_BAD_TARGET = 2u;
 hipError_t launch_embed_fwd(const int32_t* ids, const float* wte, const float* wpe, bf16_t* x, int B,
-                            int T, int C, int V, uint32_t* bad, hipStream_t s);
-// dwte[ids[r]] += dx[r] (fp32 atomics; adds to what is there)
-hipError_t launch_embed_bwd(const int32_t* ids, const bf16_t* dx, float* dwte, int B, int T, int C, int V,
-                            hipStream_t s);
-// dwpe[t] = (accumulate ? dwpe[t] : 0) + sum_b dx[b, t] for t < T; rows T..Tmax-1 get 0 added
-hipError_t launch_embed_bwd_pos(const bf16_t* dx, float* dwpe, int B, int T, int Tmax, int C,
-                                int accumulate, hipStream_t s);
+                            int T, int C, int V, uint32_t* bad, hipStream_t s,
+                            int32_t* ids_copy = nullptr);   // ids_copy: the ids go there too
+// dwte[ids[r]] += dx[r] (fp32 atomics; adds to what is there), and
+// dwpe[t] = (accumulate_pos ? dwpe[t] : 0) + sum_b dx[b, t] for t < T; rows
+// T..Tmax-1 get 0 added
+hipError_t launch_embed_bwd(const int32_t* ids, const bf16_t* dx, float* dwte, float* dwpe, int B, int T, int Tmax,
+                            int C, int V, int accumulate_pos, hipStream_t s);
 
 // fused softmax cross-entropy over the first V of Vp columns; dlogits
 // (scaled) overwrite the logits; losses fp32 [rows]
@@ -351,9 +351,10 @@ hipError_t launch_init_params(const InitArgs& a, hipStream_t s);
 // ---------------------------------------------------------------- optimizer
 int sumsq_parts();
 hipError_t launch_sumsq(const float* g, long n, float* parts, hipStream_t s);
-// norm = sqrt(sum parts); coef = clip/norm if norm > clip else 1
-hipError_t launch_clip_coef(const float* parts, int nparts, float clip, float* norm_coef,
-                            hipStream_t s);
+// norm = sqrt(sum parts); coef = clip/norm if norm > clip else 1; norm_out (when
+// not null) takes the norm too
+hipError_t launch_clip_coef(const float* parts, int nparts, float clip, float* norm_coef, hipStream_t s,
+                            float* norm_out = nullptr);
 
 struct AdamSegments {
   long end[16];    // exclusive end offset (elements) of each segment

@@ -829,8 +829,7 @@ gpt2_status qwen3_adamw_step(qwen3_model* m, int64_t step, float* d_grad_norm_ou
   const int OPT = QWEN3_K_OPTIMIZER;
   TRY(m->run(OPT, 0.0, 4.0 * n, [&] { return launch_sumsq(grads, n, parts, m->stream); }));
   TRY(m->run(OPT, 0.0, 4.0 * sumsq_parts(),
-             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream); }));
-  if (d_grad_norm_out) TRY(hipMemcpyAsync(d_grad_norm_out, nc, sizeof(float), hipMemcpyDeviceToDevice, m->stream));
+             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, d_grad_norm_out); }));
   AdamArgs a{};
   a.p = static_cast<float*>(m->buf.lora_f32);
   a.g = grads;
