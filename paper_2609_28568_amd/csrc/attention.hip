@@ -306,7 +306,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
 
 // ------------------------------------------------------------------ backward
 
-// D[b,h,t] = sum_d dO * O, one thread per (token, head)
 // dK, dV for 128 keys (4 waves x 32), walking query tiles of 64 from the
 // diagonal to the end.
 // At hd 128 one workgroup per CU: the K/V fragments and the dK/dV
