@@ -717,6 +717,16 @@ hipError_t launch_sumsq(const float* g, long n, float* parts, hipStream_t s) {
   return hipGetLastError();
 }
 
+bool on_this_device(const void* p) {
+  hipPointerAttribute_t at{};
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();   // memory that the runtime does not know
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 hipError_t launch_clip_coef(const float* parts, int nparts, float clip, float* norm_coef, hipStream_t s,
                             float* norm_out) {
   hipLaunchKernelGGL(clip_coef_kernel, dim3(1), dim3(256), 0, s, parts, nparts, clip, norm_coef, norm_out);

@@ -850,13 +850,14 @@ gpt2_status grouped_weight_grads(Model* m, int l0, int nl, int acc, const bf16_t
   return GPT2_OK;
 }
 
-// Whether kernels can take a caller's [BT, C] buffer in place of a copy: its
-// alignment allows their accesses, and it is none of the model's own memory
-// (which the pass reads and writes as it goes) nor overlaps `other`.
 bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
   return a && b && x < y + nb && y < x + na;
 }
+// Whether kernels can take a caller's [BT, C] buffer in place of a copy: it is
+// this device's memory, its alignment allows their accesses, and it is none of
+// the model's own memory (which the pass reads and writes as it goes) nor
+// overlaps `other`.
 bool in_place_ok(const Model* m, const void* p, size_t align, const void* other) {
   const size_t bytes = (size_t)m->d.BT * m->d.C * 2, n = m->n_params;
   if (!p || reinterpret_cast<uintptr_t>(p) % align || overlap(p, bytes, other, bytes)) return false;
@@ -866,7 +867,7 @@ bool in_place_ok(const Model* m, const void* p, size_t align, const void* other)
       {b.params_bf16, 2 * n}, {b.activations, m->act.total}, {b.workspace, m->ws.total}};
   for (const auto& o : own)
     if (overlap(p, bytes, o.first, o.second)) return false;
-  return true;
+  return on_this_device(p);
 }
 
 double lr_schedule(const gpt2_config& c, int64_t step) {
@@ -1192,8 +1193,13 @@ gpt2_status adamw_step_with(gpt2_model* m, int64_t step, float* lr_out, float* d
   const long n = (long)m->n_params;
   float* grads = static_cast<float*>(m->buf.grads_f32);
   TRY(m->run(GPT2_K_OPTIMIZER, 0.0, 4.0 * n, [&] { return launch_sumsq(grads, n, parts, m->stream); }));
-  TRY(m->run(GPT2_K_OPTIMIZER, 0.0, 4.0 * sumsq_parts(),
-             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, d_grad_norm_out); }));
+  // the kernel writes the caller's copy of the norm too, where it can reach it
+  const bool direct = d_grad_norm_out && on_this_device(d_grad_norm_out);
+  TRY(m->run(GPT2_K_OPTIMIZER, 0.0, 4.0 * sumsq_parts(), [&] {
+    return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, direct ? d_grad_norm_out : nullptr);
+  }));
+  if (d_grad_norm_out && !direct)
+    TRY(hipMemcpyAsync(d_grad_norm_out, nc, sizeof(float), hipMemcpyDeviceToDevice, m->stream));
   const double lr = lr_schedule(c, step);
   AdamArgs a{};
   a.p = static_cast<float*>(m->buf.params_f32);

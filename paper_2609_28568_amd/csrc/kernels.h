@@ -350,6 +350,9 @@ hipError_t launch_init_params(const InitArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- optimizer
 int sumsq_parts();
+// Whether kernels on the current device can take p (not null) in place of a
+// runtime copy, which also reaches host memory and other devices' memory.
+bool on_this_device(const void* p);
 hipError_t launch_sumsq(const float* g, long n, float* parts, hipStream_t s);
 // norm = sqrt(sum parts); coef = clip/norm if norm > clip else 1; norm_out (when
 // not null) takes the norm too

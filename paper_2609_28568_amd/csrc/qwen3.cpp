@@ -829,8 +829,13 @@ gpt2_status qwen3_adamw_step(qwen3_model* m, int64_t step, float* d_grad_norm_ou
   float* nc = m->wf(m->ws.normcoef);
   const int OPT = QWEN3_K_OPTIMIZER;
   TRY(m->run(OPT, 0.0, 4.0 * n, [&] { return launch_sumsq(grads, n, parts, m->stream); }));
-  TRY(m->run(OPT, 0.0, 4.0 * sumsq_parts(),
-             [&] { return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, d_grad_norm_out); }));
+  // the kernel writes the caller's copy of the norm too, where it can reach it
+  const bool direct = d_grad_norm_out && on_this_device(d_grad_norm_out);
+  TRY(m->run(OPT, 0.0, 4.0 * sumsq_parts(), [&] {
+    return launch_clip_coef(parts, sumsq_parts(), c.grad_clip, nc, m->stream, direct ? d_grad_norm_out : nullptr);
+  }));
+  if (d_grad_norm_out && !direct)
+    TRY(hipMemcpyAsync(d_grad_norm_out, nc, sizeof(float), hipMemcpyDeviceToDevice, m->stream));
   AdamArgs a{};
   a.p = static_cast<float*>(m->buf.lora_f32);
   a.g = grads;

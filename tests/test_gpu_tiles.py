@@ -85,9 +85,10 @@ def test_short_grid_attention(H, C, B, T):
         assert rel_l2(g[k], grads[k]) < REL_L2, (k, rel_l2(g[k], grads[k]))
 
 
-# The caller's buffers stand in for copies unless they are misaligned, overlap
-# or lie in the model's own memory: every form gives the same bits.
-@pytest.mark.parametrize("form", ["misaligned", "same_buffer", "own_memory"])
+# The caller's buffers stand in for copies unless they are misaligned, overlap,
+# lie in the model's own memory or (pinned) in the host's: every form gives the
+# same bits.
+@pytest.mark.parametrize("form", ["misaligned", "same_buffer", "own_memory", "pinned_host"])
 def test_block_buffer_forms(form):
     from paper_2609_28568_amd import binding
     B, T, C = 2, 75, 64
@@ -98,10 +99,12 @@ def test_block_buffer_forms(form):
     def passes(x_in, x_out, d_out, d_in, m):
         x_in.copy_(x)
         m.block_forward(0, x_in, x_out)
-        y = x_out.clone()
+        torch.cuda.synchronize()
+        y = x_out.cuda().clone()
         d_out.copy_(dy)
         m.block_backward(0, d_out, d_in)
-        return y, d_in.clone(), m.flat("grads")[64 * C + T * C:-2 * C].clone()
+        torch.cuda.synchronize()
+        return y, d_in.cuda().clone(), m.flat("grads")[64 * C + T * C:-2 * C].clone()
 
     m = binding.GPT2(binding.make_config(w, synth.OPTIM))
     m.set_params(p)
@@ -116,6 +119,8 @@ def test_block_buffer_forms(form):
     elif form == "same_buffer":
         a, b = torch.empty_like(x), torch.empty_like(x)
         bufs = [a, a, b, b]
+    elif form == "pinned_host":
+        bufs = [torch.empty(B * T, C, dtype=torch.bfloat16, pin_memory=True) for _ in range(4)]
     else:
         bufs = [m.activation("lnf").view(B * T, C), m.activation("att", 0).view(B * T, C),
                 m.activation("lnf").view(B * T, C), m.activation("residual", 0).view(B * T, C)]
@@ -129,6 +134,36 @@ def test_block_buffer_forms(form):
     m.close()
     for a, b in zip(got, ref):
         assert torch.equal(a, b)
+
+
+# The gradient norm written by the clip kernel and, for memory of the host, copied
+@pytest.mark.parametrize("model", ["gpt2", "qwen3"])
+def test_gradient_norm_to_pinned_host(model):
+    from paper_2609_28568_amd import binding, qwen3_binding as qb
+    norms = []
+    for pinned in (False, True):
+        out = torch.zeros(1, pin_memory=True) if pinned else torch.zeros(1, device="cuda")
+        if model == "gpt2":
+            w = workload("tiny")
+            m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+            m.set_params(synth.init_params(w))
+            ids, tgt = synth.token_batch(w)
+        else:
+            w = dict(synth.QWEN3_WORKLOADS["qwen3_tiny"])
+            m = qb.Qwen3(qb.make_config(w, synth.QWEN3_OPTIM))
+            base, lora = synth.init_qwen3(w, b_std=0.02)
+            m.set_base(base)
+            m.set_lora(lora)
+            ids, tgt = synth.token_batch(w)
+        m.forward(torch.from_numpy(ids), torch.from_numpy(tgt))
+        m.backward()
+        g = (m.flat("grads") if model == "gpt2" else m.flat("lora_grads")).double().norm().item()
+        m.adamw_step(0, out)
+        torch.cuda.synchronize()
+        norms.append(out.item())
+        m.close()
+        assert norms[-1] == pytest.approx(g, rel=1e-5)
+    assert norms[0] == norms[1]
 
 
 # Depths at the edges of the grouped weight-gradient plan at 768 wide (192
