@@ -302,7 +302,8 @@ WsLayout ws_layout(const Dims& d) {
     const GemmGroupedArgs gg = dw_groups(d, nl);
     pq = std::max(pq, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_QKV));
     pf = std::max(pf, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_FC));
-    if (nl == 1) pp = (size_t)p.splits * gemm_grouped_bias_parts(gg, G_FCPROJ);
+    // one block's MLP-down product, the only one, may be the split tail itself
+    if (nl == 1) pp = (size_t)(p.np > 0 ? p.tail_splits : p.splits) * gemm_grouped_bias_parts(gg, G_FCPROJ);
   }
   // products into the residual stream: the attention and MLP-down projections,
   // and the input gradients of MLP up, q|k|v and the head
@@ -840,8 +841,9 @@ gpt2_status grouped_weight_grads(Model* m, int l0, int nl, int acc, const bf16_t
   const long nq = (long)nl * 3 * C, nf = (long)nl * F;
   rs.add(q->bsum, plan.splits * gemm_grouped_bias_parts(g, G_QKV), nq, m->gf(K_QKVB) + l * 3 * C, nq);
   rs.add(fc->bsum, plan.splits * gemm_grouped_bias_parts(g, G_FC), nf, m->gf(K_FCB) + l * F, nf);
-  if (dres_out)
-    rs.add(fp->bsum, plan.splits * gemm_grouped_bias_parts(g, G_FCPROJ), (long)C, m->gf(K_FCPROJB) + l * C, (long)C);
+  if (dres_out)   // one layer: fp holds the whole product, in the chunks of the tail plan too
+    rs.add(fp->bsum, std::max(fp->splits, 1) * gemm_grouped_bias_parts(g, G_FCPROJ), (long)C, m->gf(K_FCPROJB) + l * C,
+           (long)C);
   double fl = 0.0, by = 0.0;
   for (int i = 0; i < g.ngroups; ++i) fl += 2.0 * g.grp[i].M * (double)g.grp[i].N * d.BT * g.grp[i].count;
   for (int i = 0; i < rs.count; ++i) by += 4.0 * rs.s[i].n * (rs.s[i].slices + 1 + acc);

@@ -54,6 +54,42 @@ def test_block_against_oracle(B, T):
         assert e < REL_L2, (k, e)
 
 
+# One block wide enough for a full round of 512 weight-gradient tiles: its
+# MLP-down product is the split tail of the grouped launch and carries its bias
+# sums in every chunk. 66 tokens (two chunks, one of two tokens) and 200; each
+# gradient written and added to
+@pytest.mark.parametrize("C,F", [(1024, 4096), (1024, 4032), (1536, 6144)])
+@pytest.mark.parametrize("B,T", [(2, 33), (1, 200)])
+def test_wide_block_against_oracle(C, F, B, T):
+    from paper_2609_28568_amd import binding
+    w = workload("tiny", n_layer=1, n_head=C // 64, d_model=C, d_ff=F, vocab=64, vocab_padded=64, max_seq_len=T, B=B,
+                 T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=71), seed=72)
+    x, dy = synth.block_inputs(w, seed=73)
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    tx, tdy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, dy))
+    out, dx = torch.empty_like(tx), torch.empty_like(tx)
+    print(f"block {C} x {F}, {B} x {T} tokens", flush=True)
+    m.block_forward(0, tx, out)
+    m.block_backward(0, tdy, dx)
+    g = m.to_dict("grads")
+    m.block_backward(0, tdy, dx, accumulate=True)
+    g2 = m.to_dict("grads")
+    out, dx = _np(out).reshape(B, T, C), _np(dx).reshape(B, T, C)
+    m.close()
+    ocfg = oracle_config(w)
+    y, cache = oracle.block_forward(x.reshape(B, T, C), p, 0, ocfg)
+    grads = oracle.zero_grads(p)
+    ref = oracle.block_backward(dy.reshape(B, T, C), cache, p, 0, ocfg, grads)
+    assert rel_l2(out, y) < REL_L2
+    assert rel_l2(dx, ref) < REL_L2
+    for k in ("ln1w", "ln1b", "qkvw", "qkvb", "attprojw", "attprojb", "ln2w", "ln2b", "fcw", "fcb", "fcprojw",
+              "fcprojb"):
+        assert rel_l2(g[k], grads[k]) < REL_L2, (k, rel_l2(g[k], grads[k]))
+        assert rel_l2(g2[k], 2.0 * grads[k]) < REL_L2, (k, rel_l2(g2[k], 2.0 * grads[k]))
+
+
 # The attention kernels for short grids (32 rows a workgroup, tiles dealt to its
 # waves) at every head size: sequences of two and more tiles with one-row tails,
 # up to and past the largest grids they take (256 and 512 workgroups)
