@@ -238,12 +238,11 @@ DwPlan dw_plan(const Dims& d, int nl) {
   DwPlan t;
   constexpr long ROUND = 512;
   const GemmGroupedArgs g = dw_groups(d, nl);
-  int bm = 192;
-  for (int i = 0; i < g.ngroups; ++i)
-    if (g.grp[i].M % 192 || g.grp[i].N % 192) bm = 128;
+  const GemmConfig c = gemm_grouped_config(g);
+  auto tiles = [&](const GemmGroup& p) { return (long)((p.M + c.bm - 1) / c.bm) * ((p.N + c.bn - 1) / c.bn); };
   long total = 0, elems = 0;
   for (int i = 0; i < g.ngroups; ++i) {
-    total += (long)((g.grp[i].M + bm - 1) / bm) * ((g.grp[i].N + bm - 1) / bm) * g.grp[i].count;
+    total += tiles(g.grp[i]) * g.grp[i].count;
     elems += (long)g.grp[i].M * g.grp[i].N * g.grp[i].count;
   }
   if (total < ROUND) {
@@ -253,7 +252,7 @@ DwPlan dw_plan(const Dims& d, int nl) {
     // 421 + 11 us unsplit, 282 + 32 split 2 ways, 275 + 98 5 ways, 280 + 149
     // 8 ways (325 as four launches split 8 or 16 ways each); on 999 tokens
     // unsplit is best.
-    const double t1 = bm == 192 ? 1.64 : 0.85, t2 = bm == 192 ? 2.2 : 1.2;
+    const double t1 = c.bm == 192 ? 1.64 : 0.85, t2 = c.bm == 192 ? 2.2 : 1.2;
     double best = 0.0;
     for (int want = 1; want <= 16 && want * total <= ROUND; ++want) {
       int chunk = 0;
@@ -269,7 +268,7 @@ DwPlan dw_plan(const Dims& d, int nl) {
     return t;
   }
   const GemmGroup& last = g.grp[G_FCPROJ];
-  const long tpp = (long)((last.M + bm - 1) / bm) * ((last.N + bm - 1) / bm);
+  const long tpp = tiles(last);
   const long tail = total % ROUND;
   if (tail == 0 || tail > ROUND / 2 || tail % tpp || tail / tpp > last.count) return t;
   int splits = (int)(ROUND / tail);

@@ -134,6 +134,8 @@ int gemm_grouped_bias_parts(const GemmGroupedArgs& g, int i);
 // epilogue (K does not enter for a transposed A).
 struct GemmConfig { int bm, bn, bk, ns; };
 GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi);
+// ... and that a grouped launch uses for all of its products
+GemmConfig gemm_grouped_config(const GemmGroupedArgs& g);
 // Plan a contraction split of K into about `want` pieces: writes the chunk
 // length (a multiple of the 64-wide k tile) and returns the split count.
 int gemm_split_plan(int K, int want, int* k_chunk);

@@ -30,7 +30,7 @@ int main() {
   for (int C = 64; C <= 2048; C += 64)
     for (int F : {64, C, 2 * C, 3 * C, 4 * C - 64, 4 * C, 4 * C + 64, 5376})
       for (int L : {1, 2, 4, 7, 12})
-        for (int T : {1, 65, 130, 999, 2048, 16384}) {
+        for (int T : {1, 65, 130, 999, 2048, 4096, 16384}) {
           gpt2_config c{};
           c.n_layer = L; c.n_head = C / 64; c.d_model = C; c.d_ff = F; c.vocab = 64; c.vocab_padded = 64;
           c.max_seq_len = T; c.B = 1; c.T = T; c.grad_accum = 1;

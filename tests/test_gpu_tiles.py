@@ -225,6 +225,52 @@ def test_grouped_weight_gradients_by_depth(L):
         assert rel_l2(g[k], ref[k]) < REL_L2, (k, rel_l2(g[k], ref[k]))
 
 
+# The 256 x 128 tiles of the grouped weight gradients (1024 of them or more,
+# 4096 tokens or more), ragged tokens: one 2048-wide block without a tail, and
+# three 1024-wide layers of which one MLP-down product is the split tail
+def test_grouped_256_row_tiles_of_one_block():
+    from paper_2609_28568_amd import binding
+    B, T, C = 16, 257, 2048
+    w = workload("tiny", n_layer=1, n_head=16, d_model=C, d_ff=4 * C, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=71), seed=72)
+    x, dy = synth.block_inputs(w, seed=73)
+    x3, dy3 = x.reshape(B, T, C), dy.reshape(B, T, C)
+    dy3[:-2] = 0.0   # the last two sequences carry gradient
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    tx, tdy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, dy))
+    print(f"block of {C}, {B} x {T} tokens", flush=True)
+    m.block_forward(0, tx)
+    m.block_backward(0, tdy)
+    g = m.to_dict("grads")
+    m.close()
+    ocfg = oracle_config(w)
+    cache = oracle.block_forward(x3[-2:], p, 0, ocfg)[1]
+    grads = oracle.zero_grads(p)
+    oracle.block_backward(dy3[-2:], cache, p, 0, ocfg, grads)
+    for k in ("qkvw", "qkvb", "attprojw", "attprojb", "fcw", "fcb", "fcprojw", "fcprojb"):
+        assert rel_l2(g[k], grads[k]) < REL_L2, (k, rel_l2(g[k], grads[k]))
+
+
+def test_grouped_256_row_tiles_of_three_layers():
+    from paper_2609_28568_amd import binding
+    B, T, C = 16, 257, 1024
+    w = workload("tiny", n_layer=3, n_head=16, d_model=C, d_ff=4 * C, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
+    p = synth.perturb_params(synth.init_params(w, seed=81), seed=82)
+    ids, tgt = synth.token_batch(w, seed=83)
+    m = binding.GPT2(binding.make_config(w, synth.OPTIM))
+    m.set_params(p)
+    print(f"3 layers of {C}, {B} x {T} tokens", flush=True)
+    m.forward(torch.from_numpy(ids), torch.from_numpy(tgt))
+    m.backward()
+    g = m.to_dict("grads")
+    m.close()
+    ocfg = oracle_config(w)
+    ref = oracle.backward(p, oracle.forward(p, ids, tgt, ocfg), ocfg)
+    for k in oracle.KINDS:
+        assert rel_l2(g[k], ref[k]) < REL_L2, (k, rel_l2(g[k], ref[k]))
+
+
 # The token-table scatter against a float64 sum: runs of one id that span
 # half-waves and workgroups, ids out of range skipped, few and many positions
 @pytest.mark.parametrize("n,distinct", [(1, 1), (255, 1), (257, 3), (1000, 500), (4096, 2), (4097, 4000), (5000, 37)])
