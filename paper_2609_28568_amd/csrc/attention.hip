@@ -775,14 +775,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv8_kernel(AttnArgs a) {
 // partial results are added up through LDS: four times the workgroups, a
 // quarter of the walk. They pay with a fourth of the operand reuse, their LDS
 // allows one workgroup per CU, and the partial results cost a round trip
-// through LDS. Forward and dQ take them for walks of three tiles or more while
-// every workgroup has a CU to itself; dK/dV, whose partial results replace more
-// work per tile, for two tiles or more and up to two workgroups per CU.
-// Measured against the kernels above (us): forward, 203 tokens, 12 heads of 64
-// (84 workgroups) 6.9 -> 5.0, but 6.9 -> 8.1 at 4 x 256 tokens (384) and 6.8 ->
-// 7.0 for two tiles (24); dQ 10.2 -> 11.3 at 384; dK/dV 12.7 -> 11.6 at 384,
-// 16.6 -> 14.4 at 3 x 333 tokens (396), 13.1 -> 10.8 for 2 x 96 tokens of head
-// size 128 (12).
+// through LDS. split_walk and dkdv_split say which grids take them.
 
 constexpr int SB = 32;   // rows owned by one workgroup
 
@@ -906,8 +899,9 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_split_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
     }
-    // a wave's first tile may hide every key from a query: its shift is still
-    // -inf, and its probabilities come out 0 with any finite one
+    // every tile of the walk has a key that the query sees (kv0 <= q0), but with
+    // infinite inputs all of a wave's may score -inf where another wave's do not:
+    // its probabilities come out 0 with any finite shift
     const float shift = m_run == -INFINITY ? 0.0f : m_run;
     float rsum = 0.0f;
 #pragma unroll
@@ -1202,16 +1196,45 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_split_kernel(AttnArgs a)
   }
 }
 
-// Whether `heads` heads with walks of up to `tiles` tiles take the kernels for
-// short grids: at least min_tiles, at most max_blocks workgroups of 32 rows
-bool split_walk(const AttnArgs& a, int heads, int tiles, int min_tiles, int max_blocks) {
-  return tiles >= min_tiles && (long)heads * ((a.T + SB - 1) / SB) <= max_blocks;
+// Forward and dQ take the kernels for short grids for walks of three tiles or
+// more while every workgroup of 32 rows has a CU to itself. Measured in place
+// of the kernels above (us; head size, sequence-heads x tokens, workgroups):
+// forward 64, 12 x 203 (84) 9.6 -> 7.7; 4 x 2048 (256) 33.6 -> 18.7; 128, 1 x
+// 8192 (256) 176 -> 74, 16 x 129 (80) 10.2 -> 10.0; but 64,
+// 48 x 256 (384) 6.9 -> 8.1, and two tiles (24) 6.8 -> 7.0 by the kernel alone.
+// dQ 64, 12 x 672 (252): backward 43.3 -> 35.7, but 10.2 -> 11.3 alone at 384.
+bool split_walk(const AttnArgs& a, int tiles) {
+  return tiles >= 3 && (long)a.B * a.H * ((a.T + SB - 1) / SB) <= 256;
+}
+
+// dK/dV, whose partial results replace more work per tile, takes them from two
+// tiles on. Past one workgroup per CU a second one waits its turn and its start
+// and combining are hidden by nothing but a longer walk, most of all at head
+// size 128, where a wave has one stage in LDS and waits for each load in full:
+// the walk that pays grows with the grid. Backward in us, kernels above ->
+// these (head size, sequence-heads x tokens, workgroups):
+//   64: 12 x 203 (84) 21.7 -> 15.8; 48 x 256 (384) 23.9 -> 22.8; 36 x 333 (396)
+//     dK/dV alone 16.6 -> 14.4; 25 x 640 (500) 40.4 -> 37.3; but 96 x 97 (384)
+//     17.9 -> 20.1, 51 x 300 (510) 27.0 -> 27.9;
+//   128: 64 x 128 (256) 24.3 -> 22.7; 20 x 512 (320) 43.5 -> 40.7; 11 x 1024
+//     (352) 68.7 -> 66.4; 8 x 2048 (512) 120.2 -> 108.6; but 64 x 129 (320) 26.5
+//     -> 30.5, 21 x 576 (378) 47.2 -> 51.1, 15 x 1056 (495) 74.2 -> 79.6, and
+//     with two query heads to a key head one tile each (64 tokens) 19.7 -> 20.2.
+template <int HD>
+bool dkdv_split(const AttnArgs& a, int tiles) {
+  const int Hkv = a.Hkv > 0 ? a.Hkv : a.H, walk = tiles * (a.H / Hkv);
+  const long wgs = (long)a.B * Hkv * ((a.T + SB - 1) / SB);
+  int least;
+  if (HD >= 128) least = wgs <= 256 ? (tiles > 1 ? 2 : 3) : wgs <= 320 ? 8 : wgs <= 384 ? 16 : 24;
+  else if (HD >= 64) least = wgs <= 256 ? 2 : wgs <= 384 ? 4 : 6;
+  else least = wgs <= 384 ? 2 : 3;
+  return wgs <= 512 && walk >= least;
 }
 
 template <int HD>
 hipError_t fwd_t(const AttnArgs& a, hipStream_t s) {
   const int BH = a.B * a.H, tiles = (a.T + TILE - 1) / TILE;
-  if (split_walk(a, BH, tiles, 3, 256))
+  if (split_walk(a, tiles))
     hipLaunchKernelGGL(attn_fwd_split_kernel<HD>, dim3((a.T + SB - 1) / SB * BH), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL(attn_fwd_kernel<HD>, dim3((a.T + BQ - 1) / BQ * BH), dim3(256), 0, s, a);
@@ -1223,13 +1246,13 @@ hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   // dQ first: it also computes D = rowsum(dO * O), which dK/dV reads
   const int nb = (a.T + BQ - 1) / BQ, ns = (a.T + SB - 1) / SB, Hkv = a.Hkv > 0 ? a.Hkv : a.H;
   const int tiles = (a.T + TILE - 1) / TILE;
-  if (split_walk(a, a.B * a.H, tiles, 3, 256))
+  if (split_walk(a, tiles))
     hipLaunchKernelGGL(attn_bwd_dq_split_kernel<HD>, dim3(ns * a.B * a.H), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL(attn_bwd_dq_kernel<HD>, dim3(nb * a.B * a.H), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (split_walk(a, a.B * Hkv, tiles * (a.H / Hkv), 2, 512))
+  if (dkdv_split<HD>(a, tiles))
     hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<HD>, dim3(ns * a.B * Hkv), dim3(256), 0, s, a);
   else if constexpr (HD == 128)
     hipLaunchKernelGGL(attn_bwd_dkdv8_kernel<HD>, dim3(nb * a.B * Hkv), dim3(512), 0, s, a);

@@ -92,9 +92,11 @@ def test_wide_block_against_oracle(C, F, B, T):
 
 # The attention kernels for short grids (32 rows a workgroup, tiles dealt to its
 # waves) at every head size: sequences of two and more tiles with one-row tails,
-# up to and past the largest grids they take (256 and 512 workgroups)
+# up to and past the largest grids they take (256 and 512 workgroups); one head
+# of 128 in 320 workgroups with walks that are too short (5 tiles) and just long
+# enough (8)
 @pytest.mark.parametrize("H,C", [(4, 64), (4, 128), (2, 128), (1, 128)])
-@pytest.mark.parametrize("B,T", [(1, 65), (2, 130), (1, 257), (3, 300), (32, 129)])
+@pytest.mark.parametrize("B,T", [(1, 65), (2, 130), (1, 257), (3, 300), (32, 129), (32, 300), (20, 512)])
 def test_short_grid_attention(H, C, B, T):
     from paper_2609_28568_amd import binding
     w = workload("tiny", n_layer=1, n_head=H, d_model=C, d_ff=4 * C, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
