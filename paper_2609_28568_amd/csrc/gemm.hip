@@ -196,7 +196,9 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   if constexpr (GROUPED) {
     // one tile of one product of one group: the 1-D grid runs through the
     // groups in order, each group's products in order, each product's tiles
-    // n fastest; every XCD takes a contiguous run of that order
+    // n fastest; every XCD takes a contiguous run of that order (the first
+    // tiles % 8 XCDs one more than the others). Dealt as they come, the tiles
+    // of a launch of 1963 (one 1600-wide block, 16,384 tokens) took 1594 us, 1273 so.
     int b = blockIdx.x;
     const int tot = gridDim.x, nfull = P.gg.nfull;
     if (nfull > 0) {
@@ -204,8 +206,9 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
       // of the last group's tiles
       const int f8 = nfull >> 3, x = b & 7, loc = b >> 3;
       b = loc < f8 ? x * f8 + loc : nfull + x * ((tot - nfull) >> 3) + (loc - f8);
-    } else if ((tot & 7) == 0) {
-      b = (b & 7) * (tot >> 3) + (b >> 3);
+    } else {
+      const int x = b & 7;
+      b = x * (tot >> 3) + min(x, tot & 7) + (b >> 3);
     }
     int k = 0;
 #pragma unroll

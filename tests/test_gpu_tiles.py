@@ -57,8 +57,8 @@ def test_block_against_oracle(B, T):
 # One block wide enough for a full round of 512 weight-gradient tiles: its
 # MLP-down product is the split tail of the grouped launch and carries its bias
 # sums in every chunk. 66 tokens (two chunks, one of two tokens) and 200; each
-# gradient written and added to
-@pytest.mark.parametrize("C,F", [(1024, 4096), (1024, 4032), (1536, 6144)])
+# gradient written and added to; at 320 x 1280 a launch of 93 tiles, no multiple of the 8 XCDs
+@pytest.mark.parametrize("C,F", [(1024, 4096), (1024, 4032), (1536, 6144), (320, 1280)])
 @pytest.mark.parametrize("B,T", [(2, 33), (1, 200)])
 def test_wide_block_against_oracle(C, F, B, T):
     from paper_2609_28568_amd import binding
