@@ -1012,46 +1012,26 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
   return launch_cfg<128, 128, 64, 2>(g, b_t, epi, s);
 }
 
-// One tile shape for every group: 192 x 192 when all of them are multiples of
-// 192 in both output dimensions (the weight-gradient tile of gemm_config);
-// 256 x 128 when all are multiples of that, give two rounds of such tiles and
-// contract over many tokens; else 128 x 128. (A product split over two groups
-// counts once.) Each group's operands (plus the up to 256 rows a tile may
-// address past their end) must stay within 32-bit byte offsets.
-// 256 x 128 against 128 x 128, launch and reductions in us: one 2048-wide block
-// (1536 large tiles) 1565 : 2111 on 16,384 tokens, 475 : 529 on 4096, 278 : 300
-// on 2048; 2048 x 5120 (1088) 397 : 397 on 4096, 231 : 224 on 2048; 12 layers of
-// 512 (1152) 399 : 438 on 4096, 136 : 129 on 512; 24 of 1024 (9216) 2371 : 2989
-// on 4096. Under two rounds its last round is too empty: one 1280-wide block
-// (600) 254 : 236, 12 layers of 256 (288) 198 : 189, both on 4096.
-constexpr long GROUPED_256_TILES = 1024;
-constexpr int GROUPED_256_TOKENS = 4096;
-
-GemmConfig gemm_grouped_config(const GemmGroupedArgs& gg) {
-  bool m192 = true, m256 = true;
-  long tiles256 = 0;
-  for (int i = 0; i < gg.ngroups; ++i) {
-    const GemmGroup& gr = gg.grp[i];
-    m192 = m192 && gr.M % 192 == 0 && gr.N % 192 == 0;
-    m256 = m256 && gr.M % 256 == 0 && gr.N % 128 == 0;
-    tiles256 += (long)(gr.M / 256) * (gr.N / 128) * gr.count;
-  }
-  if (m192) return {192, 192, 32, 2};
-  if (m256 && tiles256 >= GROUPED_256_TILES && gg.K >= GROUPED_256_TOKENS) return {256, 128, 32, 2};
-  return {128, 128, 32, 2};
+static GemmConfig grouped_config(const GemmGroupedArgs& gg) {
+  return gg.bm ? GemmConfig{gg.bm, gg.bn, 32, 2} : GemmConfig{128, 128, 32, 2};
 }
 
 int gemm_grouped_bias_parts(const GemmGroupedArgs& gg, int i) {
-  const int bn = gemm_grouped_config(gg).bn;
+  const int bn = grouped_config(gg).bn;
   return ((gg.grp[i].N + bn - 1) / bn) * 2;
 }
 
+// Each group's operands (plus the up to 256 rows a tile may address past their
+// end) must stay within 32-bit byte offsets.
 hipError_t launch_gemm_grouped(const GemmGroupedArgs& gg, hipStream_t s) {
   if (gg.ngroups < 1 || gg.ngroups > GEMM_GROUPS || gg.K < 1) return hipErrorInvalidValue;
   long tiles = 0, last = 0;
-  const GemmConfig c = gemm_grouped_config(gg);
+  const GemmConfig c = grouped_config(gg);
+  const bool c192 = c.bm == 192 && c.bn == 192, c128 = (c.bm == 256 || c.bm == 128) && c.bn == 128;
+  if (!c192 && !c128) return hipErrorInvalidValue;
   for (int i = 0; i < gg.ngroups; ++i) {
     const GemmGroup& gr = gg.grp[i];
+    if (c192 && (gr.M % 192 || gr.N % 192)) return hipErrorInvalidValue;
     if (!gr.A || !gr.B || !gr.C || gr.M < 1 || gr.N < 1 || gr.count < 1 || gr.N % 4) return hipErrorInvalidValue;
     if (gr.splits > 1) {
       // chunks of whole 64-token steps covering K; slices of plain sums
@@ -1068,6 +1048,6 @@ hipError_t launch_gemm_grouped(const GemmGroupedArgs& gg, hipStream_t s) {
       return hipErrorInvalidValue;
   }
   if (gg.nfull != 0 && (gg.nfull < 0 || gg.nfull % 8 || gg.nfull != tiles - last || last % 8)) return hipErrorInvalidValue;
-  if (c.bm == 192) return launch_grouped_t<192, 192, 32>(gg, s);
+  if (c192) return launch_grouped_t<192, 192, 32>(gg, s);
   return c.bm == 256 ? launch_grouped_t<256, 128, 32>(gg, s) : launch_grouped_t<128, 128, 32>(gg, s);
 }

@@ -221,7 +221,7 @@ GemmGroupedArgs dw_groups(const Dims& d, int nl) {
 }
 
 // How the grouped weight-gradient launch over nl layers fills the chip, which
-// runs 512 tiles at a time (two workgroups on each of the 256 CUs).
+// runs a round of 512 tiles at a time (two workgroups on each of the 256 CUs).
 // Many layers: when the last round would be at most half full and consists
 // of whole MLP-down products (the last group), np of those split their token
 // contraction into tail_splits chunks, so that the final round is full of
@@ -229,58 +229,96 @@ GemmGroupedArgs dw_groups(const Dims& d, int nl) {
 // less than a round in all: every product splits into `splits` chunks. Either
 // way the split products' fp32 slices are reduced afterwards.
 struct DwPlan {
+  int bm = 128, bn = 128;
   int splits = 1, chunk = 0;
   int np = 0, tail_splits = 1, tail_chunk = 0;
   long nfull = 0;
 };
 
-DwPlan dw_plan(const Dims& d, int nl) {
-  DwPlan t;
+// A tile and the time of 64 tokens, in us, with one on each CU and with two.
+struct DwTile {
+  int bm, bn;
+  double t1, t2;
+};
+
+// The plan with one tile shape, and its estimated time in us: rounds of tiles,
+// and for a split into few chunks of at least 512 tokens the slices written and
+// read back at about 3 TB/s (splits of up to four rounds in all).
+// One 768-wide block on 16,384 tokens (192 tiles of 192 x 192), launch +
+// reduction: 421 + 11 us unsplit, 282 + 32 split 2 ways, 275 + 98 5 ways, 280 +
+// 149 8 ways (325 as four launches split 8 or 16 ways each); on 999 tokens
+// unsplit is best.
+double dw_plan_with(const Dims& d, int nl, const DwTile& c, DwPlan* out) {
   constexpr long ROUND = 512;
   const GemmGroupedArgs g = dw_groups(d, nl);
-  const GemmConfig c = gemm_grouped_config(g);
   auto tiles = [&](const GemmGroup& p) { return (long)((p.M + c.bm - 1) / c.bm) * ((p.N + c.bn - 1) / c.bn); };
   long total = 0, elems = 0;
   for (int i = 0; i < g.ngroups; ++i) {
     total += tiles(g.grp[i]) * g.grp[i].count;
     elems += (long)g.grp[i].M * g.grp[i].N * g.grp[i].count;
   }
+  auto rounds_us = [&](long n, long tokens) {
+    const long r = n % ROUND;
+    return (tokens + 63) / 64 * (n / ROUND * c.t2 + (r == 0 ? 0.0 : r <= ROUND / 2 ? c.t1 : c.t2));
+  };
+  DwPlan t;
+  t.bm = c.bm;
+  t.bn = c.bn;
+  double best = rounds_us(total, d.BT);
   if (total < ROUND) {
-    // Time per 64 tokens with one tile per CU and with two, and the slices
-    // written and read back at about 3 TB/s, in us; no split past one round.
-    // One 768-wide block on 16,384 tokens (192 tiles), launch + reduction:
-    // 421 + 11 us unsplit, 282 + 32 split 2 ways, 275 + 98 5 ways, 280 + 149
-    // 8 ways (325 as four launches split 8 or 16 ways each); on 999 tokens
-    // unsplit is best.
-    const double t1 = c.bm == 192 ? 1.64 : 0.85, t2 = c.bm == 192 ? 2.2 : 1.2;
-    double best = 0.0;
-    for (int want = 1; want <= 16 && want * total <= ROUND; ++want) {
+    for (int want = 2; want <= 16 && want * total <= 4 * ROUND; ++want) {
       int chunk = 0;
       const int s = gemm_split_plan((int)d.BT, want, &chunk);
-      if (s != want || (s > 1 && chunk < 512)) continue;
-      const double us = chunk / 64 * (total * s <= ROUND / 2 ? t1 : t2) + (s > 1 ? 8.0 * s * elems / 3e6 : 0.0);
-      if (best == 0.0 || us < 0.95 * best) {
+      if (s != want || chunk < 512) continue;
+      const double us = rounds_us(total * s, chunk) + 8.0 * s * elems / 3e6;
+      if (us < 0.95 * best) {
         best = us;
         t.splits = s;
         t.chunk = chunk;
       }
     }
-    return t;
+    *out = t;
+    return best;
   }
   const GemmGroup& last = g.grp[G_FCPROJ];
   const long tpp = tiles(last);
   const long tail = total % ROUND;
-  if (tail == 0 || tail > ROUND / 2 || tail % tpp || tail / tpp > last.count) return t;
-  int splits = (int)(ROUND / tail);
-  if (splits > 4) splits = 4;
-  int chunk = 0;
-  splits = gemm_split_plan((int)d.BT, splits, &chunk);
-  if (splits < 2 || ((tail * splits) % 8) != 0) return t;
-  t.np = (int)(tail / tpp);
-  t.tail_splits = splits;
-  t.tail_chunk = chunk;
-  t.nfull = total - tail;
-  return t;
+  if (tail != 0 && tail <= ROUND / 2 && tail % tpp == 0 && tail / tpp <= last.count) {
+    int chunk = 0;
+    const int splits = gemm_split_plan((int)d.BT, std::min((int)(ROUND / tail), 4), &chunk);
+    if (splits >= 2 && (tail * splits) % 8 == 0) {
+      t.np = (int)(tail / tpp);
+      t.tail_splits = splits;
+      t.tail_chunk = chunk;
+      t.nfull = total - tail;
+      best = rounds_us(total - tail, d.BT) + rounds_us(tail * splits, chunk);
+    }
+  }
+  *out = t;
+  return best;
+}
+
+// One tile shape for every product: 192 x 192 when all are whole numbers of it,
+// else 256 x 128 where it promises to be faster than 128 x 128 over 4096 tokens
+// or more (below, prologues and epilogues count: 512 tokens, 12 layers of 512,
+// 136 us against 129; 2048 tokens, 2048 x 5120, 231 against 224). The times of
+// the 128-row tiles are those of launches of several rounds: 2048 wide on 16,384
+// tokens, 3 rounds of 256 x 128 in 1565 us, 6 of 128 x 128 in 2111.
+// One block's backward on 16,384 tokens, us (four launches, each with a tile and
+// split of its own -> one launch with 128 x 128 tiles unsplit -> now):
+//   704 x 1408 638 -> 709 -> 563, 768 x 2048 673 -> 734 -> 622, 640 x 2560 695 ->
+//   748 -> 632, 1024 x 64 721 -> 752 -> 630, 896 x 896 735 -> 764 -> 633, 1792 x
+//   4736 2709 -> 2788 -> 2449, 1920 x 5120 3014 -> 3193 -> 3049, 2048 x 5440 3348
+//   -> 3521 -> 3275.
+DwPlan dw_plan(const Dims& d, int nl) {
+  DwPlan a, b;
+  if (d.C % 192 == 0 && d.F % 192 == 0) {
+    dw_plan_with(d, nl, {192, 192, 1.64, 2.2}, &a);
+    return a;
+  }
+  const double us = dw_plan_with(d, nl, {128, 128, 0.85, 1.37}, &a);
+  if (d.BT < 4096) return a;
+  return dw_plan_with(d, nl, {256, 128, 1.4, 2.25}, &b) < 0.97 * us ? b : a;
 }
 
 WsLayout ws_layout(const Dims& d) {
@@ -298,7 +336,9 @@ WsLayout ws_layout(const Dims& d) {
     const size_t per_layer = 4 * C * C + 2 * C * F;
     if (p.splits > 1) sk = std::max(sk, (size_t)p.splits * nl * per_layer);
     if (p.np > 0) sk = std::max(sk, (size_t)p.tail_splits * p.np * C * F);
-    const GemmGroupedArgs gg = dw_groups(d, nl);
+    GemmGroupedArgs gg = dw_groups(d, nl);
+    gg.bm = p.bm;
+    gg.bn = p.bn;
     pq = std::max(pq, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_QKV));
     pf = std::max(pf, (size_t)nl * p.splits * gemm_grouped_bias_parts(gg, G_FC));
     // one block's MLP-down product, the only one, may be the split tail itself
@@ -806,6 +846,8 @@ gpt2_status grouped_weight_grads(Model* m, int l0, int nl, int acc, const bf16_t
 
   ReduceSegs rs{};
   const DwPlan plan = dw_plan(d, nl);
+  g.bm = plan.bm;
+  g.bn = plan.bn;
   if (plan.splits > 1) {
     // every product in slices, group after group in the split-K buffer
     float* part = m->wsf(w.splitk);

@@ -123,10 +123,13 @@ struct GemmGroupedArgs {
   int K;
   int accumulate;
   int nfull;   // tiles before the last group when its tiles fill the final round (0: no such plan)
+  // tile of every product: 192 x 192 (all of them whole numbers of it),
+  // 256 x 128 or 128 x 128 (0 x 0 too)
+  int bm, bn;
 };
 hipError_t launch_gemm_grouped(const GemmGroupedArgs& g, hipStream_t s);
 // Partial rows (slots) a grouped launch writes for group i's bias sums, per
-// contraction chunk; it depends only on the groups' M and N
+// contraction chunk; it depends only on the group's N and the tile
 int gemm_grouped_bias_parts(const GemmGroupedArgs& g, int i);
 
 // Block tile (bm x bn, contraction depth bk per stage, ns stages) the GEMM
@@ -134,8 +137,6 @@ int gemm_grouped_bias_parts(const GemmGroupedArgs& g, int i);
 // epilogue (K does not enter for a transposed A).
 struct GemmConfig { int bm, bn, bk, ns; };
 GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi);
-// ... and that a grouped launch uses for all of its products
-GemmConfig gemm_grouped_config(const GemmGroupedArgs& g);
 // Plan a contraction split of K into about `want` pieces: writes the chunk
 // length (a multiple of the 64-wide k tile) and returns the split count.
 int gemm_split_plan(int K, int want, int* k_chunk);

@@ -227,13 +227,15 @@ def test_grouped_weight_gradients_by_depth(L):
         assert rel_l2(g[k], ref[k]) < REL_L2, (k, rel_l2(g[k], ref[k]))
 
 
-# The 256 x 128 tiles of the grouped weight gradients (1024 of them or more,
-# 4096 tokens or more), ragged tokens: one 2048-wide block without a tail, and
-# three 1024-wide layers of which one MLP-down product is the split tail
-def test_grouped_256_row_tiles_of_one_block():
+# The 256 x 128 tiles of the grouped weight gradients (4096 tokens or more),
+# ragged tokens: one 2048-wide block without a tail; 704 x 1408 (three chunks of
+# the tokens, tiles that reach past the rows); 1024 x 64 (fewer rows than a
+# tile); three 1024-wide layers of which one MLP-down product is the split tail
+@pytest.mark.parametrize("H,C,F", [(16, 2048, 8192), (11, 704, 1408), (16, 1024, 64)])
+def test_grouped_256_row_tiles_of_one_block(H, C, F):
     from paper_2609_28568_amd import binding
-    B, T, C = 16, 257, 2048
-    w = workload("tiny", n_layer=1, n_head=16, d_model=C, d_ff=4 * C, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
+    B, T = 16, 257
+    w = workload("tiny", n_layer=1, n_head=H, d_model=C, d_ff=F, vocab=64, vocab_padded=64, max_seq_len=T, B=B, T=T)
     p = synth.perturb_params(synth.init_params(w, seed=71), seed=72)
     x, dy = synth.block_inputs(w, seed=73)
     x3, dy3 = x.reshape(B, T, C), dy.reshape(B, T, C)
@@ -241,7 +243,7 @@ def test_grouped_256_row_tiles_of_one_block():
     m = binding.GPT2(binding.make_config(w, synth.OPTIM))
     m.set_params(p)
     tx, tdy = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, dy))
-    print(f"block of {C}, {B} x {T} tokens", flush=True)
+    print(f"block of {C} x {F}, {B} x {T} tokens", flush=True)
     m.block_forward(0, tx)
     m.block_backward(0, tdy)
     g = m.to_dict("grads")
