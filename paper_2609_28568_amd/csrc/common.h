@@ -102,15 +102,6 @@ DEV float wave_sum(float v) {
   const float2 r = rows16(v);
   return group16_sum(r.x + r.y);
 }
-DEV float wave_max(float v) {
-  v = max32(v);
-  const float2 r = rows16(v);
-  v = fmaxf(r.x, r.y);
-  v = fmaxf(v, row_ror<8>(v));
-  v = fmaxf(v, row_ror<4>(v));
-  v = fmaxf(v, row_ror<2>(v));
-  return fmaxf(v, row_ror<1>(v));
-}
 
 // Softmax statistics (max m, sum s of exp(x - m)) of two sets merged into (m, s)
 DEV void merge_ms(float& m, float& s, float m2, float s2) {
@@ -156,11 +147,6 @@ DEV float4 sum_slices(const float* p, int n, size_t stride) {
   }
   return a;
 }
-
-// Transpose two 4-byte words holding (r0c0,r0c1) and (r1c0,r1c1) into
-// (r0c0,r1c0) and (r0c1,r1c1).
-DEV uint32_t lo_pair(uint32_t r0, uint32_t r1) { return (r0 & 0xffffu) | (r1 << 16); }
-DEV uint32_t hi_pair(uint32_t r0, uint32_t r1) { return (r0 >> 16) | (r1 & 0xffff0000u); }
 
 // GELU, tanh form: 0.5 u (1 + tanh(y)) with y = sqrt(2/pi) (u + 0.044715 u^3).
 // Evaluated as u * sigmoid(2y) (the same function, since 0.5 (1 + tanh(y)) =

@@ -98,19 +98,6 @@ DEV float block_sum(float v, float* sh) {
   return t;
 }
 
-template <int NT>
-DEV float block_max(float v, float* sh) {
-  v = wave_max(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) sh[w] = v;
-  __syncthreads();
-  float t = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) t = fmaxf(t, sh[i]);
-  return t;
-}
-
 // one block of 1024 threads, each with up to 16 loads in flight at a time
 __global__ __launch_bounds__(1024) void mean_kernel(const float* __restrict__ x, int n, float inv,
                                                     float* __restrict__ out, uint32_t* __restrict__ flag) {

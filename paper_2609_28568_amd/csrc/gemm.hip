@@ -49,7 +49,6 @@ typedef __attribute__((address_space(3))) float lds_f32_t;
 // the others do not reserve registers for those reads.
 constexpr int EPI_BF16_RES = 4;
 constexpr int EPI_F32_ACC = 5;
-constexpr int EPI_BF16_SCALE = 6;   // EPI_BF16 with the accumulator scaled by alpha
 
 DEV int bitrev3(int x) { return ((x & 1) << 2) | (x & 2) | ((x >> 2) & 1); }
 
@@ -289,7 +288,9 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   }
 
   // B column offset of this tile's output row block
-  const int bcol = g.b_step * ((g.b_bound[0] > 0 && m0 >= g.b_bound[0]) + (g.b_bound[1] > 0 && m0 >= g.b_bound[1]));
+  int bcol = 0;
+  if constexpr (GROUPED)
+    bcol = g.b_step * ((g.b_bound[0] > 0 && m0 >= g.b_bound[0]) + (g.b_bound[1] > 0 && m0 >= g.b_bound[1]));
 
   auto stage = [&](int kt) { return smem + (kt % NS) * STAGE; };
   auto issue = [&](int kti) {
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   // k-tiles, and the two waves reading the same A fragments alternate
   // k-steps, so each wave adds up 1/(2 ntn) of its fragments. Lane l holds
   // row l%32 of each 32-row fragment at k-slots 8*(l/32)..+7.
-  constexpr bool BSUM = A_T && (EPI == EPI_F32 || EPI == EPI_F32_ACC);
+  constexpr bool BSUM = GROUPED;
   const bool bsum_on = BSUM && g.bsum != nullptr;
   const int tn = n0 / BN;
   float bs[BSUM ? TM : 1];
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
       for (int i = 0; i < TM; ++i) {
         const float v = sum32(bs[i]);
         const int m = m0 + wm * WTM + 32 * i + (lane & 31);
-        if (lane < 32 && m < g.M) g.bsum[slot * (g.bsum_ld ? g.bsum_ld : g.M) + m] = v;
+        if (lane < 32 && m < g.M) g.bsum[slot * g.bsum_ld + m] = v;
       }
     }
   }
@@ -514,8 +515,7 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
   bf16_t* Cb = static_cast<bf16_t*>(g.C);
   const int ncol0 = n0 + wn * WTN;
   float4 bias4[NB];
-  if constexpr (EPI == EPI_BF16 || EPI == EPI_BF16_RES || EPI == EPI_GELU || EPI == EPI_BF16_SCALE ||
-                EPI == EPI_CE_GRAD) {
+  if constexpr (EPI == EPI_BF16 || EPI == EPI_BF16_RES || EPI == EPI_GELU || EPI == EPI_CE_GRAD) {
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int n = ncol0 + ((lane + 64 * q) % CPR) * 4;
@@ -663,9 +663,6 @@ __global__ __launch_bounds__(64 * gemm_waves(BM, BK), 2) void gemm_kernel(KParam
             v2 *= gelu_tanh_grad(lo_f(rd[cc].y)); v3 *= gelu_tanh_grad(hi_f(rd[cc].y));
             *reinterpret_cast<uint2*>(Cbi + off) = make_uint2(pack2(v0, v1), pack2(v2, v3));
           } else {
-            if constexpr (EPI == EPI_BF16_SCALE) {
-              v0 *= g.alpha; v1 *= g.alpha; v2 *= g.alpha; v3 *= g.alpha;
-            }
             const float4 bb = bias4[cc % NB];
             v0 += bb.x; v1 += bb.y; v2 += bb.z; v3 += bb.w;
             if constexpr (EPI == EPI_GELU) {
@@ -728,18 +725,14 @@ hipError_t launch_grouped_t(const GemmGroupedArgs& gg, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Non-transposed A with an optional second contraction segment and output scale.
+// Non-transposed A with an optional second contraction segment.
 template <int BM, int BN, int BK, int NS, bool B_T>
 hipError_t launch_bf16(const GemmArgs& g, hipStream_t s) {
-  const bool scale = g.alpha != 0.0f && g.alpha != 1.0f;
-  if (g.K2 > 0) {
-    if (scale) return hipErrorInvalidValue;
+  if (g.K2 > 0)
     return g.residual ? launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_RES, true>(g, s)
                       : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16, true>(g, s);
-  }
-  if (g.residual) return scale ? hipErrorInvalidValue : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_RES>(g, s);
-  return scale ? launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_SCALE>(g, s)
-               : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16>(g, s);
+  return g.residual ? launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16_RES>(g, s)
+                    : launch_t<BM, BN, BK, NS, false, B_T, EPI_BF16>(g, s);
 }
 
 // Every product with A not transposed.
@@ -925,11 +918,6 @@ int gemm_ce_parts(int M, int N, int K) {
   return ((N + c.bn - 1) / c.bn) * 2;
 }
 
-int gemm_bias_parts(int M, int N, int splits) {
-  const GemmConfig c = gemm_config(M, N, 0, 1, 1, EPI_F32);
-  return (splits < 1 ? 1 : splits) * ((N + c.bn - 1) / c.bn) * 2;
-}
-
 int gemm_split_plan(int K, int want, int* k_chunk) {
   if (want < 1) want = 1;
   int kc = (K + want - 1) / want;
@@ -972,12 +960,6 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
         (size_t)((b_t ? g.K2 : g.N) + 256) * g.ldb2 * 2 >= (1ull << 32))
       return hipErrorInvalidValue;
   }
-  if (g.b_step != 0) {
-    // row blocks must not straddle a bound; B must be read transposed ([K][N])
-    if (!b_t || g.b_step < 0) return hipErrorInvalidValue;
-    for (int i = 0; i < 2; ++i)
-      if (g.b_bound[i] < 0 || g.b_bound[i] % 128) return hipErrorInvalidValue;
-  }
   // a tile's output columns must lie within one block of the second segment
   int mult = 0;
   if (g.K2 > 0) {
@@ -987,8 +969,6 @@ hipError_t launch_gemm(const GemmArgs& g0, int a_t, int b_t, int epi, hipStream_
     }
   }
   const GemmConfig c = gemm_config_for(g.M, g.N, g.splits > 1 ? g.k_chunk : Kt, a_t, b_t, epi, mult, g.splits);
-  // an output row block must not straddle a B column-offset bound
-  if (g.b_step != 0 && ((g.b_bound[0] % c.bm) || (g.b_bound[1] % c.bm))) return hipErrorInvalidValue;
   // m fastest when A is the smaller operand and stays in an XCD's 4 MB L2
   // while the column panels of B stream past it once (203 x 50304 x 768:
   // 37 -> 30 us, 1024 x 50304 x 768: 118 -> 84 us with 128 x 192 tiles)

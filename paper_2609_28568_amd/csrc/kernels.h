@@ -44,30 +44,17 @@ struct GemmArgs {
   int splits;              // split of the contraction over grid.z (EPI_F32 only)
   long split_stride;       // elements between split output slices
   int k_chunk;             // contraction length per split (from gemm_split_plan)
-  // EPI_F32 with A read transposed (a weight gradient dY^T X): when set, the
-  // GEMM also writes partial sums of A's rows over the contraction (the bias
-  // gradient, sum over tokens of dY) into [gemm_bias_parts(M, N, splits)][M];
-  // summing those rows gives the bias gradient
-  float* bsum;
-  // EPI_BF16 without residual: the accumulator is multiplied by alpha before
-  // the bias (0 or 1: no scaling)
-  float alpha;
   // Optional second contraction segment (K2 > 0; A not transposed, K and K2
-  // multiples of 64; a split runs over both segments as one contraction): C += A2 B2 over K2 more indices, A2 [M][lda2]
-  // and B2 in B's orientation (row stride ldb2). Output columns n >=
-  // a2_bound[i] (for each non-zero bound, multiples of 128) read A2 from K2
-  // columns further right per bound passed, so column blocks of the output
-  // can contract with different column blocks of A2.
+  // multiples of 64; a split runs over both segments as one contraction):
+  // C += A2 B2 over K2 more indices, A2 [M][lda2] and B2 in B's orientation
+  // (row stride ldb2). Output columns n >= a2_bound[i] (for each non-zero
+  // bound, multiples of 128) read A2 from K2 columns further right per bound
+  // passed, so column blocks of the output can contract with different column
+  // blocks of A2.
   const bf16_t* A2;
   const bf16_t* B2;
   int K2, lda2, ldb2;
   int a2_bound[2];
-  // Output rows m >= b_bound[i] (for each non-zero bound, multiples of 128)
-  // read B from b_step columns further right per bound passed, so row blocks
-  // of the output can contract with different column blocks of B.
-  int b_bound[2], b_step;
-  // row stride of the bsum partial rows (0: M)
-  int bsum_ld;
   // Softmax cross-entropy over the output rows (the tied LM head, rows =
   // token positions, columns = vocabulary entries; only columns < ce_V count,
   // targets outside [0, ce_V) read column 0):
@@ -86,6 +73,10 @@ struct GemmArgs {
   // order of the output tiles: 0 the column tiles of a row panel one after
   // the other, 1 the row tiles of a column panel
   int m_fast;
+  // Grouped launches only, set by the kernel from the product's group: the bias
+  // partial rows and their stride, and the column blocks of B
+  float* bsum;
+  int bsum_ld, b_bound[2], b_step;
 };
 
 // Grouped weight gradients: launch_gemm_grouped runs, in one launch, every
@@ -95,12 +86,13 @@ struct GemmArgs {
 // operands and outputs sit at fixed element strides from the group's first
 // one (C_p row stride N). With bsum, product p also writes the partial sums of
 // A_p's rows (its bias gradient) into rows [slot][p][M] of bsum, slot <
-// gemm_bias_parts(M, N, 1); summing over slots gives the bias gradients of
-// the group's products, stored one after another.
+// gemm_grouped_bias_parts; summing over slots gives the bias gradients of the
+// group's products, stored one after another.
 // A group with splits > 1 divides its contraction into `splits` chunks of
 // k_chunk tokens (a multiple of 64): product p's chunk z writes the plain sum
 // (never accumulating) to C_p + z * split_stride, for the caller to reduce,
-// and its bsum rows to slots z * gemm_bias_parts(M, N, 1) on. With nfull > 0 the groups before the last
+// and its bsum rows to slots z * gemm_grouped_bias_parts on: the caller's bsum
+// holds `splits` times as many rows. With nfull > 0 the groups before the last
 // one hold nfull tiles and the last one the rest (both multiples of 8), and
 // each of the 8 XCDs takes an equal share of both (the last group's tiles
 // filling the final round).
@@ -115,7 +107,10 @@ struct GemmGroup {
   int count;
   int splits, k_chunk;   // contraction split (splits <= 1: none)
   long split_stride;
-  int b_bound[2], b_step;   // as in GemmArgs (128 x 128 tiles only)
+  // Output rows m >= b_bound[i] (for each non-zero bound, multiples of the
+  // tile's rows) read B from b_step columns further right per bound passed, so
+  // row blocks of the output can contract with different column blocks of B.
+  int b_bound[2], b_step;
 };
 struct GemmGroupedArgs {
   GemmGroup grp[GEMM_GROUPS];
@@ -148,8 +143,6 @@ struct Slices {
   const float* p;
   int n;
 };
-// Partial rows a weight-gradient GEMM writes into GemmArgs::bsum
-int gemm_bias_parts(int M, int N, int splits);
 hipError_t launch_gemm(const GemmArgs& g, int a_t, int b_t, int epi, hipStream_t s);
 // float2 partials per row that EPI_CE_STATS writes for an M x N product over K
 int gemm_ce_parts(int M, int N, int K);
@@ -323,8 +316,6 @@ hipError_t launch_lora_rows(const LoraRowArgs& a, hipStream_t s);
 // elements, out a multiple of 64): the adapter B matrices with the
 // contraction index contiguous, for launch_lora_rows.
 hipError_t launch_lora_bt(const bf16_t* B, bf16_t* Bt, int L, int out, int rp, hipStream_t s);
-// x[r][c] *= sc for r < rows, c < cols (row stride ld)
-hipError_t launch_scale_bf16(bf16_t* x, long rows, int cols, int ld, float sc, hipStream_t s);
 
 // fp32 -> bf16 copy of n elements (n % 4 == 0)
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, long n, hipStream_t s);

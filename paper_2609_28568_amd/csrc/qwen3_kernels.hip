@@ -322,16 +322,6 @@ __global__ void swiglu_bwd_kernel(const bf16_t* __restrict__ dm, const bf16_t* _
   *reinterpret_cast<uint2*>(dgu + (size_t)r * 2 * F + F + c) = make_uint2(pack2(du[0], du[1]), pack2(du[2], du[3]));
 }
 
-// x[r][c] *= s for rows x cols (row stride ld), bf16 in place
-__global__ void scale_bf16_kernel(bf16_t* __restrict__ x, long rows, int cols, int ld, float s) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * cols) return;
-  const long r = i / cols;
-  const int c = (int)(i % cols);
-  bf16_t* p = x + (size_t)r * ld + c;
-  *p = f2bf(bf2f(*p) * s);
-}
-
 inline unsigned nblocks(long n, int nt) { return (unsigned)((n + nt - 1) / nt); }
 
 }  // namespace
@@ -431,10 +421,5 @@ hipError_t launch_swiglu_fwd(const bf16_t* gu, bf16_t* m, long rows, int F, hipS
 hipError_t launch_swiglu_bwd(const bf16_t* dm, const bf16_t* gu, bf16_t* dgu, long rows, int F, hipStream_t s) {
   if (F % 4) return hipErrorInvalidValue;
   hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(nblocks(rows * F / 4, 256)), dim3(256), 0, s, dm, gu, dgu, rows, F);
-  return hipGetLastError();
-}
-
-hipError_t launch_scale_bf16(bf16_t* x, long rows, int cols, int ld, float sc, hipStream_t s) {
-  hipLaunchKernelGGL(scale_bf16_kernel, dim3(nblocks(rows * cols, 256)), dim3(256), 0, s, x, rows, cols, ld, sc);
   return hipGetLastError();
 }
