@@ -256,11 +256,15 @@ gpt2_status gpt2_activation_info(const gpt2_model* m, int32_t which,
 
 /* One block of section "Model" (pre-LayerNorm attention and MLP with their
  * residual connections) in isolation, used to measure and check one block:
- * d_x_in bf16 [BT,C] is copied into the residual slot of `layer`, the block
- * runs, and its output is copied to d_x_out (bf16 [BT,C], optional). The
+ * d_x_in bf16 [BT,C] goes to the residual slot of `layer`, the block runs, and
+ * its output goes to the next slot and to d_x_out (bf16 [BT,C], optional). The
  * backward takes the upstream gradient d_dx_out (bf16 [BT,C]), writes the
  * layer's parameter gradients (overwrite or accumulate) and the gradient
- * with respect to the block input to d_dx_in (bf16 [BT,C], optional). */
+ * with respect to the block input to d_dx_in (bf16 [BT,C], optional). The
+ * kernels read and write the caller's buffers themselves where they are this
+ * device's memory, aligned (8 bytes; d_dx_out 16), outside the model's own
+ * memory and, for d_dx_out, not overlapping d_dx_in; others are copied.
+ * d_dx_out is read until the call's last kernel has run. */
 gpt2_status gpt2_block_forward(gpt2_model* m, int32_t layer,
                                const void* d_x_in, void* d_x_out);
 gpt2_status gpt2_block_backward(gpt2_model* m, int32_t layer,
@@ -283,7 +287,9 @@ gpt2_status gpt2_embedding_backward(gpt2_model* m, const int32_t* d_ids,
  *   GPT2_FUSION_RESIDUAL_NORM, how a residual connection meets the pre-norm
  *   after it (the paper's fused residual-and-pre-norm lever):
  *     0 (default) the projection GEMM's epilogue adds the residual and the
- *       LayerNorm reads the sum;
+ *       LayerNorm reads the sum; with few tokens (about 500 at 768 wide) the
+ *       projection's contraction is split instead, and the LayerNorm adds up
+ *       its fp32 slices, the bias and the residual;
  *     1 the projection writes its branch, one kernel forms the rounded sum
  *       and normalises it;
  *     2 the composed path: a separate addition kernel, then the LayerNorm.
@@ -312,12 +318,14 @@ gpt2_status gpt2_set_fusion(gpt2_model* m, int32_t fusion, int32_t mode);
  * gpt2_probe_read synchronises and reports (host pointers, each optional)
  * totals since the last reset. */
 typedef enum gpt2_kclass {
-  GPT2_K_GEMM_FWD = 0,       /* x W^T + bias (+ residual): one kernel */
+  GPT2_K_GEMM_FWD = 0,       /* x W^T + bias (+ residual): one kernel; a split
+                                projection's fp32 slices are summed under
+                                GPT2_K_LAYERNORM */
   GPT2_K_GEMM_FWD_GELU = 1,  /* x W^T + bias with the GELU epilogue */
-  GPT2_K_GEMM_DX = 2,        /* dY W */
+  GPT2_K_GEMM_DX = 2,        /* dY W (or split slices, likewise) */
   GPT2_K_GEMM_DX_GELU = 3,   /* dY W times GELU'(pre-activation) */
-  GPT2_K_GEMM_DW = 4,        /* dY^T X into fp32 gradients (or split slices);
-                                the LM head's, and the single-block path's */
+  GPT2_K_GEMM_DW = 4,        /* dY^T X into fp32 gradients (or split slices):
+                                the LM head's */
   GPT2_K_ATTN_FWD = 5,
   GPT2_K_ATTN_BWD = 6,       /* dQ (which also computes D), then dK/dV */
   GPT2_K_LAYERNORM = 7,      /* forward and backward */
@@ -325,7 +333,8 @@ typedef enum gpt2_kclass {
   GPT2_K_OPTIMIZER = 9,      /* norm, clip coefficient and AdamW */
   GPT2_K_OTHER = 10,         /* embedding, reductions, casts */
   GPT2_K_GEMM_DW_GROUPED = 11, /* every block weight gradient of a backward
-                                  pass in one grouped launch */
+                                  pass, or of one block in isolation, in one
+                                  grouped launch */
   GPT2_K_COUNT = 12
 } gpt2_kclass;
 

@@ -140,7 +140,7 @@ enum {
   QWEN3_K_NORM = 5,          /* RMSNorm forward/backward, q/k head norm + rotary forward/backward */
   QWEN3_K_CROSS_ENTROPY = 6,
   QWEN3_K_OPTIMIZER = 7,     /* norm, clip coefficient and AdamW */
-  QWEN3_K_OTHER = 8,         /* embedding gather, SwiGLU, scales, reductions */
+  QWEN3_K_OTHER = 8,         /* embedding gather, SwiGLU, adapter transposes, reductions */
   QWEN3_K_COUNT = 9
 };
 gpt2_status qwen3_probe_enable(qwen3_model* m, uint32_t class_mask);

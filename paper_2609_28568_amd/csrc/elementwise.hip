@@ -494,8 +494,9 @@ __global__ __launch_bounds__(256) void clip_coef_kernel(const float* __restrict_
 // flight at a time. A segment shorter than the grid starts on the block that
 // its offset in the flat buffer falls to, so that the segments of a small model
 // go to different blocks instead of one block after another (135 K parameters
-// in 16 segments: 15.4 -> 7.5 us; the long segments of the 124M model ran
-// 669 -> 728 us when they were shifted too). Segment ends are multiples of 4 (checked at launch).
+// in 16 segments: 15.4 -> 7.5 us; with the long segments of the 124M model
+// shifted too it took 695 us, 635 without). Segment ends are multiples of 4
+// (checked at launch).
 __global__ __launch_bounds__(256) void adamw_kernel(AdamArgs a) {
   const float coef = a.norm_coef[1];
   const long stride = (long)gridDim.x * 256 * 4;

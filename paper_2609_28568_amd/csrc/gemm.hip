@@ -832,7 +832,11 @@ static long config_tiles(const GemmConfig& c, int M, int N) {
 // 203 x 768 x 3072 36.7 -> 14.0 (5.6 split 8 ways), 1024 x 3072 x 768
 // 14.3 -> 10.8, 1024 x 768 x 3072 37.7 -> 14.4, 4096 x 768 x 3072
 // 38.1 -> 29.4. Products of 256 to 511 tiles were timed too: the larger tiles
-// stay ahead there (4096 x 2304 x 768: 22.1 against 25.7).
+// stay ahead there (4096 x 2304 x 768: 22.1 against 25.7). Outside the widths
+// and contractions of the fit the rule is an extrapolation, checked by whole
+// passes against the large tiles only: blocks, logits, losses and steps 64 to
+// 2048 wide, 1 to 16,384 rows, contractions to 151,936 (the head's input
+// gradient), 416 of them, none slower than the runs' spread for it.
 struct SmallTile {
   GemmConfig c;
   double base, t1, t2;
@@ -884,7 +888,8 @@ GemmConfig gemm_config(int M, int N, int K, int a_t, int b_t, int epi) {
 // consumer) instead of 4 in all; 6 TB/s is what they move at while they stay
 // in the caches. A split has to promise a quarter of the time, since near 1000
 // rows the smaller promises were not kept; products with at least 256 tiles
-// of their own are not split. Measured (us, product alone): 203 x 768 x 768
+// of their own are not split. It extrapolates as the rule above does.
+// Measured (us, product alone): 203 x 768 x 768
 // 5.6 -> 3.6 (4 splits), 203 x 768 x 3072 14.0 -> 5.8 (4), 1024 x 768 x 3072
 // 14.4 -> 11.1 (4, which the consumer's reads use up: not split).
 int gemm_slices(int M, int N, int K, int K2, int b_t, int* k_chunk) {
@@ -1027,7 +1032,8 @@ hipError_t launch_gemm_grouped(const GemmGroupedArgs& gg, hipStream_t s) {
     if ((size_t)(gg.K + 256) * gr.lda * 2 >= (1ull << 32) || (size_t)(gg.K + 256) * gr.ldb * 2 >= (1ull << 32))
       return hipErrorInvalidValue;
   }
-  if (gg.nfull != 0 && (gg.nfull < 0 || gg.nfull % 8 || gg.nfull != tiles - last || last % 8)) return hipErrorInvalidValue;
+  if (gg.nfull != 0 && (gg.nfull < 0 || gg.nfull % 8 || gg.nfull != tiles - last || last % 8))
+    return hipErrorInvalidValue;
   if (c192) return launch_grouped_t<192, 192, 32>(gg, s);
   return c.bm == 256 ? launch_grouped_t<256, 128, 32>(gg, s) : launch_grouped_t<128, 128, 32>(gg, s);
 }

@@ -84,8 +84,8 @@ void kind_sizes(const Dims& d, size_t n[K_NKIND]) {
 const bool kDecay[K_NKIND] = {true, true, false, false, true, false, true, false,
                               false, false, true, false, true, false, false, false};
 
-// contraction splits for a weight-gradient GEMM with an M x N output
-// output tiles of the weight-gradient GEMM (the tile shape gemm.hip picks)
+// output tiles of a weight-gradient GEMM with an M x N output (the tile shape
+// gemm.hip picks)
 long dw_tiles(int M, int N) {
   const GemmConfig c = gemm_config(M, N, 0, 1, 1, EPI_F32);
   return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
@@ -561,9 +561,9 @@ hipError_t reduce_ln_parts(Model* m) {
 // LayerNorm backward into the residual-stream gradient: dres_out = (has_res ?
 // dres_in : 0) + dx; also writes the gain and shift gradients and, when dbias
 // is given, the column sum of the new residual gradient (the bias gradient of
-// the projection that produced it). The partial sums go to slot `slot` of the LayerNorm partials and their
-// reduction is queued for reduce_ln_parts. dy: the bf16 gradient, unless sl
-// holds it as slices.
+// the projection that produced it). The partial sums go to slot `slot` of the
+// LayerNorm partials and their reduction is queued for reduce_ln_parts. dy: the
+// bf16 gradient, unless sl holds it as slices.
 hipError_t ln_bwd(Model* m, const bf16_t* dy, const Slices& sl, const bf16_t* x, const float* mean, const float* rstd,
                   const float* w, const bf16_t* dres_in, bf16_t* dres_out, int has_res, float* dw, float* db,
                   float* dbias, int accumulate, int slot) {

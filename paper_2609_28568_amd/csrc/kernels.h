@@ -216,7 +216,9 @@ struct ReduceSeg {
 struct ReduceSegs {
   ReduceSeg s[REDUCE_SEGS];
   int count;
-  void add(const float* src, int slices, long stride, float* dst, long n) { s[count++] = {src, dst, n, stride, slices}; }
+  void add(const float* src, int slices, long stride, float* dst, long n) {
+    s[count++] = {src, dst, n, stride, slices};
+  }
 };
 hipError_t launch_reduce_segs(const ReduceSegs& r, int accumulate, hipStream_t s);
 // Sums over S slices of partial rows, for narrow rows and many slices: job j
@@ -276,11 +278,13 @@ hipError_t launch_rmsnorm_fwd(const bf16_t* x, const bf16_t* w, bf16_t* y, float
 hipError_t launch_slices_rmsnorm_fwd(const Slices& sl, const bf16_t* res, bf16_t* xsum, const bf16_t* w, bf16_t* y,
                                      float* rstd, int rows, int C, float eps, hipStream_t s);
 // dres_out = (accumulate ? dres_in : 0) + the RMSNorm input gradient (the gain
-// is frozen) over all rows of x (dres_in may be dres_out); dy (a bf16 array, or with slices.n > 0 fp32 slices) and rstd hold only the rows of positions t >= mask_from, compacted as
-// launch_rmsnorm_fwd writes them; the other rows get a zero gradient
-hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* rstd, const bf16_t* w,
-                              const bf16_t* dres_in, bf16_t* dres_out, int accumulate, int rows, int C, int T,
-                              int mask_from, hipStream_t s);
+// is frozen) over all rows of x (dres_in may be dres_out); dy (a bf16 array, or
+// with slices.n > 0 fp32 slices) and rstd hold only the rows of positions t >=
+// mask_from, compacted as launch_rmsnorm_fwd writes them; the other rows get a
+// zero gradient
+hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const Slices& slices, const bf16_t* x, const float* rstd,
+                              const bf16_t* w, const bf16_t* dres_in, bf16_t* dres_out, int accumulate, int rows,
+                              int C, int T, int mask_from, hipStream_t s);
 // raw q|k|v [BT][(H + 2 Hkv) hd] -> packed q|k|v in the same layout for the
 // grouped-query attention kernels: query and key heads RMS-normalised and
 // rotated, value heads copied; rstd of every q and k head saved

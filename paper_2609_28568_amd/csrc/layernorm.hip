@@ -259,7 +259,8 @@ __global__ void residual_add_kernel(const bf16_t* __restrict__ res, const bf16_t
 
 template <int MAXCH>
 hipError_t fwd_t(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
-                 const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s, bf16_t* xcopy) {
+                 const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s,
+                 bf16_t* xcopy) {
   const dim3 grid((rows + 3) / 4), block(256);
   if (sl.n > 0)
     hipLaunchKernelGGL((ln_fwd_kernel<MAXCH, SRC_SLICES>), grid, block, 0, s, nullptr, sl, bias, res, xsum, w, b, y,
@@ -274,7 +275,8 @@ hipError_t fwd_t(const bf16_t* x, const Slices& sl, const float* bias, const bf1
 }
 
 hipError_t fwd(const bf16_t* x, const Slices& sl, const float* bias, const bf16_t* res, bf16_t* xsum, const float* w,
-               const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s, bf16_t* xcopy) {
+               const float* b, bf16_t* y, float* mean, float* rstd, int rows, int C, float eps, hipStream_t s,
+               bf16_t* xcopy) {
   if (C <= 256) return fwd_t<1>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
   if (C <= 512) return fwd_t<2>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);
   if (C <= 768) return fwd_t<3>(x, sl, bias, res, xsum, w, b, y, mean, rstd, rows, C, eps, s, xcopy);

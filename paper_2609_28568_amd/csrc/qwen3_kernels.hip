@@ -40,8 +40,9 @@ DEV int loss_index(int p, int T, int mask_from) {
 template <int MAXCH, bool SL>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restrict__ x, Slices sl,
                                                           const bf16_t* __restrict__ res, bf16_t* __restrict__ xsum,
-                                                          const bf16_t* __restrict__ w, bf16_t* __restrict__ y, float* __restrict__ rstd_out,
-                                                          int rows, int C, float eps, int T, int mask_from) {
+                                                          const bf16_t* __restrict__ w, bf16_t* __restrict__ y,
+                                                          float* __restrict__ rstd_out, int rows, int C, float eps,
+                                                          int T, int mask_from) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -100,7 +101,8 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
                                                           const bf16_t* __restrict__ x,
                                                           const float* __restrict__ rstd_in,
                                                           const bf16_t* __restrict__ w, const bf16_t* dres_in,
-                                                          bf16_t* dres_out, int accumulate, int rows, int C, int T, int mask_from) {
+                                                          bf16_t* dres_out, int accumulate, int rows, int C, int T,
+                                                          int mask_from) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
