@@ -1,8 +1,10 @@
 // Host check of the grouped weight-gradient plans: for every width, depth and
 // token count below, the launch that grouped_weight_grads would make writes
 // its bias rows and contraction slices inside the workspace areas laid out for
-// them, and the reduction after it reads exactly what was written. The launches
-// are replaced by recorders; no GPU is touched and no pointer is followed.
+// them, and the reduction after it reads exactly what was written; its tile is
+// one that the launch takes, and a split tail is the launch's last tiles. The
+// launches are replaced by recorders; no GPU is touched and no pointer is
+// followed.
 #include "../../paper_2609_28568_amd/csrc/gpt2.cpp"
 
 #include <cstdio>
@@ -28,7 +30,7 @@ static const ReduceSeg* seg_of(const float* src) {
 int main() {
   int checked = 0, bad = 0;
   for (int C = 64; C <= 2048; C += 64)
-    for (int F : {64, C, 2 * C, 3 * C, 4 * C - 64, 4 * C, 4 * C + 64, 5376})
+    for (int F : {64, C, 2 * C, C * 8 / 3 / 64 * 64 + 64, 3 * C, 4 * C - 64, 4 * C, 4 * C + 64, 5376})
       for (int L : {1, 2, 4, 7, 12})
         for (int T : {1, 65, 130, 999, 2048, 4096, 16384}) {
           gpt2_config c{};
@@ -59,6 +61,15 @@ int main() {
           for (int isolated = 0; isolated < 2; ++isolated) {
             const bf16_t* dy = isolated ? static_cast<const bf16_t*>(at(8ull << 44)) : nullptr;
             if (grouped_weight_grads(&m, isolated ? L - 1 : 0, isolated ? 1 : L, 0, dy) != GPT2_OK) return 2;
+            long tiles = 0, last = 0;
+            for (int i = 0; i < g_launch.ngroups; ++i) {
+              const GemmGroup& gr = g_launch.grp[i];
+              const int bm = g_launch.bm, bn = g_launch.bn;
+              last = (long)((gr.M + bm - 1) / bm) * ((gr.N + bn - 1) / bn) * gr.count * std::max(gr.splits, 1);
+              tiles += last;
+              if (bm == 192 ? bn != 192 || gr.M % 192 || gr.N % 192 : bn != 128 || (bm != 128 && bm != 256)) return 3;
+            }
+            if (g_launch.nfull && (g_launch.nfull != tiles - last || g_launch.nfull % 8 || last % 8)) return 4;
             for (int i = 0; i < g_launch.ngroups; ++i) {
               const GemmGroup& gr = g_launch.grp[i];
               const int chunks = gr.splits > 1 ? gr.splits : 1;
@@ -67,17 +78,19 @@ int main() {
                 const int rows = chunks * gemm_grouped_bias_parts(g_launch, i);
                 const ReduceSeg* s = seg_of(gr.bsum);
                 if (!fits(gr.bsum, (size_t)rows * gr.count * gr.M)) what = "bias rows outside their area";
-                else if (!s || s->slices != rows || s->stride != (long)gr.count * gr.M) what = "bias rows not all summed";
+                else if (!s || s->slices != rows || s->stride != (long)gr.count * gr.M)
+                  what = "bias rows not all summed";
               }
               if (!what && chunks > 1) {
                 const ReduceSeg* s = seg_of(static_cast<const float*>(gr.C));
-                if (!fits(static_cast<const float*>(gr.C), (size_t)chunks * gr.split_stride)) 
+                if (!fits(static_cast<const float*>(gr.C), (size_t)chunks * gr.split_stride))
                   what = "slices outside their area";
                 else if (!s || s->slices != chunks || s->stride != gr.split_stride) what = "slices not all summed";
               }
               ++checked;
               if (what && ++bad <= 10)
-                std::printf("C %d F %d L %d T %d %s group %d: %s\n", C, F, L, T, isolated ? "isolated" : "training", i, what);
+                std::printf("C %d F %d L %d T %d %s group %d: %s\n", C, F, L, T, isolated ? "isolated" : "training", i,
+                            what);
             }
           }
         }
