@@ -302,8 +302,11 @@ double dw_plan_with(const Dims& d, int nl, const DwTile& c, DwPlan* out) {
 // else 256 x 128 where it promises to be faster than 128 x 128 over 4096 tokens
 // or more (below, prologues and epilogues count: 512 tokens, 12 layers of 512,
 // 136 us against 129; 2048 tokens, 2048 x 5120, 231 against 224). The times of
-// the 128-row tiles are those of launches of several rounds: 2048 wide on 16,384
-// tokens, 3 rounds of 256 x 128 in 1565 us, 6 of 128 x 128 in 2111.
+// the 128-column tiles come from launches of several rounds, reductions included:
+// one 2048-wide block, 3 rounds of 256 x 128 in 1565 us on 16,384 tokens and 475 on
+// 4096, 6 of 128 x 128 in 2111 and 529; with a last round of one tile a CU, one
+// 1280-wide block on 4096 tokens, 600 tiles of 256 x 128 in 254, 1200 of 128 x 128
+// in 236. Those of 192 x 192 come from one 768-wide block (above).
 // One block's backward on 16,384 tokens, us (four launches, each with a tile and
 // split of its own -> one launch with 128 x 128 tiles unsplit -> now):
 //   704 x 1408 638 -> 709 -> 563, 768 x 2048 673 -> 734 -> 622, 640 x 2560 695 ->
